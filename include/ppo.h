@@ -9,8 +9,9 @@
  *     gamma_s = t[c_s - 1] / B[order[s-1]][order[s]]      s = 1..k-1          (Eq. 3)
  *     beta    = max_s gamma_s                              (0 when k = 1)      (Eq. 2)
  * The library returns, per instance, the minimum of beta over every feasible (order, cuts) pair —
- * the true optimum that the paper's Theorem 1 bounds from below — by evaluating every one of the
- * k! node orderings with a memory-windowed min-max chain-partition DP.
+ * the true optimum that the paper's Theorem 1 bounds from below — by a memory-windowed min-max
+ * chain-partition DP, one per node ordering (all k! of them: the staged calls) or one over the sets of
+ * nodes not yet used (ppo_solve, ppo_solve_ws, ppo_solve_static, ppo_solve_subsets).
  *
  * Arithmetic (identical in the CPU oracle used by the tests):
  *     P[0] = 0, P[i+1] = P[i] + (double)m[i], accumulated in index order in binary64;
@@ -69,7 +70,8 @@ int ppo_version(void);
 /* Text for a return code (static storage; for PPO_EHIP, the last HIP error seen by this thread). */
 const char *ppo_strerror(int code);
 
-/* Which enumeration kernel ppo_solve_range (and everything built on it) launches.  Process-wide,
+/* Which enumeration kernel ppo_solve_range (and everything built on it) launches.  With AUTO the whole-search
+ * calls (ppo_solve, ppo_solve_ws, ppo_solve_static) go by subsets of nodes instead; with the others they enumerate.  Process-wide,
  * not synchronised with calls in flight on other threads; meant for tests and tuning.
  *   PPO_ENUM_AUTO     paired kernel (two orderings per lane, rows in registers, wave-uniform memory windows)
  *                     when k >= 6 and L-k+2 <= 96, otherwise the generic kernel
@@ -90,12 +92,15 @@ size_t ppo_workspace_bytes(int L, int k, int n_inst);
  *   cuts_out  [n_inst][k-1]   c_1..c_{k-1} (index of the first layer of segments 1..k-1); -1 if infeasible
  *   order_out [n_inst][k]     node hosting segment s; -1 if infeasible
  * Allocates its scratch with the stream-ordered allocator and releases it on the same stream.
- * Equivalent to ppo_prepare, ppo_init_keys, ppo_solve_range over [0, k!), ppo_finalize. */
+ * Same results as ppo_prepare, ppo_init_keys, ppo_solve_range over [0, k!), ppo_finalize, found by dynamic
+ * programming over subsets of nodes. */
 int ppo_solve(const float *t, const float *m, int L, const float *M, const float *B, int k, int n_inst,
               float *beta_out, int32_t *cuts_out, int32_t *order_out, void *stream);
 
 /* Same, with caller-supplied device scratch of at least ppo_workspace_bytes(L,k,n_inst) bytes,
- * 256-byte aligned.  The scratch may be reused once the stream has passed this call's work. */
+ * 256-byte aligned.  The scratch may be reused once the stream has passed this call's work.  Where the rows of
+ * many nodes (k >= 8) want more than was given, they are taken from the stream-ordered allocator for the length
+ * of the call; while the stream is being captured, or if there is no memory, the call makes do with what it has. */
 int ppo_solve_ws(const float *t, const float *m, int L, const float *M, const float *B, int k, int n_inst,
                  float *beta_out, int32_t *cuts_out, int32_t *order_out, void *workspace, size_t workspace_bytes,
                  void *stream);

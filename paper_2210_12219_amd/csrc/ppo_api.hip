@@ -13,6 +13,10 @@ hipError_t launch_enumerate(const Layout&, int, const void*, uint32_t, uint32_t,
 hipError_t launch_traceback(const Layout&, int, const void*, const uint64_t*, float*, int32_t*, int32_t*,
                             hipStream_t);
 void set_enumeration_variant(int);
+int enumeration_variant();
+size_t subset_slot_bytes(int L, int k);
+hipError_t launch_subset_solve(const float*, const float*, const float*, const float*, int, int, int, float*, int32_t*,
+                               int32_t*, void*, size_t, hipStream_t);
 size_t cluster_tables_bytes(int L, int n);
 bool cluster_few_supported(int L, int n, int pmax);
 size_t cluster_few_tables_bytes(int L, int n, int pmax);
@@ -101,6 +105,33 @@ int run_finalize(int L, int k, int n_inst, const void* ws, const uint64_t* best_
                 "traceback launch");
     }
     return PPO_OK;
+}
+
+// The whole search by subsets of nodes (ppo_subset.hip) with `slot_count` row areas at `slots`.
+int run_subset_solve(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
+                     float* beta_out, int32_t* cuts_out, int32_t* order_out, void* slots, size_t slot_count,
+                     hipStream_t stream) {
+    PPO_HIP(ppo::launch_subset_solve(t, m, M, B, L, k, n_inst, beta_out, cuts_out, order_out, slots, slot_count, stream),
+            "subset search launch");
+    return PPO_OK;
+}
+
+// Row areas that keep every compute unit busy: one per instance, at most as many as workgroups stay resident at once,
+// at most 1 GiB of them.
+size_t wanted_slots(size_t slot, int n_inst) {
+    size_t want = ((size_t)1 << 30) / slot;
+    if (want > 1024) want = 1024;
+    if (want > (size_t)n_inst) want = (size_t)n_inst;
+    return want;
+}
+
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -341,6 +372,39 @@ int ppo_finalize(int L, int k, int n_inst, const void* workspace, size_t workspa
                         static_cast<hipStream_t>(stream));
 }
 
+// The search on scratch of `bytes` bytes (at least ppo_workspace_bytes).  By subsets of nodes, unless a test has asked
+// for one of the enumeration kernels or no row area can be had: the rows of a workgroup lie in LDS, or in the given
+// scratch where it holds as many areas as are wanted, or in an allocation of their own where that is allowed.
+static int solve_on_scratch(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
+                            float* beta_out, int32_t* cuts_out, int32_t* order_out, void* ws, size_t bytes,
+                            bool may_allocate, hipStream_t s) {
+    if (ppo::enumeration_variant() == PPO_ENUM_AUTO) {
+        const size_t slot = ppo::subset_slot_bytes(L, k);
+        if (slot == 0) return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, nullptr, 0, s);
+        const size_t have = bytes / slot, want = wanted_slots(slot, n_inst);
+        if (have < want && may_allocate && !capturing(s)) {
+            void* slots = nullptr;
+            if (hipMallocAsync(&slots, slot * want, s) == hipSuccess) {
+                int rc = run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, slots, want, s);
+                const hipError_t e = hipFreeAsync(slots, s);
+                if (rc == PPO_OK && e != hipSuccess) rc = hip_fail(e, "hipFreeAsync (subset rows)");
+                return rc;
+            }
+            (void)hipGetLastError();   // no memory for the rows: what was given has to do
+        }
+        if (have > 0)
+            return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, have < want ? have : want, s);
+    }
+    const ppo::Layout y = ppo::Layout::make(L, k);
+    uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<unsigned char*>(ws) + tables_bytes(y, n_inst));
+    int rc = run_prepare(t, m, L, M, B, k, n_inst, ws, s);
+    if (rc) return rc;
+    PPO_HIP(ppo::launch_init_keys(keys, n_inst, s), "init_keys launch");
+    rc = run_range(L, k, n_inst, ws, 0u, ppo::factorial_u32(k), keys, false, nullptr, s);
+    if (rc) return rc;
+    return run_finalize(L, k, n_inst, ws, keys, beta_out, cuts_out, order_out, s);
+}
+
 int ppo_solve_ws(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
                  float* beta_out, int32_t* cuts_out, int32_t* order_out, void* workspace, size_t workspace_bytes,
                  void* stream) {
@@ -349,15 +413,8 @@ int ppo_solve_ws(const float* t, const float* m, int L, const float* M, const fl
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !M || !B || !beta_out || !order_out || (k > 1 && !cuts_out) || bad_workspace(workspace)) return PPO_EINVAL;
     if (workspace_bytes < ppo_workspace_bytes(L, k, n_inst)) return PPO_ENOSPC;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const ppo::Layout y = ppo::Layout::make(L, k);
-    uint64_t* keys = reinterpret_cast<uint64_t*>(static_cast<unsigned char*>(workspace) + tables_bytes(y, n_inst));
-    rc = run_prepare(t, m, L, M, B, k, n_inst, workspace, s);
-    if (rc) return rc;
-    PPO_HIP(ppo::launch_init_keys(keys, n_inst, s), "init_keys launch");
-    rc = run_range(L, k, n_inst, workspace, 0u, ppo::factorial_u32(k), keys, false, nullptr, s);
-    if (rc) return rc;
-    return run_finalize(L, k, n_inst, workspace, keys, beta_out, cuts_out, order_out, s);
+    return solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, workspace, workspace_bytes, true,
+                            static_cast<hipStream_t>(stream));
 }
 
 int ppo_solve(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
@@ -367,10 +424,16 @@ int ppo_solve(const float* t, const float* m, int L, const float* M, const float
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !M || !B || !beta_out || !order_out || (k > 1 && !cuts_out)) return PPO_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t bytes = ppo_workspace_bytes(L, k, n_inst);
+    const size_t slot = ppo::subset_slot_bytes(L, k);
+    size_t bytes = ppo_workspace_bytes(L, k, n_inst);
+    if (ppo::enumeration_variant() == PPO_ENUM_AUTO) {
+        if (slot == 0) return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, nullptr, 0, s);
+        const size_t rows = slot * wanted_slots(slot, n_inst);
+        if (rows > bytes) bytes = rows;   // whichever route it will be
+    }
     void* ws = nullptr;
     PPO_HIP(hipMallocAsync(&ws, bytes, s), "hipMallocAsync");
-    rc = ppo_solve_ws(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, bytes, stream);
+    rc = solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, bytes, false, s);
     hipError_t e = hipFreeAsync(ws, s);
     if (rc == PPO_OK && e != hipSuccess) rc = hip_fail(e, "hipFreeAsync");
     return rc;
@@ -415,7 +478,8 @@ int ppo_solve_static(const float* t, const float* m, int L, const float* M, cons
     if (rc) return rc;
     // every table a kernel reads is written by the stage before it and the keys are set by a fill kernel, so
     // whatever the previous call left in the array does not matter
-    return ppo_solve_ws(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, (size_t)PPO_STATIC_SCRATCH_BYTES, stream);
+    return solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, (size_t)PPO_STATIC_SCRATCH_BYTES,
+                            false, static_cast<hipStream_t>(stream));
 }
 
 int ppo_eval_orderings(const float* t, const float* m, int L, const float* M, const float* B, int k,

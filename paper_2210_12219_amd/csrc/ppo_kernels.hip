@@ -403,6 +403,8 @@ hipError_t launch_enumerate_grouped(const Layout& y, int n_inst, const void* ws,
 static std::atomic<int> g_enumeration_variant{0};   // read by every launch, set by tests: atomic, so that a set during a launch on another thread is a plain race-free read of either value
 void set_enumeration_variant(int v) { g_enumeration_variant.store(v, std::memory_order_relaxed); }
 
+int enumeration_variant() { return g_enumeration_variant.load(std::memory_order_relaxed); }
+
 size_t enumerate_lds_bytes(const Layout& y) { return (size_t)y.dec_off + (size_t)(y.L + 1) * kEnumThreads * 2; }
 
 // shared_prefix asks for the bounded mode of the paired or the grouped kernel where one of them applies; elsewhere

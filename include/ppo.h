@@ -183,10 +183,10 @@ int ppo_eval_orderings(const float *t, const float *m, int L, const float *M, co
  *            comp = (float)((Q[e] - Q[i]) / (double)v[j]), one rounding to binary32
  *   beta   = max over every comp_s (s = 0..k-1) and every gamma_s (s = 1..k-1, Eq. 3)
  * Everything else (memory rule, arithmetic of gamma, uniqueness of order and cuts, outputs, +inf and -1 when
- * nothing is feasible) as for ppo_solve; with w = 0 the results are those of ppo_solve bit for bit.  Every
- * ordering runs its own DP on binary32 values (a compute stage depends on both ends of its segment, so the
- * 16-bit order codes of ppo_solve do not apply); a plain path, not the tuned one.  Allocates its scratch
- * (k (L+1)^2 words per instance, mostly) with the stream-ordered allocator. */
+ * nothing is feasible) as for ppo_solve; with w = 0 the results are those of ppo_solve bit for bit.  Dynamic
+ * programming over subsets of nodes on binary32 values (a compute stage depends on both ends of a segment, so
+ * the 16-bit codes of ppo_solve do not apply).  Allocates its scratch (k 2^(k-1) rows of L words for each
+ * workgroup in flight, at most 1 GiB) with the stream-ordered allocator. */
 int ppo_solve_ct(const float *t, const float *m, const float *w, int L, const float *M, const float *v,
                  const float *B, int k, int n_inst, float *beta_out, int32_t *cuts_out, int32_t *order_out,
                  void *stream);

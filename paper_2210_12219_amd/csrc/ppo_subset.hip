@@ -24,7 +24,7 @@
 // instructions than the rows did (50 layers on 6 nodes: 65 us for 1024 instances, 43 with one wave).
 // Measured on one MI355X, per call: 256 x (L 12, k 4) 21 us (enumeration 58), 1024 x (50, 6) 43 us (163), 4096 x (96, 8)
 // 0.62 ms (23.1 ms), 37 x (127, 9) 90 us (97 ms), 1 x (64, 11) 80 us (3.2 ms).
-#include "ppo_common.h"
+#include "ppo_sets.h"
 
 namespace ppo {
 
@@ -37,41 +37,6 @@ constexpr int run_levels(int G) { return G == 1 ? kRunLevels : kRunLevels - 1; }
 constexpr int run_dwords(int G) { return run_levels(G) * 64 + 48; }
 constexpr uint32_t no_window(int G) { return (uint32_t)run_levels(G) * 256u; }   // byte offset of the first of those
 constexpr uint32_t kFinestCodes = kCodeInf - kCodeZero - 2u;   // buckets of the code
-
-// Sets of up to 12 nodes in increasing order of their size, then of their value (so that the first C(k, c) of size c
-// are those of the first k nodes), and the number of the first row of every set: rows are numbered set by set in
-// numeric order, member by member (see cluster_first_row in ppo_cluster.hip for the sum).
-struct SetTables {
-    uint32_t order[1 << PPO_MAX_K];       // set | first row << 16
-    int first[PPO_MAX_K + 2];             // first entry of every size
-    uint32_t choose[PPO_MAX_K + 1][PPO_MAX_K + 1];
-    constexpr SetTables() : order{}, first{}, choose{} {
-        for (int i = 0; i <= PPO_MAX_K; ++i) {
-            choose[i][0] = 1;
-            for (int j = 1; j <= i; ++j) choose[i][j] = choose[i - 1][j - 1] + (j <= i - 1 ? choose[i - 1][j] : 0u);
-        }
-        int at[PPO_MAX_K + 2] = {};
-        for (int c = 0; c <= PPO_MAX_K; ++c) first[c + 1] = first[c] + (int)choose[PPO_MAX_K][c];
-        for (int c = 0; c <= PPO_MAX_K + 1; ++c) at[c] = first[c];
-        uint32_t rows = 0;
-        for (uint32_t s = 0; s < (1u << PPO_MAX_K); ++s) {
-            int c = 0;
-            for (uint32_t b = s; b; b &= b - 1u) ++c;
-            order[at[c]++] = s | (rows << 16);
-            rows += (uint32_t)c;
-        }
-    }
-};
-constexpr SetTables kSetsHost = SetTables();
-__constant__ SetTables kSets = SetTables();
-static_assert((PPO_MAX_K << (PPO_MAX_K - 1)) < 65536, "a row's number fits 16 bits");
-
-__device__ __forceinline__ uint32_t row_of(uint32_t set_first_row, uint32_t mp, uint32_t j) {
-    // first row of R' + j from the first row of R' (j not in R'), then j's place among the members
-    const uint32_t below = mp & ((1u << j) - 1u);
-    const uint32_t above = (uint32_t)__popc((mp >> j) >> 1);
-    return set_first_row + (above << j) + ((j << j) >> 1) + below + (uint32_t)__popc(below);
-}
 
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {

@@ -121,3 +121,15 @@ def test_degenerate_and_bad_arguments(ppo):
     assert lib.ppo_solve_ct(p, p, None, 4, p, p, p, 2, 1, p, p, p, s) == ppo.PPO_EINVAL
     assert lib.ppo_solve_ct(p, p, p, 4, p, p, p, 5, 1, p, p, p, s) == ppo.PPO_EINVAL
     assert lib.ppo_solve_ct(p, p, p, 129, p, p, p, 5, 1, p, p, p, s) == ppo.PPO_ETOOBIG
+
+
+@pytest.mark.parametrize("L,k,n", [(1, 1, 2), (2, 2, 3), (63, 6, 3), (64, 6, 3), (65, 6, 3), (80, 5, 4), (128, 4, 3), (30, 8, 2)])
+def test_subset_search_at_the_edges_of_its_forms(ppo, L, k, n):
+    """One or two entries to a lane (64 layers), compute stages in LDS or in global memory (their number grows with L^2)."""
+    for quantised in (False, True):
+        w = W.random_instances(7000 + L, n, L, k, capacity_factor=1.4, quantised=quantised)
+        for seconds in (1.0, 100.0):
+            work, speed = W.compute_terms(w, seed=L, seconds=seconds, quantised=quantised)
+            got, ref = gpu_solve(ppo, w, work, speed), oracle(w, work, speed, CT.subset_dp)
+            assert np.array_equal(bits(got[0]), bits(ref[0]))
+            assert np.array_equal(got[2], ref[2]) and np.array_equal(got[1], ref[1][:, :k - 1])

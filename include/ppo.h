@@ -272,7 +272,7 @@ int ppo_min_sum_partition(const float *t, const float *m, int L, const float *ka
  *   cuts_out    [n_inst][L-1]   c_1..c_{p-1}, then -1 (may be NULL when L = 1)
  *   order_out   [n_inst][n]     node of every partition, then -1
  *   classes_out [n_inst]        classes the matching succeeded with; may be NULL
- * Allocates n_inst doubles of scratch with the stream-ordered allocator. */
+ * One launch, no scratch. */
 #define PPO_HEURISTIC_MAX_N 64
 int ppo_place_kpath(const float *t, const float *m, int L, const float *kappa, const float *B, int n, int n_inst,
                     int n_classes, float *beta_out, int32_t *segs_out, int32_t *cuts_out, int32_t *order_out,

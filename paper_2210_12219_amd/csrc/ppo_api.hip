@@ -33,8 +33,10 @@ hipError_t launch_cluster_tables_from_prepared(const Layout&, const void*, int, 
 hipError_t launch_min_sum_partition(const float*, const float*, int, const float*, int, int32_t*, int32_t*, double*,
                                     hipStream_t);
 hipError_t launch_valu_probe(int, int, uint32_t*, hipStream_t);
-hipError_t launch_heuristic(const float*, const float*, int, const float*, const float*, int, int, int, int, const float*,
-                            int, const int32_t*, const int32_t*, float*, int32_t*, int32_t*, int32_t*, int32_t*, hipStream_t);
+hipError_t launch_heuristic(const float*, const float*, int, const float*, const float*, int, int, int, const float*, int,
+                            float*, int32_t*, int32_t*, int32_t*, hipStream_t);
+hipError_t launch_kpath(const float*, const float*, int, const float*, const float*, int, int, int, float*, int32_t*, int32_t*,
+                        int32_t*, int32_t*, hipStream_t);
 size_t ct_tables_bytes(int L, int k);
 hipError_t launch_ct_tables(const float*, const float*, const float*, const float*, const float*, const float*, int, int,
                             int, void*, hipStream_t);
@@ -557,23 +559,14 @@ int ppo_place_kpath(const float* t, const float* m, int L, const float* kappa, c
     if (n_classes < 1) return PPO_EINVAL;
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !kappa || !B || !beta_out || !segs_out || !order_out || (L > 1 && !cuts_out)) return PPO_EINVAL;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    double* sums = nullptr;   // the partitioning step's sums: not part of this call's results
-    PPO_HIP(hipMallocAsync(reinterpret_cast<void**>(&sums), sizeof(double) * (size_t)n_inst, s), "hipMallocAsync (partition sums)");
-    hipError_t e = hipSuccess;
-    for (int first = 0; first < n_inst && e == hipSuccess; first += kInstPerLaunch) {
+    for (int first = 0; first < n_inst; first += kInstPerLaunch) {
         const int cnt = n_inst - first < kInstPerLaunch ? n_inst - first : kInstPerLaunch;
-        int32_t* cuts = cuts_out ? cuts_out + (size_t)first * (L - 1) : nullptr;
-        e = ppo::launch_min_sum_partition(t + (size_t)first * L, m + (size_t)first * L, L, kappa + first, cnt, segs_out + first,
-                                          cuts, sums + first, s);
-        if (e == hipSuccess)
-            e = ppo::launch_heuristic(t + (size_t)first * L, m + (size_t)first * L, L, kappa + first, B + (size_t)first * n * n, n,
-                                      cnt, n_classes, 0, nullptr, 0, segs_out + first, cuts, beta_out + first, segs_out + first,
-                                      cuts, order_out + (size_t)first * n, classes_out ? classes_out + first : nullptr, s);
+        PPO_HIP(ppo::launch_kpath(t + (size_t)first * L, m + (size_t)first * L, L, kappa + first, B + (size_t)first * n * n, n,
+                                  cnt, n_classes, beta_out + first, segs_out + first,
+                                  cuts_out ? cuts_out + (size_t)first * (L - 1) : nullptr, order_out + (size_t)first * n,
+                                  classes_out ? classes_out + first : nullptr, static_cast<hipStream_t>(stream)),
+                "placement heuristic launch");
     }
-    const hipError_t e2 = hipFreeAsync(sums, s);
-    PPO_HIP(e, "placement heuristic launch");
-    PPO_HIP(e2, "hipFreeAsync (partition sums)");
     return PPO_OK;
 }
 
@@ -590,9 +583,9 @@ int ppo_place_baseline(const float* t, const float* m, int L, const float* kappa
     for (int first = 0; first < n_inst; first += kInstPerLaunch) {
         const int cnt = n_inst - first < kInstPerLaunch ? n_inst - first : kInstPerLaunch;
         PPO_HIP(ppo::launch_heuristic(t + (size_t)first * L, m + (size_t)first * L, L, kappa + first, B + (size_t)first * n * n, n,
-                                      cnt, 1, kind, draws ? draws + (size_t)first * n_draws : nullptr, n_draws, nullptr, nullptr,
+                                      cnt, kind, draws ? draws + (size_t)first * n_draws : nullptr, n_draws,
                                       beta_out + first, segs_out + first, cuts_out ? cuts_out + (size_t)first * (L - 1) : nullptr,
-                                      order_out + (size_t)first * n, nullptr, s),
+                                      order_out + (size_t)first * n, s),
                 "comparison system launch");
     }
     return PPO_OK;

@@ -123,3 +123,21 @@ def test_the_exact_optimum_is_never_beaten(ppo):
         heur = run_kpath(ppo, w, w.M[:, 0].copy(), 5)[0]
         torch.cuda.synchronize()
         assert (bits(exact) <= bits(heur)).all() and np.isfinite(heur).all()
+
+
+def test_placement_at_the_edges_of_its_kernel(ppo):
+    """Both forms of the kernel (up to 256 instances, and more), one to three links, full 64-bit node masks, bandwidths
+    that tie, and links whose two directions differ: the oracle's results, every one of them."""
+    for n, L, n_inst, frac, classes, kind in ((2, 6, 5, 0.6, 2, "plain"), (3, 9, 600, 0.45, 3, "plain"), (6, 24, 257, 0.2, 2, "ties"),
+                                              (6, 24, 256, 0.2, 2, "one way"), (12, 40, 520, 0.1, 4, "one way"),
+                                              (33, 65, 3, 0.06, 2, "ties"), (64, 128, 2, 0.03, 1, "plain"),
+                                              (64, 128, 2, 0.03, 6, "ties"), (63, 100, 2, 0.04, 2, "one way")):
+        w = W.cluster_mixed(n, L=L, n_inst=n_inst, seed=500 + n + n_inst)
+        rng = np.random.default_rng(n * 1000 + n_inst)
+        if kind == "ties":
+            w.B[...] = np.exp2(np.round(np.log2(np.maximum(w.B, 1e-30)))).astype(np.float32)
+        if kind == "one way":
+            w.B[...] = w.B * rng.choice(np.array([0.5, 1.0, 1.0, 3.0], np.float32), w.B.shape)
+        kappa = np.maximum(frac * w.m.sum(axis=1), w.m.max(axis=1)).astype(np.float32)
+        print(f"placement edges n={n} L={L} n_inst={n_inst} {kind}", flush=True)
+        check_kpath(ppo, w, kappa, classes, f"edges n={n} L={L} {kind}")

@@ -23,7 +23,7 @@ size_t cluster_few_tables_bytes(int L, int n, int pmax);
 size_t cluster_few_rows_bytes(int L, int n, int pmax);
 hipError_t launch_cluster_few_tables(const float*, const float*, const float*, const float*, int, int, int, int, void*, void*,
                                      hipStream_t);
-hipError_t launch_cluster_few_solve(int, int, int, int, void*, void*, float*, int32_t*, int32_t*, int32_t*, hipStream_t);
+hipError_t launch_cluster_few_solve(const float*, const float*, int, int, int, int, void*, void*, float*, int32_t*, int32_t*, int32_t*, hipStream_t);
 size_t cluster_rows_bytes(int L, int n);
 hipError_t launch_cluster_tables(const float*, const float*, const float*, const float*, int, int, int, void*,
                                  hipStream_t);
@@ -341,7 +341,7 @@ int ppo_solve_cluster_few(const float* t, const float* m, int L, const float* M,
         PPO_HIP(ppo::launch_cluster_few_tables(t + first * L, m + first * L, M + first * n, B + first * n * n, L, n, pmax, cnt,
                                                ws + tables * first, row_area, s),
                 "cluster tables launch");
-        PPO_HIP(ppo::launch_cluster_few_solve(L, n, pmax, cnt, ws + tables * first, row_area, beta_out + first,
+        PPO_HIP(ppo::launch_cluster_few_solve(t + first * L, B + first * n * n, L, n, pmax, cnt, ws + tables * first, row_area, beta_out + first,
                                               segs_out + first, cuts_out ? cuts_out + first * (size_t)(n - 1) : nullptr,
                                               order_out + first * (size_t)n, s),
                 "cluster DP launch");

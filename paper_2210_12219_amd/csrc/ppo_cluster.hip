@@ -31,6 +31,19 @@ static_assert((int)kClZero + (PPO_CLUSTER_MAX_N * (PPO_CLUSTER_MAX_N - 1) / 2) *
 static_assert(((unsigned long long)PPO_CLUSTER_MAX_N << (PPO_CLUSTER_MAX_N - 1)) * ((PPO_MAX_L + 1) / 2) < (1ull << 32),
               "the dwords of one instance's rows are counted in 32 bits");
 
+// How the level kernel lays rows over lanes: chains of up to 63 layers (their rows with the entry of the chain's end fit 32
+// lanes of two entries) go two sets to a wave; up to 127 one set; 128 layers one set, with an entry beyond the lanes.
+enum { kClTwoSets = 0, kClOneSet = 1, kClWide = 2 };
+__host__ __device__ constexpr int cluster_mode(int L) { return L <= 63 ? kClTwoSets : L <= 127 ? kClOneSet : kClWide; }
+__host__ __device__ constexpr int cluster_sets_per_wave(int mode) { return mode == kClTwoSets ? 2 : 1; }
+// Run minima of a wave: rows of kClRunPitch dwords for runs of 2^0, 2^1 .. entries, then entries that are +inf, for windows
+// that are empty (two sets: the second one's lie 32 dwords on).
+__host__ __device__ constexpr int cluster_run_pitch(int mode) { return mode == kClWide ? 80 : 64; }
+__host__ __device__ constexpr int cluster_run_levels(int mode) { return mode == kClTwoSets ? 6 : 7; }
+__host__ __device__ constexpr int cluster_run_dwords(int mode) {
+    return cluster_run_levels(mode) * cluster_run_pitch(mode) + (mode == kClTwoSets ? 36 : 4);
+}
+
 struct ClusterLayout {
     int L, n, npairs, nq, rs;                       // rs: entries per row of A: 0..L-1 (entry L is never finite
                                                     // and not stored), rounded up to even
@@ -54,16 +67,23 @@ struct ClusterLayout {
         off = align_up(off + (size_t)y.nq * 4, 16);
         y.ord_off = (uint32_t)off;   // the layers 0 .. L-2 in increasing order of t (one byte each)
         off = align_up(off + (size_t)L, 256);
-        // what the level kernel keeps in LDS, ready to be copied: quotient rows of every ordered pair (rs / 2
-        // dwords each, the pitch of the rows of A), then the window queries of every (node, entry) (128 dwords
-        // per node)
+        // what the level kernel keeps in LDS, ready to be copied: quotient rows (rs / 2 dwords each, the pitch of the rows
+        // of A), then the window queries of every (node, entry); and the longest run that a query asks for
         y.img_off = (uint32_t)off;
-        off = align_up(off + q_image_bytes(n, y.rs) + (size_t)n * 512, 256);
+        off = align_up(off + y.q_image_bytes() + y.query_bytes() + 16, 256);
         y.stride = (uint32_t)off;
         return y;
     }
-    // bytes of the quotient rows in the LDS image (the window queries follow, 16-byte aligned)
-    __host__ __device__ static size_t q_image_bytes(int n, int rs) { return align_up((size_t)n * n * (rs / 2) * 4, 16); }
+    // bytes of the quotient rows in the LDS image (the window queries follow, 16-byte aligned): two sets to a wave, of
+    // every ordered pair, so that a lane finds the row of (j, j'') by one addition; one set, of every pair a < b, at
+    // pair_row (half the space, and the offset is the wave's)
+    __host__ __device__ size_t q_image_bytes() const {
+        return align_up((size_t)(cluster_mode(L) == kClTwoSets ? n * n : npairs) * (rs / 2) * 4, 16);
+    }
+    __host__ __device__ size_t query_bytes() const { return (size_t)n * (128 / cluster_sets_per_wave(cluster_mode(L))) * 4; }
+    // pair a < b is row below(b) + a.  below(j) + m > below(m) + j for m < j, so that the larger of the two is the row of
+    // the pair in either order (the value for node 0, which is never the larger one, is chosen for that).
+    __host__ __device__ static constexpr int below(int b) { return b ? (int)((uint32_t)(b * (b - 1)) >> 1) : -2; }
     // rows A[R][j] exist for j in R only: n 2^(n-1) of them per instance
     __host__ __device__ size_t rows_per_instance() const { return (size_t)n << (n - 1); }
     __host__ __device__ size_t rows_bytes() const { return rows_per_instance() * (size_t)rs * sizeof(uint16_t); }
@@ -105,11 +125,14 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
     unsigned char* hi = base + y.hi_off;
     float* dec = reinterpret_cast<float*>(base + y.dec_off);
     float* qv = reinterpret_cast<float*>(base + y.qv_off);
+    __shared__ float m_s[PPO_MAX_L];
+    for (int i = tid; i < L; i += kClPreThreads) m_s[i] = mi[i];
+    __syncthreads();
     if (tid == 0) {
         double acc = 0.0;
         P[0] = 0.0;
         for (int i = 0; i < L; ++i) {
-            acc = acc + (double)mi[i];
+            acc = acc + (double)m_s[i];
             P[i + 1] = acc;
         }
         dec[0] = 0.0f;
@@ -118,9 +141,12 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
     for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) {
         const int j = idx / (L + 1), e = idx - j * (L + 1);
         const double cap = (double)Mi[j];
-        int e2 = e;
-        while (e2 < L && (P[e2 + 1] - P[e]) <= cap) ++e2;
-        hi[idx] = (unsigned char)e2;
+        int lo = e, top = L;   // the last end that fits; P does not decrease
+        while (lo < top) {
+            const int mid = (lo + top + 1) >> 1;
+            if ((P[mid] - P[e]) <= cap) lo = mid; else top = mid - 1;
+        }
+        hi[idx] = (unsigned char)lo;
     }
     // The quotients of one link, t[i] / B, are in the order of the t[i] (a correctly rounded division by a
     // positive number is monotone), so each link's row is written sorted: position r holds the quotient of the
@@ -138,31 +164,34 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
         base[y.ord_off + pos] = (unsigned char)i;
     }
     __syncthreads();
-    for (int idx = tid; idx < y.nq; idx += kClPreThreads) {
-        const int p = idx / (L - 1), r = idx - p * (L - 1);
+    // a wave per link
+    for (int p = tid >> 6; p < y.npairs; p += kClPreThreads / 64) {
         int a = 0, rem = p;
         while (rem >= n - 1 - a) { rem -= n - 1 - a; ++a; }
-        const int b = a + 1 + rem;
-        qv[idx] = __fdiv_rn(t_s[ord_s[r]], Bi[a * n + b]);
+        const float bw = Bi[a * n + a + 1 + rem];
+        for (int r = tid & 63; r < L - 1; r += 64) qv[p * (L - 1) + r] = __fdiv_rn(t_s[ord_s[r]], bw);
     }
 }
 
-// Order codes: grid.x slices of 256 quotients, grid.y = instance.  All sorted rows are staged in LDS; a thread
-// adds up, over the links, how many of a link's quotients are strictly below its own (a binary search each).
-constexpr int kClCountThreads = 256;
+// Order codes: grid.x slices of 256 quotients, grid.y = instance.  All sorted rows are staged in LDS; four threads per
+// quotient add up, over a quarter of the links each, how many of a link's quotients are strictly below it (a binary
+// search each).  Serial searches bound it, and slices are few (75 at 20 nodes and 100 layers): one thread per quotient
+// took 54 us there.
+constexpr int kClCountSlice = 256, kClCountParts = 4, kClCountThreads = kClCountSlice * kClCountParts;
 __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterLayout y, unsigned char* __restrict__ ws) {
-    extern __shared__ __align__(16) float cl_rows[];   // [npairs][L-1]
+    extern __shared__ __align__(16) float cl_rows[];   // [npairs][L-1], then the sums of the slice
     const int L = y.L, nq = y.nq, len = L - 1, inst = blockIdx.y, tid = threadIdx.x;
     unsigned char* base = ws + (size_t)inst * y.stride;
     const float* __restrict__ qv = reinterpret_cast<const float*>(base + y.qv_off);
+    int* below_s = reinterpret_cast<int*>(cl_rows + nq);
     for (int i = tid; i < nq; i += kClCountThreads) cl_rows[i] = qv[i];
+    if (tid < kClCountSlice) below_s[tid] = 0;
     __syncthreads();
-    const int idx = blockIdx.x * kClCountThreads + tid;
-    if (idx >= nq) return;
-    const float x = cl_rows[idx];
+    const int mine = tid & (kClCountSlice - 1), idx = blockIdx.x * kClCountSlice + mine;
+    const float x = cl_rows[idx < nq ? idx : nq - 1];
     int below = 0;
     // four links at a time, so that four reads are in flight at every step of the searches
-    for (int p0 = 0; p0 < y.npairs; p0 += 4) {
+    for (int p0 = 4 * (tid / kClCountSlice); p0 < y.npairs; p0 += 4 * kClCountParts) {
         int pos[4] = {0, 0, 0, 0};   // number of entries of each row below x
         const float* row[4];
 #pragma unroll
@@ -184,6 +213,10 @@ __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterL
 #pragma unroll
         for (int u = 0; u < 4; ++u) below += p0 + u < y.npairs ? pos[u] : 0;
     }
+    atomicAdd(&below_s[mine], below);
+    __syncthreads();
+    if (tid >= kClCountSlice || idx >= nq) return;
+    below = below_s[mine];
     const int p = idx / len, r = idx - p * len;
     const int i = base[y.ord_off + r];
     reinterpret_cast<uint16_t*>(base + y.qc_off)[p * L + i] = (uint16_t)(kClZero + 1 + below);
@@ -192,17 +225,16 @@ __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterL
 
 // ---------------------------------------------------------------------------------------------
 // One level: every row A[R][j] with |R| = level.  The unit of work of a wave is a set R' with |R'| =
-// level - 1: it loads the rows A[R'][j''] once (two entries per lane) and produces A[R' + j][j] for every
-// j outside R'.  For each j: the `rest` row (quotients from a copy of the table in LDS, shifted so that
-// entry e holds q[e-1]), then a table of minima over runs of 1, 2, 4 .. 64 entries of it in LDS, from which
-// the minimum over the window (e, hi[j][e]] is two reads.  grid.x waves share the sets, grid.y = instance.
+// level - 1 (two of them on chains of up to 63 layers, 32 lanes each): it loads the rows A[R'][j''] once (two
+// entries per lane) and produces A[R' + j][j] for every j outside R'.  For each j: the `rest` row (quotients
+// from a copy of the table in LDS, shifted so that entry e holds q[e-1]), then a table of minima over runs of
+// 1, 2, 4 .. entries of it in LDS, as far as the longest window needs them, from which the minimum over the
+// window (e, hi[j][e]] is two reads.  grid.x workgroups share the sets, grid.y = instance.
+//
+// What bounds it: a row is a chain of dependent LDS and vector steps, about 55 vector instructions at ten links, so the
+// number of rows in flight counts: the quotients of unordered pairs and run tables without padding let two workgroups
+// of 16 waves share a compute unit at 20 nodes and 100 layers.
 // ---------------------------------------------------------------------------------------------
-constexpr int kClRunLevels = 7;    // runs of 2^0 .. 2^6 entries
-constexpr int kClRunRow = 160;     // entries per run-minimum row: 128 computed per set, the rest constant
-static_assert(kClRunRow / 2 >= 64 + (1 << (kClRunLevels - 3)) && kClRunRow % 2 == 0,
-              "the longest runs (2^(levels-1) entries) are built from dwords up to 2^(levels-3) beyond a lane's own");
-constexpr int kClQueryRow = 128;   // window queries per node in LDS: one dword per entry e
-
 typedef unsigned short cl_ushort2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t cl_pk_min(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(cl_ushort2, a), __builtin_bit_cast(cl_ushort2, b)));
@@ -241,27 +273,27 @@ __device__ __forceinline__ uint32_t cluster_set_at(uint32_t index, int size, int
     return set;
 }
 
-// LDS of the level kernel: the quotient rows of every ORDERED pair of nodes, rs / 2 dwords each (so that the row
-// of (j, j'') is a fixed distance from the row of (j, 0); lanes beyond a row read on into the next one, or into
-// the queries after the last, and drop what they read), the window queries of every (node, entry), and the
-// run-minimum tables of each wave.
+// LDS of the level kernel: the image (quotient rows; lanes beyond a row read on into the next one, or into the queries
+// after the last, and drop what they read; then the window queries), and the run minima of each wave.
 struct ClusterLds {
-    uint32_t hi_off, run_off, total;
+    uint32_t query_off, run_off, total;
     int waves;
     __host__ __device__ static ClusterLds make(const ClusterLayout& y, int waves) {
         ClusterLds s;
         s.waves = waves;
-        s.hi_off = (uint32_t)ClusterLayout::q_image_bytes(y.n, y.rs);
-        s.run_off = (uint32_t)align_up((size_t)s.hi_off + (size_t)y.n * kClQueryRow * 4, 16);
-        s.total = s.run_off + (uint32_t)waves * kClRunLevels * kClRunRow * 2;
+        s.query_off = (uint32_t)y.q_image_bytes();
+        s.run_off = s.query_off + (uint32_t)y.query_bytes();
+        s.total = s.run_off + (uint32_t)(waves * cluster_run_dwords(cluster_mode(y.L))) * 4u;
         return s;
     }
     // as many waves on a compute unit as its 160 KB of LDS allow (a row is a chain of dependent steps, so what
-    // counts is the number of rows in flight): two workgroups of 16 if they fit, else two of 8, else one of 16
+    // counts is the number of rows in flight): two workgroups of 16, 12 or 8 if they fit, else one of 16
     __host__ static ClusterLds choose(const ClusterLayout& y) {
-        const ClusterLds big = make(y, 16), small = make(y, 8);
-        if (2u * big.total <= 160u * 1024u) return big;
-        return 2u * small.total <= 160u * 1024u ? small : big;
+        for (int waves = 16; waves >= 8; waves -= 4) {
+            const ClusterLds s = make(y, waves);
+            if (2u * s.total <= 160u * 1024u) return s;
+        }
+        return make(y, 16);
     }
 };
 
@@ -271,76 +303,98 @@ __device__ __forceinline__ uint32_t cl_pk_min3(uint32_t a, uint32_t b, uint32_t 
     return r;
 }
 
+// the next larger set of as many nodes, and its first row
+__device__ __forceinline__ uint32_t cluster_next_set(uint32_t set, uint32_t& first_row) {
+    const uint32_t low = set & (0u - set), up = set + low;
+    set = (((up ^ set) >> 2) >> (__ffs(set) - 1)) | up;
+    uint32_t rows = 0, above = 0;
+    for (uint32_t bits = set; bits; ++above) {
+        const int b = 31 - __clz(bits);
+        bits ^= 1u << b;
+        rows += (above << b) + (((uint32_t)b << b) >> 1);
+    }
+    first_row = rows;
+    return set;
+}
+
 // C = |R'| = level - 1: the rows of the set's members sit in C registers, in the order of the members
-template <int C>
-__global__ __launch_bounds__(1024) void cluster_level_kernel(ClusterLayout y,
-                                                             const unsigned char* __restrict__ ws,
-                                                             uint16_t* __restrict__ rows, int pmax, int exact) {
+template <int C, int MODE>
+__global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
+                                                                const unsigned char* __restrict__ ws,
+                                                                uint16_t* __restrict__ rows, int pmax, int exact) {
     extern __shared__ __align__(16) unsigned char cl_smem[];
-    constexpr int level = C + 1, CA = C > 0 ? C : 1;
+    constexpr int level = C + 1, CA = C > 0 ? C : 1, G = cluster_sets_per_wave(MODE), kLanes = 64 / G;
+    constexpr int kPitch = cluster_run_pitch(MODE), kRuns = cluster_run_levels(MODE);
     const int L = y.L, n = y.n, rd = y.rs / 2;
-    const int inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63, hl = lane & (kLanes - 1);
+    const bool second = G == 2 && lane >= kLanes;   // lanes of the second set
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // the same in all lanes: keeps the set in scalar registers
     const int threads = blockDim.x, waves = threads >> 6;
     const ClusterLds lds = ClusterLds::make(y, waves);
     const unsigned char* base = ws + (size_t)inst * y.stride;
-    const uint32_t* q32 = reinterpret_cast<const uint32_t*>(cl_smem);
-    const uint32_t* query = reinterpret_cast<const uint32_t*>(cl_smem + lds.hi_off);
-    uint16_t* run = reinterpret_cast<uint16_t*>(cl_smem + lds.run_off) + wave * (kClRunLevels * kClRunRow);
+    const uint32_t* query = reinterpret_cast<const uint32_t*>(cl_smem + lds.query_off);
+    uint32_t* run32 = reinterpret_cast<uint32_t*>(cl_smem + lds.run_off) + wave * cluster_run_dwords(MODE);
     uint32_t* A32 = reinterpret_cast<uint32_t*>(rows) + (size_t)inst * (y.rows_per_instance() * rd);
     const bool more = n - level + 1 < pmax;   // segments up to and including this row's: n - level + 1
     // quotient rows and window queries: a straight copy of the image the tables kernels left (16 bytes a thread)
     {
         const uint4* img = reinterpret_cast<const uint4*>(base + y.img_off);
         uint4* dst = reinterpret_cast<uint4*>(cl_smem);
-        const int qrows16 = (int)(lds.hi_off / 16u);
-        const int first = more ? 0 : qrows16, count = qrows16 + n * 32;   // the quotient rows only if used
+        const int first = more ? 0 : (int)(lds.query_off / 16u), count = (int)(lds.run_off / 16u);   // the quotient rows only if used
         for (int i = first + tid; i < count; i += threads) dst[i] = img[i];
     }
-    // entries 128.. of the run-minimum rows never change: rest[L] = 0 if L = 128, +inf beyond the chain
-    for (int i = lane; i < kClRunLevels * (kClRunRow - 128); i += 64) {
-        const int k = i / (kClRunRow - 128), e = 128 + i % (kClRunRow - 128);
-        run[k * kClRunRow + e] = (uint16_t)(e == L ? kClZero : kClInf);
-    }
-    __syncthreads();
+    const int run_top = (int)*reinterpret_cast<const uint32_t*>(base + y.img_off + lds.run_off);
+    // with every node to be used (exact), the chain may end (rest[L] = 0) only after the last node
+    const bool may_end = !exact || C == 0;
     const uint32_t inf2 = kClInf | (kClInf << 16);
+    // 128 layers: entry 128 of rest follows the lanes' in every run row, +inf after it; these never change
+    const uint32_t after_last = may_end ? kClZero | (kClInf << 16) : inf2;
+    if (MODE == kClWide)
+        for (int i = lane; i < kRuns * (kPitch - 64); i += 64)
+            run32[i / (kPitch - 64) * kPitch + 64 + i % (kPitch - 64)] = i % (kPitch - 64) ? inf2 : after_last;
+    if (lane < cluster_run_dwords(MODE) - kRuns * kPitch) run32[kRuns * kPitch + lane] = inf2;
+    __syncthreads();
     const uint32_t all = (1u << n) - 1u;
-    const int e0 = 2 * lane, e1 = e0 + 1;
+    const int e0 = 2 * hl, e1 = e0 + 1;
     // rest[L] = 0: the half of entry L is cleared and set to the code of 0
-    const uint32_t end_keep = (e0 == L ? 0u : 0xFFFFu) | (e1 == L ? 0u : 0xFFFF0000u);
-    const uint32_t end_set = (e0 == L ? kClZero : 0u) | (e1 == L ? kClZero << 16 : 0u);
-    const uint32_t after_last = L == 128 ? kClZero : kClInf;   // entry 128 of rest
-    uint32_t* run32 = reinterpret_cast<uint32_t*>(run);
+    const uint32_t end_keep = !may_end ? ~0u : (e0 == L ? 0u : 0xFFFFu) | (e1 == L ? 0u : 0xFFFF0000u);
+    const uint32_t end_set = !may_end ? 0u : (e0 == L ? kClZero : 0u) | (e1 == L ? kClZero << 16 : 0u);
     // A wave takes a run of consecutive sets: the first from its index (binomial table, a chain of dependent
     // scalar loads), each further one from the one before (the next larger number with as many bits set).
     const uint32_t nsets = kClBinomials.c[n][C];
     const uint32_t total_waves = gridDim.x * waves;
-    const uint32_t per_wave = (nsets + total_waves - 1u) / total_waves;
+    const uint32_t per_wave = ((nsets + total_waves - 1u) / total_waves + (uint32_t)G - 1u) / (uint32_t)G * (uint32_t)G;
     uint32_t u = (blockIdx.x * waves + wave) * per_wave;
     const uint32_t u_end = u + per_wave < nsets ? u + per_wave : nsets;
     uint32_t mp = 0, first_row = 0;
     if (u < u_end) mp = cluster_set_at(u, C, n, first_row);
-    for (; u < u_end; ++u) {
+    for (; u < u_end; u += (uint32_t)G) {
+        const bool pair = G == 2 && u + 1u < u_end;
+        uint32_t mp2 = mp, first_row2 = first_row;
+        if (C > 0 && pair) mp2 = cluster_next_set(mp, first_row2);
         uint32_t a[CA];      // row A[R'][member m], two entries per lane
-        uint32_t moff[CA];   // dword offset of member m's quotient row from the row of (j, 0)
+        int moff[CA];        // where member m's quotient rows are: of (j, m) from those of j (bytes)
+        int mbelow[CA];      // one set to a wave: of (m, j) from those of j, if j < m (bytes)
         {
-            const uint32_t* arow = A32 + (size_t)(first_row * (uint32_t)rd) + lane;   // 32 bits hold an instance's dwords
-            uint32_t bits = mp;
+            const uint32_t mine = second ? first_row2 : first_row;
+            const uint32_t* arow = A32 + (size_t)(mine * (uint32_t)rd) + hl;   // 32 bits hold an instance's dwords
+            uint32_t bits = mp, bits2 = mp2;
 #pragma unroll
             for (int m = 0; m < C; ++m) {
-                moff[m] = (uint32_t)(__ffs(bits) - 1) * (uint32_t)rd;
+                const int b = __builtin_ctz(bits);
                 bits &= bits - 1u;
-                a[m] = (more && lane < rd) ? arow[m * rd] : inf2;
+                if (G == 2) {
+                    const int b2 = __builtin_ctz(bits2);
+                    bits2 &= bits2 - 1u;
+                    moff[m] = ((second ? b2 : b) * rd + hl) * 4;
+                } else {
+                    // held as they are: products put off into the loop below made its scalar instructions the limit
+                    // (level 11 of 20 nodes: 409 us)
+                    moff[m] = __builtin_amdgcn_readfirstlane(b * (rd * 4));
+                    mbelow[m] = __builtin_amdgcn_readfirstlane(ClusterLayout::below(b) * (rd * 4));
+                }
+                a[m] = (more && hl < rd) ? arow[m * rd] : inf2;
             }
-        }
-        // with every node to be used (exact), the chain may end (rest[L] = 0) only after the last node
-        const bool may_end = !exact || mp == 0u;
-        const uint32_t keep_here = may_end ? end_keep : 0xFFFFFFFFu, set_here = may_end ? end_set : 0u;
-        const uint32_t after_here = may_end ? after_last : kClInf;
-        if (exact && L == 128) {   // rest[L] sits in the constant part of the run-minimum rows
-            if (lane < kClRunLevels) run[lane * kClRunRow + 128] = (uint16_t)after_here;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
         }
         // Where the rows of this set go: lane j works out the dword offset of row A[R' + j][j], once per set, and
         // the loop below picks it with a lane read instead of a dozen scalar instructions per row.  The first row
@@ -349,54 +403,65 @@ __global__ __launch_bounds__(1024) void cluster_level_kernel(ClusterLayout y,
         // among the members.
         uint32_t out_off;
         {
-            const uint32_t jl = (uint32_t)lane & 31u;
-            const uint32_t below = mp & ((1u << jl) - 1u);
-            const uint32_t above = (uint32_t)__popc((mp >> jl) >> 1);
-            out_off = (first_row + (above << jl) + ((jl << jl) >> 1) + below + (uint32_t)__popc(below)) * (uint32_t)rd;
+            const uint32_t jl = (uint32_t)lane & 31u, set = second ? mp2 : mp;
+            const uint32_t below = set & ((1u << jl) - 1u);
+            const uint32_t above = (uint32_t)__popc((set >> jl) >> 1);
+            out_off = ((second ? first_row2 : first_row) + (above << jl) + ((jl << jl) >> 1) + below + (uint32_t)__popc(below)) * (uint32_t)rd;
         }
-        for (uint32_t jb = all & ~mp; jb; jb &= jb - 1u) {
-            const int j = __ffs(jb) - 1;
+        uint32_t jb = all & ~mp, jb2 = all & ~mp2;
+        for (int left = n - C; left > 0; --left) {
+            const int j = __builtin_ctz(jb), j2 = __builtin_ctz(jb2);
+            jb &= jb - 1u;
+            jb2 &= jb2 - 1u;
+            const int my_j = second ? j2 : j;
+            const uint2 qd = *reinterpret_cast<const uint2*>(query + my_j * (2 * kLanes) + e0);
             uint32_t v = inf2;
             if (more) {
-                const uint32_t* qj = q32 + (j * n) * rd + lane;
                 uint32_t x[CA];
+                if (G == 2) {
+                    const unsigned char* qj = cl_smem + my_j * (n * rd * 4);
 #pragma unroll
-                for (int m = 0; m < C; ++m) x[m] = cl_pk_max(qj[moff[m]], a[m]);
+                    for (int m = 0; m < C; ++m) x[m] = cl_pk_max(*reinterpret_cast<const uint32_t*>(qj + moff[m]), a[m]);
+                } else {
+                    const int joff = __builtin_amdgcn_readfirstlane(j * (rd * 4));
+                    const int jbelow = __builtin_amdgcn_readfirstlane(ClusterLayout::below(j) * (rd * 4));
+#pragma unroll
+                    for (int m = 0; m < C; ++m) {
+                        const int r1 = jbelow + moff[m], r2 = mbelow[m] + joff;
+                        x[m] = cl_pk_max(*reinterpret_cast<const uint32_t*>(cl_smem + lane * 4 + (r1 > r2 ? r1 : r2)), a[m]);
+                    }
+                }
 #pragma unroll
                 for (int m = 0; m + 1 < C; m += 2) v = cl_pk_min3(v, x[m], x[m + 1]);
                 if (C & 1) v = cl_pk_min(v, x[C - 1]);
             }
-            v = (v & keep_here) | set_here;
-            // minima over runs of 2^k entries starting at each entry
+            v = (v & end_keep) | end_set;
+            // minima over runs of 2^r entries starting at each entry; a run that passes the end of the row holds
+            // whatever lies there and is never asked for (wave shift left by one: lane i reads lane i + 1; the last
+            // lane of a row of 128 gets the entries after it)
+            auto up_one = [&](uint32_t x, uint32_t after) -> uint32_t {
+                return MODE == kClWide ? (uint32_t)__builtin_amdgcn_update_dpp((int)after, (int)x, 0x130, 0xF, 0xF, false)
+                                       : (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x130, 0xF, 0xF, true);
+            };
             run32[lane] = v;
-            // the dword of the next lane (wave shift left by one: lane i reads lane i + 1; lane 63 keeps the
-            // first operand, the entry after the last one)
-            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)after_here, (int)v, 0x130, 0xF, 0xF, false);
+            const uint32_t next = up_one(v, after_last);
             uint32_t cur = cl_pk_min(v, (v >> 16) | (next << 16));
-            run32[(kClRunRow / 2) + lane] = cur;
-            {
-                // runs of 4 and of 8: the dwords one and two lanes up come by wave shifts too; what enters at
-                // lane 63 are the entries 128 .. 131 of the row before, known beforehand
-                const uint32_t tail = after_here | (kClInf << 16);
-                const uint32_t up1 = (uint32_t)__builtin_amdgcn_update_dpp((int)tail, (int)cur, 0x130, 0xF, 0xF, false);
-                cur = cl_pk_min(cur, up1);
-                run32[2 * (kClRunRow / 2) + lane] = cur;
-                const uint32_t s1 = (uint32_t)__builtin_amdgcn_update_dpp((int)tail, (int)cur, 0x130, 0xF, 0xF, false);
-                const uint32_t up2 = (uint32_t)__builtin_amdgcn_update_dpp((int)inf2, (int)s1, 0x130, 0xF, 0xF, false);
-                cur = cl_pk_min(cur, up2);
-                run32[3 * (kClRunRow / 2) + lane] = cur;
-            }
+            run32[kPitch + lane] = cur;
+            cur = cl_pk_min(cur, up_one(cur, after_last));
+            run32[2 * kPitch + lane] = cur;
+            cur = cl_pk_min(cur, up_one(up_one(cur, after_last), inf2));
+            run32[3 * kPitch + lane] = cur;
 #pragma unroll
-            for (int k = 4; k < kClRunLevels; ++k) {
+            for (int r = 4; r < kRuns; ++r) {
+                if (r > run_top) break;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                cur = cl_pk_min(cur, run32[(k - 1) * (kClRunRow / 2) + lane + (1 << (k - 2))]);
-                run32[k * (kClRunRow / 2) + lane] = cur;
+                cur = cl_pk_min(cur, run32[(r - 1) * kPitch + lane + (1 << (r - 2))]);
+                run32[r * kPitch + lane] = cur;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            const uint2 qd = *reinterpret_cast<const uint2*>(query + j * kClQueryRow + e0);
-            const unsigned char* runb = reinterpret_cast<const unsigned char*>(run);
+            const unsigned char* runb = reinterpret_cast<const unsigned char*>(run32) + (second ? kLanes * 4 : 0);
             uint32_t res[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -406,20 +471,17 @@ __global__ __launch_bounds__(1024) void cluster_level_kernel(ClusterLayout y,
                 res[h] = r1 < r2 ? r1 : r2;
             }
             // row of j within R' + j: after the members below it
-            const uint32_t row_off = (uint32_t)__builtin_amdgcn_readlane((int)out_off, j);
-            if (lane < rd) A32[(size_t)row_off + lane] = res[0] | (res[1] << 16);
+            uint32_t row_off = (uint32_t)__builtin_amdgcn_readlane((int)out_off, j);
+            if (G == 2) {
+                const uint32_t row_off2 = (uint32_t)__builtin_amdgcn_readlane((int)out_off, kLanes + j2);
+                row_off = second ? row_off2 : row_off;
+            }
+            if (hl < rd && (!second || pair)) A32[(size_t)row_off + hl] = res[0] | (res[1] << 16);
             __builtin_amdgcn_wave_barrier();
         }
-        if (C > 0 && u + 1u < u_end) {
-            const uint32_t low = mp & (0u - mp), up = mp + low;
-            mp = (((up ^ mp) >> 2) >> (__ffs(mp) - 1)) | up;
-            first_row = 0;
-            uint32_t above = 0;
-            for (uint32_t bits = mp; bits; ++above) {
-                const int b = 31 - __clz(bits);
-                bits ^= 1u << b;
-                first_row += (above << b) + (((uint32_t)b << b) >> 1);
-            }
+        if (C > 0 && u + (uint32_t)G < u_end) {
+            first_row = first_row2;
+            mp = cluster_next_set(mp2, first_row);
         }
     }
 }
@@ -612,29 +674,53 @@ __global__ __launch_bounds__(256) void cluster_tables_from_prepared_kernel(Layou
 //   quotient rows: entry e of the row of (j, j''): q_{j,j''}[e-1] for 1 <= e <= L-1 (the cuts with a link), else +inf;
 //   window queries: the window (e, hi[j][e]] of node j at entry e is covered by two runs of 2^k entries, k the
 //   largest with 2^k <= its length: the one starting at e + 1 and the one ending at hi.  The table holds the byte
-//   offsets of their minima within a wave's run-minimum rows, 16 bits each; no window: twice an entry that is +inf.
+//   offsets of their minima within a wave's run minima, 16 bits each; no window: twice an entry that is +inf;
+//   last, the largest k.
 __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLayout y, unsigned char* __restrict__ ws) {
-    const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x;
+    __shared__ int top_s;
+    const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x, mode = cluster_mode(L);
+    const int pitch = cluster_run_pitch(mode), per_node = 128 / cluster_sets_per_wave(mode);
     unsigned char* base = ws + (size_t)inst * y.stride;
     const uint16_t* __restrict__ qc = reinterpret_cast<const uint16_t*>(base + y.qc_off);
     uint16_t* q16 = reinterpret_cast<uint16_t*>(base + y.img_off);
-    uint32_t* query = reinterpret_cast<uint32_t*>(base + y.img_off + ClusterLayout::q_image_bytes(n, y.rs));
-    for (int i = tid; i < (int)(ClusterLayout::q_image_bytes(n, y.rs) / 2); i += kClPreThreads) {
-        const int e = i % y.rs, jj = i / y.rs, j = jj / n, j2 = jj - j * n;   // jj = n * n: the padding
-        q16[i] = (uint16_t)((jj < n * n && j != j2 && e >= 1 && e <= L - 1) ? qc[pair_index(j, j2, n) * L + e - 1] : kClInf);
+    uint32_t* query = reinterpret_cast<uint32_t*>(base + y.img_off + y.q_image_bytes());
+    if (tid == 0) top_s = 0;
+    __syncthreads();
+    // a group of 64 threads per row
+    const int nrows = mode == kClTwoSets ? n * n : y.npairs;
+    for (int r = tid >> 6; r < nrows; r += kClPreThreads / 64) {
+        int a, b;
+        if (mode == kClTwoSets) {
+            a = r / n;
+            b = r - a * n;
+        } else {
+            b = 1;
+            while (ClusterLayout::below(b + 1) <= r) ++b;
+            a = r - ClusterLayout::below(b);
+        }
+        const uint16_t* __restrict__ q = qc + (a != b ? pair_index(a, b, n) : 0) * L;
+        for (int e = tid & 63; e < y.rs; e += 64)
+            q16[r * y.rs + e] = (uint16_t)((a != b && e >= 1 && e <= L - 1) ? q[e - 1] : kClInf);
     }
-    for (int i = tid; i < n * kClQueryRow; i += kClPreThreads) {
-        const int j = i / kClQueryRow, e = i - j * kClQueryRow;
+    for (int i = nrows * y.rs + tid; i < (int)(y.q_image_bytes() / 2); i += kClPreThreads) q16[i] = (uint16_t)kClInf;   // the padding
+    const uint32_t none = (uint32_t)(cluster_run_levels(mode) * pitch) * 4u;
+    int top_run = 0;
+    for (int i = tid; i < n * per_node; i += kClPreThreads) {
+        const int j = i / per_node, e = i - j * per_node;
         const int top = e < L ? (int)base[y.hi_off + j * (L + 1) + e] : 0;
-        uint32_t o1 = kClRunRow - 2, o2 = kClRunRow - 2;   // run row 0, beyond the chain
+        uint32_t o1 = none, o2 = none;
         if (top > e) {
             int k = 31 - __clz(top - e);
-            k = k > kClRunLevels - 1 ? kClRunLevels - 1 : k;
-            o1 = (uint32_t)(k * kClRunRow + e + 1);
-            o2 = (uint32_t)(k * kClRunRow + top - (1 << k) + 1);
+            k = k > cluster_run_levels(mode) - 1 ? cluster_run_levels(mode) - 1 : k;
+            o1 = (uint32_t)(k * pitch * 4 + (e + 1) * 2);
+            o2 = (uint32_t)(k * pitch * 4 + (top - (1 << k) + 1) * 2);
+            top_run = k > top_run ? k : top_run;
         }
-        query[i] = (o1 * 2u) | ((o2 * 2u) << 16);
+        query[i] = o1 | (o2 << 16);
     }
+    atomicMax(&top_s, top_run);
+    __syncthreads();
+    if (tid == 0) query[n * per_node] = (uint32_t)top_s;
 }
 
 hipError_t launch_cluster_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
@@ -645,8 +731,8 @@ hipError_t launch_cluster_tables(const float* t, const float* m, const float* M,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (y.nq > 0) {
-        const int slices = (y.nq + kClCountThreads - 1) / kClCountThreads;
-        const uint32_t lds_bytes = (uint32_t)y.nq * 4u;
+        const int slices = (y.nq + kClCountSlice - 1) / kClCountSlice;
+        const uint32_t lds_bytes = ((uint32_t)y.nq + (uint32_t)kClCountSlice) * 4u;
         static std::atomic<uint64_t> lds_allowed{0};
         e = allow_full_lds(reinterpret_cast<const void*>(&cluster_count_kernel), lds_allowed);
         if (e != hipSuccess) return e;
@@ -662,14 +748,22 @@ hipError_t launch_cluster_tables(const float* t, const float* m, const float* M,
 // one instantiation of the level kernel per set size
 using ClLevelLaunch = hipError_t (*)(dim3, dim3, uint32_t, hipStream_t, const ClusterLayout&, const unsigned char*,
                                      uint16_t*, int, int);
+template <int C, int MODE>
+static hipError_t cluster_launch_mode(dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, const ClusterLayout& y,
+                                      const unsigned char* ws, uint16_t* rows, int pmax, int exact) {
+    static std::atomic<uint64_t> lds_allowed{0};
+    const hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&cluster_level_kernel<C, MODE>), lds_allowed);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((cluster_level_kernel<C, MODE>), grid, block, lds_bytes, stream, y, ws, rows, pmax, exact);
+    return hipGetLastError();
+}
 template <int C>
 static hipError_t cluster_launch_level(dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, const ClusterLayout& y,
                                        const unsigned char* ws, uint16_t* rows, int pmax, int exact) {
-    static std::atomic<uint64_t> lds_allowed{0};
-    const hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&cluster_level_kernel<C>), lds_allowed);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cluster_level_kernel<C>, grid, block, lds_bytes, stream, y, ws, rows, pmax, exact);
-    return hipGetLastError();
+    const int mode = cluster_mode(y.L);
+    return mode == kClTwoSets ? cluster_launch_mode<C, kClTwoSets>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact)
+           : mode == kClOneSet ? cluster_launch_mode<C, kClOneSet>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact)
+                               : cluster_launch_mode<C, kClWide>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact);
 }
 template <int... Cs>
 static constexpr std::array<ClLevelLaunch, sizeof...(Cs)> cluster_level_table(std::integer_sequence<int, Cs...>) {
@@ -686,12 +780,12 @@ hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, bool exact, 
     const unsigned char* w = static_cast<const unsigned char*>(ws);
     uint16_t* r = static_cast<uint16_t*>(rows);
     const ClusterLds lds = ClusterLds::choose(y);
-    const uint32_t per_cu = (160u * 1024u) / lds.total;   // workgroups a compute unit holds: 1 or 2 (or more for small n)
-    const uint32_t resident = 256u * (per_cu < 1u ? 1u : per_cu > 4u ? 4u : per_cu);
+    const uint32_t resident = 256u * (2u * lds.total <= 160u * 1024u ? 2u : 1u);   // workgroups the chip holds
+    const uint32_t sets_each = (uint32_t)(lds.waves * cluster_sets_per_wave(cluster_mode(L)));
     hipError_t e = hipSuccess;
     for (int level = n - pmax + 1; level <= n; ++level) {
-        // a set per wave at most; no more workgroups than stay resident (each stages the quotient table once)
-        uint32_t blocks = (kClBinomialsHost.c[n][level - 1] + (uint32_t)lds.waves - 1u) / (uint32_t)lds.waves;
+        // no more workgroups than stay resident (each stages the quotient table once)
+        uint32_t blocks = (kClBinomialsHost.c[n][level - 1] + sets_each - 1u) / sets_each;
         const uint32_t cap = (resident + (uint32_t)n_inst - 1u) / (uint32_t)n_inst;
         if (blocks > cap) blocks = cap;
         e = kClLevelLaunch[level - 1](dim3(blocks, n_inst), dim3(lds.waves * 64), lds.total, stream, y, w, r, pmax,

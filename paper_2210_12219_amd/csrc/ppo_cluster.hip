@@ -645,29 +645,32 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
 // The tables of this file from those of the fixed-k precompute kernel (window starts lo, quotient codes from
 // kCodeZero + 1 up): hi[j][e] = last e' with lo[j][e'] <= e; codes and dec are the same.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void cluster_tables_from_prepared_kernel(Layout f, const unsigned char* __restrict__ fixed_ws,
+__global__ __launch_bounds__(kClPreThreads) void cluster_tables_from_prepared_kernel(Layout f, const unsigned char* __restrict__ fixed_ws,
                                                                            ClusterLayout y, unsigned char* __restrict__ ws) {
     const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x;
     const unsigned char* src = fixed_ws + (size_t)inst * f.stride;
     unsigned char* dst = ws + (size_t)inst * y.stride;
     __shared__ unsigned char lo[PPO_MAX_K * (PPO_MAX_L + 1)];
-    for (int idx = tid; idx < n * (L + 1); idx += 256) lo[idx] = src[f.lo_off + idx];
+    for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) lo[idx] = src[f.lo_off + idx];
     __syncthreads();
-    for (int idx = tid; idx < n * (L + 1); idx += 256) {
+    for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) {
         const int j = idx / (L + 1), e = idx - j * (L + 1);
-        int e2 = e;
-        while (e2 < L && lo[j * (L + 1) + e2 + 1] <= e) ++e2;
+        int e2 = e, top = L;   // window starts do not decrease
+        while (e2 < top) {
+            const int mid = (e2 + top + 1) >> 1;
+            if (lo[j * (L + 1) + mid] <= e) e2 = mid; else top = mid - 1;
+        }
         dst[y.hi_off + idx] = (unsigned char)e2;
     }
     const uint16_t* qsrc = reinterpret_cast<const uint16_t*>(src + f.qc_off);
     uint16_t* qdst = reinterpret_cast<uint16_t*>(dst + y.qc_off);
-    for (int idx = tid; idx < y.npairs * L; idx += 256) {
+    for (int idx = tid; idx < y.npairs * L; idx += kClPreThreads) {
         const int i = idx % L;
         qdst[idx] = (uint16_t)(i < L - 1 ? qsrc[idx] : kClInf);
     }
     const float* dsrc = reinterpret_cast<const float*>(src + f.dec_off);
     float* ddst = reinterpret_cast<float*>(dst + y.dec_off);
-    for (int idx = tid; idx <= y.nq; idx += 256) ddst[idx] = dsrc[idx];
+    for (int idx = tid; idx <= y.nq; idx += kClPreThreads) ddst[idx] = dsrc[idx];
 }
 
 // The image of the level kernel's LDS tables (needs hi and the codes): one workgroup per instance.
@@ -802,7 +805,7 @@ hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, bool exact, 
 hipError_t launch_cluster_tables_from_prepared(const Layout& f, const void* fixed_ws, int n_inst, void* ws,
                                                hipStream_t stream) {
     const ClusterLayout y = ClusterLayout::make(f.L, f.k);
-    hipLaunchKernelGGL(cluster_tables_from_prepared_kernel, dim3(n_inst), dim3(256), 0, stream, f,
+    hipLaunchKernelGGL(cluster_tables_from_prepared_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, f,
                        static_cast<const unsigned char*>(fixed_ws), y, static_cast<unsigned char*>(ws));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

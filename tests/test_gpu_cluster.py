@@ -305,3 +305,14 @@ def test_more_instances_than_one_launch_takes(ppo):
         ref = O.bruteforce(w3.t[sl], w3.m[sl], w3.M[sl], w3.B[sl])
         assert np.array_equal(bits(full[0][sl]), bits(ref[0])) and np.array_equal(full[2][sl], ref[2])
         assert np.array_equal(full[1][sl], ref[1])
+
+
+@pytest.mark.parametrize("L", [2, 3, 33, 62, 63, 64, 65, 127, 128])
+def test_cluster_rows_at_the_edges_of_a_wave(ppo, L):
+    """Chain lengths around the ones at which the layout of rows over lanes changes, windows from one layer to the whole
+    chain, an odd number of sets per wave, and a bounded number of segments."""
+    for n, cf, quantised in ((3, 3.5, False), (5, 1.3, True), (6, 2.5, False)):
+        w = W.random_instances(900 + L + n, 6, L, min(n, L), capacity_factor=cf, quantised=quantised)
+        for pmax in (2, w.k):
+            print(f"cluster edges L={L} n={w.k} pmax={pmax}", flush=True)
+            assert_same(solve(ppo, w, pmax), oracle(w, pmax, CO.exhaustive), f"cluster edges L={L} n={w.k} pmax={pmax}")

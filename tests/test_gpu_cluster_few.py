@@ -176,3 +176,21 @@ def test_workspace_size_does_not_matter_and_bad_shapes_are_refused(ppo):
         ppo.ppo_solve_cluster_few(*ppo.to_device(w), max_segments=13)
     with pytest.raises(ppo.PpoError):
         ppo.ppo_solve_cluster_few(*ppo.to_device(w), max_segments=4, workspace=torch.empty(1024, dtype=torch.uint8, device="cuda:0"))
+
+
+@pytest.mark.parametrize("L,n,pmax,n_inst,kind", [(2, 5, 2, 3, "ties"), (20, 40, 3, 3, "ties"), (63, 21, 4, 2, "loose"), (64, 33, 3, 40, "plain"),
+                                                  (127, 24, 3, 2, "ties"), (128, 64, 3, 2, "plain"), (128, 21, 2, 600, "loose")])
+def test_last_level_by_its_bound(ppo, L, n, pmax, n_inst, kind):
+    """The pruned last level against the oracle: links that all tie (every set stays within the bound), windows as long as
+    the chain (many entries to try), few instances and more of them than workgroups."""
+    w = W.cluster_mixed(n, L=L, n_inst=n_inst, seed=7 * L + n, capacity_factor=0.8 / pmax)
+    if kind == "ties":
+        w.B[...] = np.where(w.B > 0, np.float32(4.0), np.float32(0.0))
+        w.t[...] = np.float32(8.0)
+    if kind == "loose":
+        w.M[...] = (w.m.sum(axis=1) * np.float32(0.9))[:, None]
+    print(f"few bound L={L} n={n} pmax={pmax} {kind}", flush=True)
+    got = solve_few(ppo, w, pmax)
+    some = list(range(min(n_inst, 6))) + ([n_inst - 1] if n_inst > 6 else [])
+    part = Workload(w.name, L, n, len(some), w.seed, w.t[some], w.m[some], w.M[some], w.B[some])
+    assert_same(tuple(x[some] for x in got), oracle(part, pmax, CO.exhaustive), f"few bound L={L} n={n} pmax={pmax} {kind}")

@@ -178,8 +178,8 @@ def test_workspace_size_does_not_matter_and_bad_shapes_are_refused(ppo):
         ppo.ppo_solve_cluster_few(*ppo.to_device(w), max_segments=4, workspace=torch.empty(1024, dtype=torch.uint8, device="cuda:0"))
 
 
-@pytest.mark.parametrize("L,n,pmax,n_inst,kind", [(2, 5, 2, 3, "ties"), (20, 40, 3, 3, "ties"), (63, 21, 4, 2, "loose"), (64, 33, 3, 40, "plain"),
-                                                  (127, 24, 3, 2, "ties"), (128, 64, 3, 2, "plain"), (128, 21, 2, 600, "loose")])
+@pytest.mark.parametrize("L,n,pmax,n_inst,kind", [(2, 5, 2, 3, "ties"), (20, 40, 3, 3, "ties"), (63, 21, 4, 1, "loose"), (64, 33, 3, 40, "plain"),
+                                                  (127, 24, 3, 2, "ties"), (128, 64, 3, 1, "plain"), (128, 21, 2, 600, "loose")])
 def test_last_level_by_its_bound(ppo, L, n, pmax, n_inst, kind):
     """The pruned last level against the oracle: links that all tie (every set stays within the bound), windows as long as
     the chain (many entries to try), few instances and more of them than workgroups."""

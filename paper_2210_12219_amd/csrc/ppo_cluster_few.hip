@@ -39,9 +39,11 @@ __constant__ FewBinomials kFewBinomials = FewBinomials();
 
 struct FewState {
     uint32_t best, chosen, done, p, last, pad[3];
-    uint32_t first_best[kFewMaxN];           // per node j: the least G[S][j][0] of all sets so far
     unsigned long long used, F[2];
-    unsigned long long cand[kFewMaxN][2];    // G_j of every candidate of the current position
+    union {
+        uint32_t first_best[kFewMaxN];           // per node j, until position 0 is settled: the least G[S][j][0] of all sets so far
+        unsigned long long cand[kFewMaxN][2];    // then G_j of every candidate of the current position
+    };
     unsigned long long start[kFewMaxP][2];   // G of the node chosen at every position
     int32_t seq[kFewMaxP];
 };

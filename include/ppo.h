@@ -87,6 +87,11 @@ int ppo_set_enumeration(int variant);
 /* Bytes of device scratch that ppo_solve_ws / ppo_prepare need for this shape (0 on bad shape). */
 size_t ppo_workspace_bytes(int L, int k, int n_inst);
 
+/* Bytes at which ppo_solve_ws has room for the rows of every instance it would work on at once: what
+ * ppo_workspace_bytes says, or more where the rows do not fit LDS (9 nodes and more, 8 from 21 layers on, 7 from
+ * 65 on): an area of about k 2^(k-1) 2 L bytes for each instance, up to 1024 areas and 1 GiB.  0 on bad shape. */
+size_t ppo_solve_workspace_bytes(int L, int k, int n_inst);
+
 /* Whole search: minimum bottleneck latency (Eq. 2 minimised over all orderings and cuts).
  *   beta_out  [n_inst]        seconds if t is in Mbit and B in Mbps; +inf if no feasible solution
  *   cuts_out  [n_inst][k-1]   c_1..c_{k-1} (index of the first layer of segments 1..k-1); -1 if infeasible
@@ -98,9 +103,11 @@ int ppo_solve(const float *t, const float *m, int L, const float *M, const float
               float *beta_out, int32_t *cuts_out, int32_t *order_out, void *stream);
 
 /* Same, with caller-supplied device scratch of at least ppo_workspace_bytes(L,k,n_inst) bytes,
- * 256-byte aligned.  The scratch may be reused once the stream has passed this call's work.  Where the rows of
- * many nodes (k >= 8) want more than was given, they are taken from the stream-ordered allocator for the length
- * of the call; while the stream is being captured, or if there is no memory, the call makes do with what it has. */
+ * 256-byte aligned, and nothing else: calls no allocator, also while the stream is being captured.  The scratch
+ * may be reused once the stream has passed this call's work.  With ppo_solve_workspace_bytes(L,k,n_inst) bytes the
+ * call is as fast as it gets; with fewer, where the rows lie in the scratch, as many instances at a time as it holds
+ * areas for; with fewer than one area (few instances of 9 nodes and more), every ordering is enumerated instead, which
+ * takes tens of times as long. */
 int ppo_solve_ws(const float *t, const float *m, int L, const float *M, const float *B, int k, int n_inst,
                  float *beta_out, int32_t *cuts_out, int32_t *order_out, void *workspace, size_t workspace_bytes,
                  void *stream);

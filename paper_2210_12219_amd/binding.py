@@ -47,6 +47,8 @@ def load() -> C.CDLL:
         lib.ppo_set_enumeration.argtypes = [i]
         lib.ppo_workspace_bytes.argtypes = [i, i, i]
         lib.ppo_workspace_bytes.restype = sz
+        lib.ppo_solve_workspace_bytes.argtypes = [i, i, i]
+        lib.ppo_solve_workspace_bytes.restype = sz
         lib.ppo_solve.argtypes = inst + [i, vp, vp, vp, vp]
         lib.ppo_solve_static.argtypes = inst + [i, vp, vp, vp, vp]
         lib.ppo_solve_ws.argtypes = inst + [i, vp, vp, vp, vp, sz, vp]
@@ -125,6 +127,10 @@ def ppo_workspace_bytes(L: int, k: int, n_inst: int) -> int:
     return int(load().ppo_workspace_bytes(L, k, n_inst))
 
 
+def ppo_solve_workspace_bytes(L: int, k: int, n_inst: int) -> int:
+    return int(load().ppo_solve_workspace_bytes(L, k, n_inst))
+
+
 def to_device(w, device="cuda:0"):
     """Copy a workloads.Workload's arrays to the GPU; returns (t, m, M, B) float32 tensors."""
     torch = _torch()
@@ -170,8 +176,9 @@ def ppo_solve_static(t, m, M, B, out, stream=None):
 
 
 def alloc_workspace(L: int, k: int, n_inst: int, device="cuda:0"):
+    """Scratch for the staged calls and for ppo_solve(workspace=...) at its full speed."""
     torch = _torch()
-    return torch.empty(max(ppo_workspace_bytes(L, k, n_inst), 1), dtype=torch.uint8, device=device)
+    return torch.empty(max(ppo_solve_workspace_bytes(L, k, n_inst), 1), dtype=torch.uint8, device=device)
 
 
 def ppo_prepare(t, m, M, B, workspace, stream=None):

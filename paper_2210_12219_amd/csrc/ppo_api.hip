@@ -129,15 +129,6 @@ size_t wanted_slots(size_t slot, int n_inst) {
     return want;
 }
 
-bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 }  // namespace
 
 // The kernels read the tables with 16-byte loads at offsets that are multiples of 16 within the workspace
@@ -172,6 +163,13 @@ size_t ppo_workspace_bytes(int L, int k, int n_inst) {
     const ppo::Layout y = ppo::Layout::make(L, k);
     // tables of every instance, then one key per instance (used by ppo_solve_ws)
     return tables_bytes(y, n_inst) + ppo::align_up((size_t)n_inst * sizeof(uint64_t), 256);
+}
+
+size_t ppo_solve_workspace_bytes(int L, int k, int n_inst) {
+    const size_t least = ppo_workspace_bytes(L, k, n_inst);
+    const size_t slot = least ? ppo::subset_slot_bytes(L, k) : 0;
+    const size_t rows = slot ? slot * wanted_slots(slot, n_inst) : 0;
+    return rows > least ? rows : least;
 }
 
 int ppo_prepare(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
@@ -376,26 +374,15 @@ int ppo_finalize(int L, int k, int n_inst, const void* workspace, size_t workspa
                         static_cast<hipStream_t>(stream));
 }
 
-// The search on scratch of `bytes` bytes (at least ppo_workspace_bytes).  By subsets of nodes, unless a test has asked
-// for one of the enumeration kernels or no row area can be had: the rows of a workgroup lie in LDS, or in the given
-// scratch where it holds as many areas as are wanted, or in an allocation of their own where that is allowed.
+// The search on scratch of `bytes` bytes (at least ppo_workspace_bytes), and on nothing else.  By subsets of nodes, unless
+// a test has asked for one of the enumeration kernels or the scratch does not hold a single row area: the rows of a
+// workgroup lie in LDS, or in the scratch, as many areas at a time as it holds.
 static int solve_on_scratch(const float* t, const float* m, int L, const float* M, const float* B, int k, int n_inst,
-                            float* beta_out, int32_t* cuts_out, int32_t* order_out, void* ws, size_t bytes,
-                            bool may_allocate, hipStream_t s) {
+                            float* beta_out, int32_t* cuts_out, int32_t* order_out, void* ws, size_t bytes, hipStream_t s) {
     if (ppo::enumeration_variant() == PPO_ENUM_AUTO) {
         const size_t slot = ppo::subset_slot_bytes(L, k);
         if (slot == 0) return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, nullptr, 0, s);
         const size_t have = bytes / slot, want = wanted_slots(slot, n_inst);
-        if (have < want && may_allocate && !capturing(s)) {
-            void* slots = nullptr;
-            if (hipMallocAsync(&slots, slot * want, s) == hipSuccess) {
-                int rc = run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, slots, want, s);
-                const hipError_t e = hipFreeAsync(slots, s);
-                if (rc == PPO_OK && e != hipSuccess) rc = hip_fail(e, "hipFreeAsync (subset rows)");
-                return rc;
-            }
-            (void)hipGetLastError();   // no memory for the rows: what was given has to do
-        }
         if (have > 0)
             return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, have < want ? have : want, s);
     }
@@ -417,7 +404,7 @@ int ppo_solve_ws(const float* t, const float* m, int L, const float* M, const fl
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !M || !B || !beta_out || !order_out || (k > 1 && !cuts_out) || bad_workspace(workspace)) return PPO_EINVAL;
     if (workspace_bytes < ppo_workspace_bytes(L, k, n_inst)) return PPO_ENOSPC;
-    return solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, workspace, workspace_bytes, true,
+    return solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, workspace, workspace_bytes,
                             static_cast<hipStream_t>(stream));
 }
 
@@ -437,7 +424,7 @@ int ppo_solve(const float* t, const float* m, int L, const float* M, const float
     }
     void* ws = nullptr;
     PPO_HIP(hipMallocAsync(&ws, bytes, s), "hipMallocAsync");
-    rc = solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, bytes, false, s);
+    rc = solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, bytes, s);
     hipError_t e = hipFreeAsync(ws, s);
     if (rc == PPO_OK && e != hipSuccess) rc = hip_fail(e, "hipFreeAsync");
     return rc;
@@ -483,7 +470,7 @@ int ppo_solve_static(const float* t, const float* m, int L, const float* M, cons
     // every table a kernel reads is written by the stage before it and the keys are set by a fill kernel, so
     // whatever the previous call left in the array does not matter
     return solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, (size_t)PPO_STATIC_SCRATCH_BYTES,
-                            false, static_cast<hipStream_t>(stream));
+                            static_cast<hipStream_t>(stream));
 }
 
 int ppo_eval_orderings(const float* t, const float* m, int L, const float* M, const float* B, int k,

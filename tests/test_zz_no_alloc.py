@@ -73,3 +73,49 @@ def test_static_scratch_entry_point_under_graph_capture():
         assert np.array_equal(got[0].cpu().numpy().view(np.uint32), ref[0].cpu().numpy().view(np.uint32)), trial
         assert np.array_equal(got[1].cpu().numpy(), ref[1].cpu().numpy()), trial
         assert np.array_equal(got[2].cpu().numpy(), ref[2].cpu().numpy()), trial
+
+
+def captured(ppo, w, call, trials=3):
+    """Captures call(inputs, outputs) once after one eager call, replays it on other inputs of the same shape, and
+    compares every replay with the oracle."""
+    import torch
+    from oracle import ppo_oracle as O
+    inputs, got = ppo.to_device(w), ppo.alloc_outputs(w.n_inst, w.k)
+    call(inputs, got)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(inputs, got)
+    for trial in range(trials):
+        v = W.random_instances(3200 + trial, w.n_inst, w.L, w.k, capacity_factor=1.2 + 0.2 * trial, quantised=trial == 1)
+        for dst, src in zip(inputs, ppo.to_device(v)):
+            dst.copy_(src)
+        for o in got:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = O.subset_dp(v.t, v.m, v.M, v.B)
+        assert np.array_equal(got[0].cpu().numpy().view(np.uint32), ref[0].view(np.uint32)), trial
+        assert np.array_equal(got[1].cpu().numpy(), ref[1]) and np.array_equal(got[2].cpu().numpy(), ref[2]), trial
+        junk = torch.ones(1000, device="cuda:0").sum()      # work of the program's own between the replays
+        torch.cuda.synchronize()
+        assert float(junk) == 1000.0
+
+
+@pytest.mark.parametrize("L,k,n,scratch", [(60, 9, 12, "whole"), (60, 9, 12, "least"), (24, 10, 2, "least"), (30, 11, 5, "whole"),
+                                           (60, 9, 12, "static"), (30, 11, 27, "static")])
+def test_capture_with_rows_in_the_scratch(L, k, n, scratch):
+    """9 nodes and more, a launch per level: all instances at once, as many at a time as the scratch has room for, and
+    none (every ordering is enumerated then)."""
+    import torch
+    from paper_2210_12219_amd import binding as ppo
+    least, whole, area = ppo.ppo_workspace_bytes(L, k, n), ppo.ppo_solve_workspace_bytes(L, k, n), ppo.ppo_solve_workspace_bytes(L, k, 1)
+    print(f"captured search L={L} k={k} n={n} {scratch}: {least // area} areas in the least scratch", flush=True)
+    assert whole == n * area and least // area == {(60, 9, 12): 3, (24, 10, 2): 0}.get((L, k, n), least // area)
+    first = W.random_instances(3199, n, L, k, capacity_factor=1.3)
+    if scratch == "static":
+        captured(ppo, first, lambda x, out: ppo.ppo_solve_static(*x, out=out))
+        return
+    ws = torch.empty(whole if scratch == "whole" else least, dtype=torch.uint8, device="cuda:0")
+    captured(ppo, first, lambda x, out: ppo.ppo_solve(*x, out=out, workspace=ws))

@@ -96,7 +96,8 @@ size_t ppo_solve_workspace_bytes(int L, int k, int n_inst);
  *   beta_out  [n_inst]        seconds if t is in Mbit and B in Mbps; +inf if no feasible solution
  *   cuts_out  [n_inst][k-1]   c_1..c_{k-1} (index of the first layer of segments 1..k-1); -1 if infeasible
  *   order_out [n_inst][k]     node hosting segment s; -1 if infeasible
- * Allocates its scratch with the stream-ordered allocator and releases it on the same stream.
+ * Allocates its scratch with the stream-ordered allocator and releases it on the same stream: what
+ * ppo_solve_workspace_bytes says, or less where memory is short (the instances go in turns then).
  * Same results as ppo_prepare, ppo_init_keys, ppo_solve_range over [0, k!), ppo_finalize, found by dynamic
  * programming over subsets of nodes. */
 int ppo_solve(const float *t, const float *m, int L, const float *M, const float *B, int k, int n_inst,
@@ -193,7 +194,7 @@ int ppo_eval_orderings(const float *t, const float *m, int L, const float *M, co
  * nothing is feasible) as for ppo_solve; with w = 0 the results are those of ppo_solve bit for bit.  Dynamic
  * programming over subsets of nodes on binary32 values (a compute stage depends on both ends of a segment, so
  * the 16-bit codes of ppo_solve do not apply).  Allocates its scratch (k 2^(k-1) rows of L words for each
- * workgroup in flight, at most 1 GiB) with the stream-ordered allocator. */
+ * workgroup in flight, at most 1 GiB, less where memory is short) with the stream-ordered allocator. */
 int ppo_solve_ct(const float *t, const float *m, const float *w, int L, const float *M, const float *v,
                  const float *B, int k, int n_inst, float *beta_out, int32_t *cuts_out, int32_t *order_out,
                  void *stream);

@@ -129,6 +129,17 @@ size_t wanted_slots(size_t slot, int n_inst) {
     return want;
 }
 
+// That many areas from the stream-ordered allocator, or where memory is short half as many, and so on (they are used in
+// turns then).  hipErrorOutOfMemory: there is none for a single one.
+hipError_t alloc_areas(size_t slot, size_t want, void** areas, size_t* count, hipStream_t stream) {
+    for (*count = want; *count > 0; *count /= 2) {
+        const hipError_t e = hipMallocAsync(areas, slot * *count, stream);
+        if (e != hipErrorOutOfMemory) return e;
+        (void)hipGetLastError();
+    }
+    return hipErrorOutOfMemory;
+}
+
 }  // namespace
 
 // The kernels read the tables with 16-byte loads at offsets that are multiples of 16 within the workspace
@@ -415,13 +426,22 @@ int ppo_solve(const float* t, const float* m, int L, const float* M, const float
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !M || !B || !beta_out || !order_out || (k > 1 && !cuts_out)) return PPO_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t slot = ppo::subset_slot_bytes(L, k);
-    size_t bytes = ppo_workspace_bytes(L, k, n_inst);
     if (ppo::enumeration_variant() == PPO_ENUM_AUTO) {
+        const size_t slot = ppo::subset_slot_bytes(L, k);
         if (slot == 0) return run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, nullptr, 0, s);
-        const size_t rows = slot * wanted_slots(slot, n_inst);
-        if (rows > bytes) bytes = rows;   // whichever route it will be
+        void* areas = nullptr;
+        size_t count = 0;
+        const hipError_t e = alloc_areas(slot, wanted_slots(slot, n_inst), &areas, &count, s);
+        if (e == hipSuccess) {
+            rc = run_subset_solve(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, areas, count, s);
+            const hipError_t e2 = hipFreeAsync(areas, s);
+            if (rc == PPO_OK && e2 != hipSuccess) rc = hip_fail(e2, "hipFreeAsync (subset rows)");
+            return rc;
+        }
+        if (e != hipErrorOutOfMemory) return hip_fail(e, "hipMallocAsync (subset rows)");
     }
+    // an enumeration kernel asked for by a test, or no memory for the rows of one instance
+    const size_t bytes = ppo_workspace_bytes(L, k, n_inst);
     void* ws = nullptr;
     PPO_HIP(hipMallocAsync(&ws, bytes, s), "hipMallocAsync");
     rc = solve_on_scratch(t, m, L, M, B, k, n_inst, beta_out, cuts_out, order_out, ws, bytes, s);
@@ -502,9 +522,10 @@ int ppo_solve_ct(const float* t, const float* m, const float* w, int L, const fl
     if (n_inst == 0) return PPO_OK;
     if (!t || !m || !w || !M || !v || !B || !beta_out || !order_out || (k > 1 && !cuts_out)) return PPO_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t slot = ppo::ct_slot_bytes(L, k), count = wanted_slots(slot, n_inst);
+    const size_t slot = ppo::ct_slot_bytes(L, k);
+    size_t count = 0;
     void* slots = nullptr;
-    PPO_HIP(hipMallocAsync(&slots, slot * count, s), "hipMallocAsync (compute-term rows)");
+    PPO_HIP(alloc_areas(slot, wanted_slots(slot, n_inst), &slots, &count, s), "hipMallocAsync (compute-term rows)");
     const hipError_t e = ppo::launch_ct_solve(t, m, w, M, v, B, L, k, n_inst, beta_out, cuts_out, order_out, slots, count, s);
     const hipError_t e2 = hipFreeAsync(slots, s);
     PPO_HIP(e, "compute-term search launch");

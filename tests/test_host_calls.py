@@ -98,3 +98,34 @@ def test_a_scratch_without_room_for_one_area(record):
     assert res["rc"] == 0 and not allocations(res) and not any("subset" in x for x in kernels(res))
     short, = record({"entry": "ws", "L": 64, "k": 11, "n": 1, "bytes": 256})
     assert short["rc"] == binding.PPO_ENOSPC and not short["log"]
+
+
+@pytest.mark.parametrize("entry,L,k,n", [("ppo_solve", 127, 9, 37), ("ppo_solve", 100, 8, 300), ("ppo_solve", 128, 12, 150),
+                                         ("ct", 100, 8, 64), ("ct", 50, 6, 1024)])
+def test_less_scratch_where_memory_is_short(record, entry, L, k, n):
+    """The areas wanted, then half as many, and so on to one; ppo_solve does without any."""
+    base = {"entry": entry, "L": L, "k": k, "n": n}
+    wanted, = allocations(record(base)[0])
+    assert wanted <= 1 << 30
+    one, = allocations(record({**base, "n": 1})[0])
+    assert wanted % one == 0 and wanted // one == min(n, 1024, (1 << 30) // one)
+    for most in (wanted - 1, wanted // 3, one):
+        res, = record({**base, "limit": most})
+        got, = allocations(res)
+        assert res["rc"] == 0 and one <= got <= most < 2 * got + one and kernels(res)
+        assert [x[0] for x in res["log"]].count("free") == 1
+    res, = record({**base, "limit": one - 1})
+    if entry == "ct":
+        assert res["rc"] == binding.PPO_EHIP and not kernels(res) and not allocations(res)
+        return
+    # every ordering enumerated, on the least scratch; where there is no memory for that either, an error
+    least = record({"entry": "sizes", "L": L, "k": k, "n": n})[0]["least"]
+    assert (res["rc"] == 0) == (least < one) and (least < one) == bool(kernels(res))
+    few = {**base, "n": 1, "limit": one - 1}
+    res, = record(few)
+    assert res["rc"] == 0 and kernels(res) and not any("subset" in x for x in kernels(res))
+
+
+def test_a_shape_with_its_rows_in_lds_allocates_nothing(record):
+    res, = record({"entry": "ppo_solve", "L": 50, "k": 6, "n": 1024})
+    assert res["rc"] == 0 and not allocations(res) and len(kernels(res)) == 1

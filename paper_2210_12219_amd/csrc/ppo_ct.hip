@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kCtWaves * 64) void ct_solve_kernel(
     const uint32_t all = (1u << k) - 1u;
     const int T = L * (L + 1) / 2;
 
-    for (int inst = blockIdx.x; inst < n_inst; inst += gridDim.x) {
+    for (uint32_t inst = blockIdx.x; inst < (uint32_t)n_inst; inst += gridDim.x) {
         for (int i = tid; i < L; i += threads) {
             const float x = t_in[(size_t)inst * L + i];
             t_s[i] = x == 0.0f ? 0.0f : x;   // a zero of either sign is +0

@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 6) void
     const uint32_t all = (1u << k) - 1u;
     if (lane < 48) run32[run_levels(G) * 64 + lane] = kCodeInf | (kCodeInf << 16);
 
-    for (int inst = blockIdx.x; inst < n_inst; inst += gridDim.x) {
+    for (uint32_t inst = blockIdx.x; inst < (uint32_t)n_inst; inst += gridDim.x) {
         uint4* image = reinterpret_cast<uint4*>(rows + row_dwords(k, rd));
         if (PART == kAfterLevels) {
             for (uint32_t i = (uint32_t)tid; i < lds.run_off / 16u; i += (uint32_t)threads)
@@ -682,9 +682,16 @@ hipError_t launch_subset_solve(const float* t, const float* m, const float* M, c
         return hipGetLastError();
     };
     static std::atomic<uint64_t> allowed[8];
-    if (slot == 0)
-        return G == 2 ? launch(&subset_solve_kernel<2, kSmallK, true, kWhole>, allowed[0], 0, n_inst, (uint32_t)n_inst)
-                      : launch(&subset_solve_kernel<1, kSmallK, true, kWhole>, allowed[1], 0, n_inst, (uint32_t)n_inst);
+    if (slot == 0) {
+        // a workgroup per instance; a launch may have fewer than 2^32 threads, which 4.2 million workgroups of 1024 are not
+        constexpr int kMost = 1 << 20;
+        for (int first = 0;; first += kMost) {
+            const int left = n_inst - first, cnt = left < kMost ? left : kMost;
+            const hipError_t e = G == 2 ? launch(&subset_solve_kernel<2, kSmallK, true, kWhole>, allowed[0], first, cnt, (uint32_t)cnt)
+                                        : launch(&subset_solve_kernel<1, kSmallK, true, kWhole>, allowed[1], first, cnt, (uint32_t)cnt);
+            if (e != hipSuccess || cnt == left) return e;
+        }
+    }
     if (k <= kSmallK)
         return G == 2 ? launch(&subset_solve_kernel<2, kSmallK, false, kWhole>, allowed[2], 0, n_inst, (uint32_t)slot_count)
                       : launch(&subset_solve_kernel<1, kSmallK, false, kWhole>, allowed[3], 0, n_inst, (uint32_t)slot_count);

@@ -73,7 +73,7 @@ int hipLaunchKernel(const void *function, dim3 grid, dim3 block, void **args, si
     (void)args; (void)stream;
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].function == function) name = kernels[i].name;
-    /* the runtime counts the threads of each dimension in 32 bits and refuses what does not fit */
+    /* documented limits: fewer than 2^32 threads in each dimension, 65,535 blocks in y and z */
     if ((uint64_t)grid.x * block.x > 0xFFFFFFFFu || (uint64_t)grid.y * block.y > 0xFFFFFFFFu ||
         (uint64_t)grid.z * block.z > 0xFFFFFFFFu || grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535)
         return fail(kInvalidConfiguration);

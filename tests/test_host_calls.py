@@ -129,3 +129,13 @@ def test_less_scratch_where_memory_is_short(record, entry, L, k, n):
 def test_a_shape_with_its_rows_in_lds_allocates_nothing(record):
     res, = record({"entry": "ppo_solve", "L": 50, "k": 6, "n": 1024})
     assert res["rc"] == 0 and not allocations(res) and len(kernels(res)) == 1
+
+
+@pytest.mark.parametrize("entry", ["ppo_solve", "ws"])
+@pytest.mark.parametrize("L,k,n", [(10, 8, 4_200_000), (3, 2, 70_000_000), (1, 1, 2**31 - 1)])
+def test_millions_of_small_instances(record, entry, L, k, n):
+    """A launch may have fewer than 2^32 threads."""
+    res, = record({"entry": entry, "L": L, "k": k, "n": n, "bytes": 2**62})
+    assert res["rc"] == 0, "a launch beyond the documented limits"
+    grids = [int(x[2]) for x in res["log"] if x[0] == "launch"]
+    assert sum(grids) == n and all("subset" in x for x in kernels(res))

@@ -317,21 +317,20 @@ __global__ __launch_bounds__(kCtWaves * 64) void ct_solve_kernel(
         }
         if (tid == 0) sh.longest = 0u;
         if (wave < 2) {
-            // prefix sums in index order in binary64: the weights by one wave, the work by another
+            // prefix sums in index order in binary64: the weights by one wave, the work by another (all lanes of it add
+            // and store the same)
             const float* src = (wave == 0 ? m_in : w_in) + (size_t)inst * L;
             double* dst = wave == 0 ? P : Q;
             double acc = 0.0;
+            dst[0] = 0.0;
             for (int base = 0; base < L; base += 64) {
                 const float x = base + lane < L ? src[base + lane] : 0.0f;
-                if (lane == 0) {
 #pragma unroll
-                    for (int i = 0; i < 64; ++i) {
-                        acc = acc + (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), i));
-                        dst[base + i + 1] = acc;
-                    }
+                for (int i = 0; i < 64; ++i) {
+                    acc = acc + (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), i));
+                    dst[base + i + 1] = acc;
                 }
             }
-            if (lane == 0) dst[0] = 0.0;
         }
         __syncthreads();
         int longest = 0;

@@ -133,3 +133,21 @@ def test_subset_search_at_the_edges_of_its_forms(ppo, L, k, n):
             got, ref = gpu_solve(ppo, w, work, speed), oracle(w, work, speed, CT.subset_dp)
             assert np.array_equal(bits(got[0]), bits(ref[0]))
             assert np.array_equal(got[2], ref[2]) and np.array_equal(got[1], ref[1][:, :k - 1])
+
+
+@pytest.mark.parametrize("L,k,n", [(12, 4, 1500), (70, 3, 1300), (20, 8, 1100), (100, 5, 1100)])
+def test_a_workgroup_with_several_instances(ppo, L, k, n):
+    """More instances than the 1024 row areas: a workgroup takes another one on the tables and rows of the last.
+    Capacities from none that fits to all that fit, so that windows grow and shrink from one to the next, and work from
+    nothing to all there is; one entry to a lane and two, compute stages in LDS
+    and (100 layers) in the area."""
+    w = W.random_instances(7700 + L, n, L, k, capacity_factor=1.4)
+    rng = np.random.default_rng(n)
+    w.M[...] *= np.exp(rng.uniform(np.log(0.4), np.log(30.0), (n, 1))).astype(np.float32)
+    work, speed = W.compute_terms(w, seed=L, seconds=5.0)
+    work *= rng.choice(np.array([0.0, 0.1, 1.0, 50.0], np.float32), (n, 1))
+    print(f"ct several instances a workgroup L={L} k={k} n={n}", flush=True)
+    got = gpu_solve(ppo, w, work, speed)
+    assert np.isinf(got[0][1024:]).any() and np.isfinite(got[0][1024:]).any()
+    idx = list(range(40)) + list(range(984, n))
+    assert_same(got, oracle(w, work, speed, CT.subset_dp, idx), f"L={L} k={k} n={n}", idx)

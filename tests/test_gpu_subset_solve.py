@@ -56,3 +56,21 @@ def test_quotients_a_few_units_apart(L, k):
 def test_more_instances_than_row_areas():
     """With the static scratch 27 of these share 16 MiB: several rounds of launches."""
     check(W.random_instances(6500, 27, 30, 11, capacity_factor=1.3), static=True)
+
+
+@pytest.mark.parametrize("L,k,n", [(70, 7, 1100), (22, 8, 300)])
+def test_a_workgroup_with_several_instances(L, k, n):
+    """Rows in global memory, fewer areas than instances (1024 of ppo_solve's own, fewer in the least scratch): a workgroup
+    takes another instance on the tables and rows of the last, with capacities from none that fits to all that fit."""
+    import torch
+    from paper_2210_12219_amd import binding as ppo
+    w = W.random_instances(6600 + L, n, L, k, capacity_factor=1.4)
+    w.M[...] *= np.exp(np.random.default_rng(n).uniform(np.log(0.4), np.log(30.0), (n, 1))).astype(np.float32)
+    ref = check(w)
+    least, area = ppo.ppo_workspace_bytes(L, k, n), ppo.ppo_solve_workspace_bytes(L, k, 1)
+    areas = least // area
+    assert 1 <= areas < min(n, 1024) and np.isinf(ref[0][areas:]).any() and np.isfinite(ref[0][areas:]).any()
+    out = ppo.ppo_solve(*ppo.to_device(w), workspace=torch.empty(least, dtype=torch.uint8, device="cuda:0"))
+    got = [x.cpu().numpy() for x in out]
+    assert np.array_equal(got[0].view(np.uint32), ref[0].view(np.uint32))
+    assert np.array_equal(got[2], ref[2]) and np.array_equal(got[1], ref[1])

@@ -1,4 +1,7 @@
-"""Parity of the HIP path (through the C ABI) with the CPU oracle, bit for bit: beta, cuts, ordering."""
+"""Parity of the HIP path (through the C ABI) with the CPU oracle, bit for bit: beta, cuts, ordering.
+
+gpu_solve is the whole-search call (by subsets of nodes); gpu_enumerate is the staged search that evaluates every
+ordering.  A workload or shape that is there for an enumeration kernel goes through both."""
 import math
 
 import numpy as np
@@ -31,6 +34,25 @@ def gpu_solve(ppo, w, **kw):
     return beta.cpu().numpy(), cuts.cpu().numpy(), order.cpu().numpy()
 
 
+def gpu_enumerate(ppo, w, variant=None):
+    """ppo_prepare, ppo_init_keys, ppo_solve_range over every rank, ppo_finalize, with the enumeration kernel asked for"""
+    import torch
+    dev = ppo.to_device(w)
+    ws = ppo.alloc_workspace(w.L, w.k, w.n_inst)
+    keys = torch.empty(w.n_inst, dtype=torch.int64, device="cuda:0")
+    try:
+        if variant is not None:
+            ppo.ppo_set_enumeration(variant)
+        ppo.ppo_prepare(*dev, ws)
+        ppo.ppo_init_keys(keys)
+        ppo.ppo_solve_range(w.L, w.k, w.n_inst, ws, 0, math.factorial(w.k), keys)
+        out = ppo.ppo_finalize(w.L, w.k, w.n_inst, ws, keys)
+        torch.cuda.synchronize()
+    finally:
+        ppo.ppo_set_enumeration(ppo.PPO_ENUM_AUTO)
+    return tuple(x.cpu().numpy() for x in out)
+
+
 def assert_same(got, ref, what=""):
     bad = np.nonzero(bits(got[0]) != bits(ref[0]))[0]
     assert bad.size == 0, f"{what}: beta differs at instances {bad[:8]}: {got[0][bad[:4]]} vs {ref[0][bad[:4]]}"
@@ -51,6 +73,7 @@ def test_tiny_workload_against_brute_force_and_exhaustive(ppo):
     got = gpu_solve(ppo, w)
     assert_same(got, O.bruteforce(w.t, w.m, w.M, w.B), "tiny vs brute force")
     assert_same(got, O.exhaustive(w.t, w.m, w.M, w.B)[:3], "tiny vs exhaustive")
+    assert_same(gpu_enumerate(ppo, w), got, "tiny, every ordering")
     assert np.isinf(got[0]).sum() > 10          # the workload does contain infeasible instances
 
 
@@ -68,7 +91,9 @@ def test_per_ordering_beta_tiny_and_resnet(ppo):
 
 def test_resnet_workload_full(ppo):
     w = W.resnet50_shaped()
-    assert_same(gpu_solve(ppo, w), O.exhaustive(w.t, w.m, w.M, w.B)[:3], "resnet50_shaped")
+    ref = O.exhaustive(w.t, w.m, w.M, w.B)[:3]
+    assert_same(gpu_solve(ppo, w), ref, "resnet50_shaped")
+    assert_same(gpu_enumerate(ppo, w), ref, "resnet50_shaped, every ordering")
 
 
 def test_transformer_workload_full(ppo):
@@ -76,6 +101,7 @@ def test_transformer_workload_full(ppo):
     w = W.transformer_encoder()
     got = gpu_solve(ppo, w)
     assert_same(got, O.subset_dp(w.t, w.m, w.M, w.B), "transformer vs subset DP")
+    assert_same(gpu_enumerate(ppo, w), got, "transformer, every ordering")
     head = w.take(8)
     assert_same(tuple(x[:8] for x in got), O.exhaustive(head.t, head.m, head.M, head.B)[:3],
                 "transformer vs exhaustive")
@@ -96,11 +122,12 @@ def sampled_orderings_match(ppo, w, inst, n_ranges, width, seed):
 
 
 def test_headline_workload_full(ppo):
-    """Full size, in the launch configuration the benchmark times: the optimum against the independent
-    subset DP, plus beta of sampled orderings one by one against the per-ordering oracle."""
+    """Full size, by the whole-search call and by the staged calls in the launch configuration the benchmark times: the
+    optimum against the independent subset DP, plus beta of sampled orderings one by one against the per-ordering oracle."""
     w = W.headline()
     got = gpu_solve(ppo, w)
     assert_same(got, O.subset_dp(w.t, w.m, w.M, w.B), "headline vs subset DP")
+    assert_same(gpu_enumerate(ppo, w), got, "headline, every ordering")
     sampled_orderings_match(ppo, w, [0, 17, 63], 3, 3000, seed=1)
 
 
@@ -196,6 +223,7 @@ def test_large_workload_full(ppo):
     got = gpu_solve(ppo, w)
     assert np.isfinite(got[0][0])
     assert_same(got, O.subset_dp(w.t, w.m, w.M, w.B), "large vs subset DP")
+    assert_same(gpu_enumerate(ppo, w), got, "large, every ordering")
     sampled_orderings_match(ppo, w, [0], 4, 5000, seed=2)
 
 
@@ -207,6 +235,7 @@ def test_small_instances_with_ties_and_exact_capacity_hits(ppo):
         w = W.random_instances(seed, 50, L, k, capacity_factor=float(rng.uniform(1.0, 1.8)), quantised=bool(seed % 2))
         ref = O.exhaustive(w.t, w.m, w.M, w.B)[:3] if k == 5 else O.bruteforce(w.t, w.m, w.M, w.B)
         assert_same(gpu_solve(ppo, w), ref, f"random L={L} k={k} seed={seed}")
+        assert_same(gpu_enumerate(ppo, w), ref, f"random L={L} k={k} seed={seed}, every ordering")
 
 
 def test_degenerate_shapes(ppo):
@@ -215,10 +244,12 @@ def test_degenerate_shapes(ppo):
     w.M[::2] *= np.float32(0.5)                     # every other instance cannot hold the model
     got = gpu_solve(ppo, w)
     assert_same(got, O.bruteforce(w.t, w.m, w.M, w.B), "k=1")
+    assert_same(gpu_enumerate(ppo, w), got, "k=1, every ordering")
     assert np.isinf(got[0][::2]).all() and (got[0][1::2] == 0).all()
     # L = k: every segment is a single layer
     w = W.random_instances(2, 40, 5, 5, capacity_factor=3.0)
     assert_same(gpu_solve(ppo, w), O.bruteforce(w.t, w.m, w.M, w.B), "L=k")
+    assert_same(gpu_enumerate(ppo, w), O.bruteforce(w.t, w.m, w.M, w.B), "L=k, every ordering")
     # L = k = 1
     w = W.random_instances(3, 4, 1, 1, capacity_factor=1.5)
     assert_same(gpu_solve(ppo, w), O.bruteforce(w.t, w.m, w.M, w.B), "L=k=1")
@@ -226,6 +257,7 @@ def test_degenerate_shapes(ppo):
     w = W.random_instances(4, 5, 9, 3, capacity_factor=0.5)
     got = gpu_solve(ppo, w)
     assert np.isinf(got[0]).all() and (got[1] == -1).all() and (got[2] == -1).all()
+    assert_same(gpu_enumerate(ppo, w), got, "nothing fits, every ordering")
     # zero transfer sizes are legal and give beta = +0
     w = W.random_instances(5, 3, 6, 3, capacity_factor=3.0)
     w.t[:] = 0
@@ -240,6 +272,7 @@ def test_degenerate_shapes(ppo):
     ref = O.bruteforce(w.t, w.m, w.M, w.B)
     assert not (bits(ref[0]) == 0x80000000).any() and (bits(ref[0]) == 0).any()
     assert_same(got, ref, "t=-0")
+    assert_same(gpu_enumerate(ppo, w), ref, "t=-0, every ordering")
     plus = W.Workload(w.name, w.L, w.k, w.n_inst, w.seed, np.abs(w.t), w.m, w.M, w.B)
     assert_same(got, O.bruteforce(plus.t, plus.m, plus.M, plus.B), "t=-0 against t=+0")
 
@@ -261,6 +294,7 @@ def test_memory_rule_in_binary64(ppo):
     assert_same(gpu_solve(ppo, w), ref, "near 2^24")
     dev = ppo.to_device(w)
     ws = ppo.alloc_workspace(L, k, n)
+    assert_same(gpu_enumerate(ppo, w), ref, "near 2^24, every ordering")
     for route in ("bounded", "subsets"):
         keys = torch.empty(n, dtype=torch.int64, device="cuda:0")
         ppo.ppo_prepare(*dev, ws)
@@ -342,16 +376,21 @@ def test_division_is_correctly_rounded_on_a_million_pairs(ppo):
 
 
 def test_grouped_kernel_row_lengths(ppo):
-    """The grouped kernel cuts a row of NP = ceil((L-k+2)/2) output dwords into one to four parts of three
-    chunks: sweep NP from 1 to its maximum of 48 (and one past it, which goes to the generic kernel), with
-    k = 6, 7 and 9, against the subset DP."""
+    """The paired kernel has a piece of code for every entry of a row, and the grouped kernel cuts a row of
+    NP = ceil((L-k+2)/2) output dwords into one to four parts of three chunks: sweep NP from 1 to its maximum of 48 (and
+    one past it, which goes to the generic kernel), with k = 6, 7 and 9, through the whole-search call and through every
+    enumeration kernel, against the subset DP."""
     cases = [(6, 6), (6, 7), (6, 9), (6, 13), (6, 27), (6, 28), (6, 29), (6, 51), (6, 52), (6, 53), (6, 75),
              (6, 76), (6, 77), (6, 99), (6, 100), (6, 101), (7, 7), (7, 30), (7, 54), (7, 78), (7, 101), (7, 102),
              (9, 9), (9, 20), (9, 57), (9, 103)]
     for n, (k, L) in enumerate(cases):
         w = W.random_instances(7000 + n, 3 if k == 9 else 10, L, k, capacity_factor=1.15 + 0.1 * (n % 4),
                                quantised=bool(n % 3 == 0))
-        assert_same(gpu_solve(ppo, w), O.subset_dp(w.t, w.m, w.M, w.B), f"grouped row lengths k={k} L={L}")
+        ref = O.subset_dp(w.t, w.m, w.M, w.B)
+        assert_same(gpu_solve(ppo, w), ref, f"row lengths k={k} L={L}, by subsets")
+        for variant in (ppo.PPO_ENUM_AUTO, ppo.PPO_ENUM_GENERIC, ppo.PPO_ENUM_GROUPED):
+            print(f"row lengths k={k} L={L} kernel {variant}", flush=True)
+            assert_same(gpu_enumerate(ppo, w, variant), ref, f"row lengths k={k} L={L} kernel {variant}")
 
 
 def test_grouped_kernel_behind_the_switch(ppo):

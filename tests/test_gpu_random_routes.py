@@ -1,7 +1,7 @@
 """Random small problems through every route of the library, each against the CPU oracles, bit for bit.
 
-The shapes are drawn per seed: k, L and the batch size for the fixed-k routes (enumeration, shared prefix with
-a bound, subset DP), the cluster size, the segment limit and the capacity regime for the cluster form, a random
+The shapes are drawn per seed: k, L and the batch size for the fixed-k routes (whole search, every ordering with
+each enumeration kernel in turn, shared prefix with a bound, staged subset DP), the cluster size, the segment limit and the capacity regime for the cluster form, a random
 capacity per instance for the partitioning step.  The named workloads fix their shapes; this file moves them."""
 import math
 
@@ -52,13 +52,19 @@ def test_fixed_k_routes_on_random_shapes(ppo):
         ref = O.subset_dp(w.t, w.m, w.M, w.B)
         dev = ppo.to_device(w)
         got = tuple(x.cpu().numpy() for x in ppo.ppo_solve(*dev))
-        same(got, ref, what + " enumeration")
+        same(got, ref, what + " whole search")
         ws = ppo.alloc_workspace(L, k, n_inst)
-        for route in ("bounded", "subsets"):
+        for route in ("range", "bounded", "subsets"):
             keys = torch.empty(n_inst, dtype=torch.int64, device="cuda:0")
             ppo.ppo_prepare(*dev, ws)
             ppo.ppo_init_keys(keys)
-            if route == "bounded":
+            if route == "range":
+                try:
+                    ppo.ppo_set_enumeration((ppo.PPO_ENUM_AUTO, ppo.PPO_ENUM_GENERIC, ppo.PPO_ENUM_GROUPED)[seed % 3])
+                    ppo.ppo_solve_range(L, k, n_inst, ws, 0, math.factorial(k), keys)
+                finally:
+                    ppo.ppo_set_enumeration(ppo.PPO_ENUM_AUTO)
+            elif route == "bounded":
                 ppo.ppo_solve_range_bounded(L, k, n_inst, ws, 0, math.factorial(k), keys, None)
             else:
                 ppo.ppo_solve_subsets(L, k, n_inst, ws, keys)

@@ -76,7 +76,7 @@ struct ClusterLayout {
     }
     // bytes of the quotient rows in the LDS image (the window queries follow, 16-byte aligned): two sets to a wave, of
     // every ordered pair, so that a lane finds the row of (j, j'') by one addition; one set, of every pair a < b, at
-    // pair_row (half the space, and the offset is the wave's)
+    // below(b) + a (half the space, and the offset is the wave's)
     __host__ __device__ size_t q_image_bytes() const {
         return align_up((size_t)(cluster_mode(L) == kClTwoSets ? n * n : npairs) * (rs / 2) * 4, 16);
     }

@@ -38,8 +38,8 @@ constexpr FewBinomials kFewBinomialsHost = FewBinomials();
 __constant__ FewBinomials kFewBinomials = FewBinomials();
 
 struct FewState {
-    uint32_t best, chosen, done, p, last, pad[3];
-    unsigned long long used, F[2];
+    uint32_t best, chosen, done;
+    unsigned long long used;
     union {
         uint32_t first_best[kFewMaxN];           // per node j, until position 0 is settled: the least G[S][j][0] of all sets so far
         unsigned long long cand[kFewMaxN][2];    // then G_j of every candidate of the current position
@@ -165,8 +165,6 @@ __global__ __launch_bounds__(kFewTableThreads) void few_tables_kernel(const floa
             st->best = kInfBits;
             st->chosen = kFewNone;
             st->done = 0u;
-            st->p = 0u;
-            st->last = 0u;
             st->used = 0ull;
         }
     }
@@ -609,10 +607,6 @@ __global__ __launch_bounds__(kFewStepWaves * 64) void few_step_kernel(FewLayout 
     if (threadIdx.x == 0) {
         st->chosen = kFewNone;
         st->used = used;
-        st->p = (uint32_t)p;
-        st->last = (uint32_t)last;
-        st->F[0] = F0;
-        st->F[1] = F1;
     }
 }
 

@@ -80,13 +80,12 @@ def run_sharing(w):
     return outputs / runs, per_output / outputs, shared / outputs
 
 
-def profiled(name, version):
+def profiled(name):
     """Figures that only a profiler run can give (HBM traffic, share of the vector issue slots), read from the
     summary under profiles/ that `python -m paper_2210_12219_amd.profile_summary` wrote from rocprofv3 output, and
-    only while that summary is of the library version that is running; otherwise {}."""
-    from paper_2210_12219_amd.profile_summary import read_summary
-    got = read_summary(os.path.join(ROOT, "profiles", name + ".md"))
-    return got if got.get("ppo_version") == float(version) else {}
+    only while the kernel's code is the one that was profiled; otherwise {}."""
+    from paper_2210_12219_amd.profile_summary import current_summary
+    return current_summary(os.path.join(ROOT, "profiles", name + ".md"))
 
 
 def copy_probe(torch):
@@ -138,15 +137,14 @@ def bench_ct(args, torch, ppo, workloads):
         out = ppo.ppo_solve_ct(t, m, wd, M, vd, B, out=out)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
-    kf = math.factorial(w.k)
     print(json.dumps({
-        "metric": f"node orderings evaluated/sec with the compute-time term at k={w.k},L={w.L}",
-        "value": w.n_inst * kf / (wall / args.steps), "unit": "orderings/s", "n_gpus": 1, "steps": args.steps,
+        "metric": f"instances solved exactly/sec with the compute-time term at k={w.k},L={w.L} (dynamic programming over node subsets)",
+        "value": w.n_inst / (wall / args.steps), "unit": "instances/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": wall * 1e3 / args.steps, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-        "config": {"workload": f"{w.name}: {w.n_inst} instances x (L={w.L}, k={w.k}), {kf} orderings each, "
+        "config": {"workload": f"{w.name}: {w.n_inst} instances x (L={w.L}, k={w.k}), "
                                "work per layer log-uniform over a factor of 30, node speeds 1x/2x/4x, 10 s for the model",
-                   "orderings_per_step": w.n_inst * kf},
+                   "dp_rows_per_instance": w.k * 2 ** (w.k - 1)},
         "roofline": None}), flush=True)
 
 
@@ -263,7 +261,7 @@ def bench_cluster(args, torch, ppo, workloads):
         # against the whole call (tables, one launch per level, trace), not the level kernel alone
         "roofline": {"bound": "hbm", "kernel": "cluster_level_kernel (all levels) + tables + trace",
                      "achieved": achieved, "peak": 8000.0, "unit": "GB/s", "frac": achieved / 8000.0,
-                     "traffic": profiled(f"cluster_solve_n{N}", ppo.load().ppo_version()).get("traffic_bytes_per_launch")
+                     "traffic": profiled(f"cluster_solve_n{N}").get("traffic_bytes_per_launch")
                      if (n_inst == 1 and pmax == N) else None,
                      "bytes_per_step": alg_bytes},
     }
@@ -290,11 +288,11 @@ def bench_cluster_few(args, torch, ppo, workloads):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     full = sum(math.comb(N, c) * c for c in range(1, max(pmax, 2)))
-    top = math.comb(N, pmax) * pmax if pmax > 1 else 0
-    # every full row (L binary32 entries, rounded up to even) is written once and read once by the level above,
-    # every entry of the last level is written once; the passes that rebuild the answer read them again
+    marks = math.comb(N, pmax - 1) if pmax > 1 else 0
+    # every row below the last level (L binary32 entries, rounded up to even) is written once and read once by the level
+    # above; of the last level only a mark per set of the level below is kept, written and read once
     row_bytes = 4 * ((w.L + 1) & ~1)
-    alg_bytes = (2 * full * row_bytes + 4 * top) * n_inst
+    alg_bytes = (2 * full * row_bytes + 2 * 4 * marks) * n_inst
     achieved = alg_bytes / (wall / args.steps) / 1e9
     print(json.dumps({
         "metric": f"clusters solved exactly/sec at n={N},L={w.L}, up to {pmax} segments (dynamic programming over sets of nodes still to be used)",
@@ -302,8 +300,8 @@ def bench_cluster_few(args, torch, ppo, workloads):
         "warmup": args.warmup, "ms_per_step": wall * 1e3 / args.steps, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"{w.name}: {n_inst} instances x (L={w.L}, n={N}), capacities for {pmax} segments, seed={w.seed}",
-                   "dp_rows_per_instance": full + top, "segments_found": [int(x) for x in out[1].cpu().numpy()[:8]]},
-        "roofline": {"bound": "hbm", "kernel": "few_level_kernel (all levels) + tables + answer passes",
+                   "dp_rows_per_instance": full, "segments_found": [int(x) for x in out[1].cpu().numpy()[:8]]},
+        "roofline": {"bound": "hbm", "kernel": "few_level_kernel, few_top_kernel + tables + answer passes",
                      "achieved": achieved, "peak": 8000.0, "unit": "GB/s", "frac": achieved / 8000.0, "traffic": None,
                      "bytes_per_step": alg_bytes}}), flush=True)
 
@@ -417,7 +415,7 @@ def main():
     ops_per_launch = (cand + maxops) * n * kf
     achieved = ops_per_launch / (enum_ms * 1e-3) / 1e12
 
-    prof = profiled(f"enumerate_paired_{args.workload}", ppo.load().ppo_version())
+    prof = profiled(f"enumerate_paired_{args.workload}")
     result = {
         "metric": "node orderings (full DPs) evaluated/sec at k=10,L=100; % of VALU peak",
         "value": value, "unit": "orderings/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -431,7 +429,7 @@ def main():
         # kernel) per second of the enumeration kernel; peak: 32-bit lane operations of the vector ALUs.  The kernel
         # works on packed 16-bit halves, whose peak is twice that (frac_packed16); valu_issue is the share of the
         # vector issue slots the kernel filled according to the hardware counters (from the committed profile of
-        # this library version, else null), as is traffic.
+        # this kernel code, else null), as is traffic.
         "roofline": {"bound": "alu", "kernel": "enumerate", "achieved": achieved, "peak": VALU_PEAK_TOPS,
                      "unit": "Tlane-op/s", "frac": achieved / VALU_PEAK_TOPS,
                      "frac_packed16": achieved / (2.0 * VALU_PEAK_TOPS),

@@ -149,11 +149,13 @@ __global__ __launch_bounds__(256) void ct_enumerate_kernel(CtLayout y, const uns
 // comp does not decrease with e' (the weights of the work are >= 0 and both roundings are monotone), so rest may be
 // replaced by its least value up to e': that one does not increase, and the minimum lies where the two cross.  The
 // crossing is found by descending through minima over runs of 2^r entries: log2(window) steps instead of a candidate per
-// entry of the window.  1024 x (50 layers, 6 nodes): 122 us, against 2.76 ms with a programme per ordering.
+// entry of the window.  1024 x (50 layers, 6 nodes): 119 us, against 2.76 ms with a programme per ordering.
 //
 // What bounds it: the chain of dependent LDS reads of a row (six levels of runs, six steps of two reads each) with eight
-// to twenty-four waves on a compute unit.  The compute stages of an instance stay in LDS while two workgroups fit beside
-// each other (a descent reads them once a step, scattered); beyond that, and for the rows, the caches hold them.
+// to twenty-four waves on a compute unit: of the time of the 3.7 waves on a SIMD 0.58 is spent waiting, 206 vector,
+// 102 scalar and 37 LDS instructions a row fill 0.57, 0.28 and 0.26 of their units' time (1024 x (50, 6)).  The compute
+// stages of an instance stay in LDS while two workgroups fit beside each other (a descent reads them once a step,
+// scattered); beyond that, and for the rows, the caches hold them.
 // ---------------------------------------------------------------------------------------------
 namespace {
 

@@ -17,13 +17,17 @@
 // after the last one "code <= code of beta*" says the same as "value <= beta*".  No quotient is ranked among the others,
 // which is what the tables of the enumeration spend most of their time on.
 //
-// What bounds it: vector issue.  A row of 65 to 128 entries is 33 vector instructions at four links, 10 of them for the
-// links, the rest for the window minima, which 50 to 64 lanes of two entries share; rows of up to 64 entries go two sets
-// to a wave.  Up to 8 nodes one launch does everything for an instance in one workgroup (no tables in HBM, no launch
-// gaps); the traceback runs on one wave, because run by all of them (redundantly, with barriers) it issued more
-// instructions than the rows did (50 layers on 6 nodes: 65 us for 1024 instances, 43 with one wave).
-// Measured on one MI355X, per call: 256 x (L 12, k 4) 21 us (enumeration 58), 1024 x (50, 6) 43 us (163), 4096 x (96, 8)
-// 0.62 ms (23.1 ms), 37 x (127, 9) 90 us (97 ms), 1 x (64, 11) 80 us (3.2 ms).
+// What bounds it: no single unit.  4096 x (96, 8) issues 47 vector, 44 scalar and 14 LDS instructions a row (tables and
+// answer included), which fills 0.55 of the vector, 0.52 of the scalar and 0.38 of the LDS units' time; of the time of its
+// seven waves on a SIMD 0.61 is spent waiting: for LDS and the rows below, or at the barriers (the prefix sums and the
+// answer are one wave's work; the counter does not tell these apart).  1024 x (50, 6): 0.56, 0.28 and 0.24, six waves, 0.66 waiting.
+// Rows of up to 64 entries go two sets to a wave, longer ones leave lanes beyond the chain idle.  Up to 8 nodes one launch
+// does everything for an instance in one workgroup (no tables in HBM, no launch gaps); the answer is walked by one wave,
+// because run by all of them (redundantly, with barriers) it issued more instructions than the rows did (50 layers on 6
+// nodes: 65 us for 1024 instances, 43 with one wave).
+// Measured on one MI355X, per call with scratch and outputs kept (in brackets with the call's own scratch; the enumeration
+// before): 256 x (L 12, k 4) 18 us (21; 58), 1024 x (50, 6) 44 us (43; 163), 4096 x (96, 8) 0.61 ms (0.62; 23.1 ms),
+// 37 x (127, 9) 87 us (91; 97 ms), 1 x (64, 11) 76 us (92; 3.2 ms).
 #include "ppo_sets.h"
 
 namespace ppo {
@@ -660,8 +664,8 @@ static hipError_t launch_level(int L, int k, int cnt, uint32_t* slots, size_t sl
 
 // slots: `slot_count` areas of subset_slot_bytes (unused if that is 0).  Up to kSmallK nodes a workgroup does the whole
 // search and keeps its area for all its instances; with more nodes an instance has enough sets for many workgroups, and
-// the levels of `slot_count` instances at a time are launches over all of them: 1 x (64, 11) 72 us against 176 in one
-// workgroup, 64 x (100, 10) 137 against 323, 37 x (127, 9) 88 against 175.
+// the levels of `slot_count` instances at a time are launches over all of them: 1 x (64, 11) 76 us against 410 in one
+// workgroup, 64 x (100, 10) 133 against 358, 37 x (127, 9) 87 against 174.
 hipError_t launch_subset_solve(const float* t, const float* m, const float* M, const float* B, int L, int k, int n_inst,
                                float* beta_out, int32_t* cuts_out, int32_t* order_out, void* slots, size_t slot_count,
                                hipStream_t stream) {

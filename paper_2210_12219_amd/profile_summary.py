@@ -1,24 +1,28 @@
 """Turns rocprofv3 CSV output into the short summaries kept under profiles/, and reads them back for bench.py.
 
     python -m paper_2210_12219_amd.profile_summary --kernel enumerate_paired_kernel --workload headline \\
-        --stats DIR_OF_KERNEL_TRACE --counters DIR [DIR ...] --traffic FETCH_DIR WRITE_DIR \\
-        --orderings 232243200 --command "..." > profiles/enumerate_paired_headline.md
+        --source ppo_paired.hip ppo_pair_asm.h --stats DIR_OF_KERNEL_TRACE --counters DIR [DIR ...] \\
+        --traffic FETCH_DIR WRITE_DIR         --orderings 232243200 --command "..." > profiles/enumerate_paired_headline.md
 
 --stats     a directory written by `rocprofv3 --kernel-trace --stats --output-format csv`
 --counters  directories written by `rocprofv3 --pmc ... --output-format csv` (one per pass)
 --traffic   two such directories for FETCH_SIZE and WRITE_SIZE, taken with `bench.py --copy-probe`: the counters
             are scaled by what they read for the probe's plain copy kernel (256 MiB read, 256 MiB written)
-The summary starts with `key: value` lines (`ppo_version`, `kernel_avg_ns`, `valu_issue`, `traffic_bytes_per_launch`
-...) that `read_summary` parses; bench.py quotes them only while the library's version is still the one profiled.
+--source    the files of csrc/ that hold the kernel's code
+The summary starts with `key: value` lines (`kernel_avg_ns`, `valu_issue`, `traffic_bytes_per_launch` ...) that
+`read_summary` parses, among them a digest of the sources' code; `current_summary`, and through it bench.py, quotes
+them only while the code is still the one profiled.
 """
 from __future__ import annotations
 
 import argparse
 import csv
 import glob
+import hashlib
 import os
 import re
 
+CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 PROBE_BYTES = 256 * 1024 * 1024   # bench.py --copy-probe: one kernel that reads and writes this much
 
 
@@ -89,11 +93,31 @@ def read_summary(path):
     return out
 
 
+def source_digest(files, csrc=CSRC):
+    """of the code of these files, comments and white space left out"""
+    h = hashlib.sha256()
+    for f in files:
+        text = open(os.path.join(csrc, f)).read()
+        text = re.sub(r"/\*.*?\*/", " ", re.sub(r"//[^\n]*", " ", text), flags=re.S)
+        h.update(" ".join(text.split()).encode() + b"\0")
+    return "sha-" + h.hexdigest()[:16]
+
+
+def current_summary(path, csrc=CSRC):
+    """read_summary(path) while the kernel's code is the one profiled, else {}."""
+    got = read_summary(path)
+    files = str(got.get("source", "")).split()
+    if not files or not all(os.path.exists(os.path.join(csrc, f)) for f in files):
+        return {}
+    return got if got.get("source_digest") == source_digest(files, csrc) else {}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--kernel", required=True)
     ap.add_argument("--workload", required=True)
     ap.add_argument("--ppo-version", type=int, required=True)
+    ap.add_argument("--source", nargs="+", required=True, help="files of csrc/ with the kernel's code")
     ap.add_argument("--stats")
     ap.add_argument("--counters", nargs="*", default=[])
     ap.add_argument("--traffic", nargs=2)
@@ -102,7 +126,8 @@ def main():
     ap.add_argument("--note", action="append", default=[])
     a = ap.parse_args()
     lines = [f"# {a.kernel}: {a.workload}", ""]
-    keys = [("ppo_version", a.ppo_version), ("kernel", a.kernel), ("workload", a.workload)]
+    keys = [("ppo_version", a.ppo_version), ("kernel", a.kernel), ("workload", a.workload),
+            ("source", " ".join(a.source)), ("source_digest", source_digest(a.source))]
     body = []
     if a.stats:
         mine, table = kernel_stats(a.stats, a.kernel)
@@ -136,7 +161,7 @@ def main():
         body.append("")
     lines += [f"{k}: {v}" for k, v in keys] + [""]
     if a.command:
-        lines += ["Commands (from the repository root on the GPU box, after `cd /tmp && export TMPDIR=/tmp`; `$R` is the root):", ""]
+        lines += ["Commands (from the repository root, after `cd /tmp && export TMPDIR=/tmp`; `$R` is the root):", ""]
         lines += [f"    {c}" for c in a.command] + [""]
     lines += [n for n in a.note] + ([""] if a.note else [])
     print("\n".join(lines + body))

@@ -125,14 +125,11 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
     unsigned char* hi = base + y.hi_off;
     float* dec = reinterpret_cast<float*>(base + y.dec_off);
     float* qv = reinterpret_cast<float*>(base + y.qv_off);
-    __shared__ float m_s[PPO_MAX_L];
-    for (int i = tid; i < L; i += kClPreThreads) m_s[i] = mi[i];
-    __syncthreads();
     if (tid == 0) {
         double acc = 0.0;
         P[0] = 0.0;
         for (int i = 0; i < L; ++i) {
-            acc = acc + (double)m_s[i];
+            acc = acc + (double)mi[i];
             P[i + 1] = acc;
         }
         dec[0] = 0.0f;
@@ -164,12 +161,11 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
         base[y.ord_off + pos] = (unsigned char)i;
     }
     __syncthreads();
-    // a wave per link
-    for (int p = tid >> 6; p < y.npairs; p += kClPreThreads / 64) {
+    for (int idx = tid; idx < y.nq; idx += kClPreThreads) {
+        const int p = idx / (L - 1), r = idx - p * (L - 1);
         int a = 0, rem = p;
         while (rem >= n - 1 - a) { rem -= n - 1 - a; ++a; }
-        const float bw = Bi[a * n + a + 1 + rem];
-        for (int r = tid & 63; r < L - 1; r += 64) qv[p * (L - 1) + r] = __fdiv_rn(t_s[ord_s[r]], bw);
+        qv[idx] = __fdiv_rn(t_s[ord_s[r]], Bi[a * n + a + 1 + rem]);
     }
 }
 
@@ -723,7 +719,12 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
         }
         query[i] = o1 | (o2 << 16);
     }
-    atomicMax(&top_s, top_run);
+    // (an atomic by every thread made 73 us of the 65 that a staged search of 1024 instances of (12, 5) takes)
+    for (int off = 32; off >= 1; off >>= 1) {
+        const int o = __shfl_xor(top_run, off, 64);
+        top_run = o > top_run ? o : top_run;
+    }
+    if ((tid & 63) == 0) atomicMax(&top_s, top_run);
     __syncthreads();
     if (tid == 0) query[n * per_node] = (uint32_t)top_s;
 }

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(64) void heuristic_kernel(const float* __restrict__
         // ---- joint system: from every start node, always on over the best link to a free node; the best start
         if (lane == 0) {
             float best_beta = inf;
-            int best_first = -1;
+            int best_first = 0;   // also if a quotient of every start overflows to +inf
             for (int first = 0; first < n; ++first) {
                 unsigned long long used = 1ull << first;
                 int cur = first;

@@ -114,6 +114,23 @@ def test_comparison_systems(ppo):
                     assert list(got[2][i][:p - 1]) == list(cuts) and list(got[3][i][:p]) == list(nodes)
 
 
+def test_quotients_that_overflow(ppo):
+    """Finite sizes over finite bandwidths whose quotients are +inf from every start node: the placement stands, its
+    bottleneck is +inf."""
+    import torch
+    w = W.cluster_geometric(6, 32, n_inst=3, seed=95)
+    t, B = (w.t * np.float32(1e30)).astype(np.float32), (w.B * np.float32(1e-20)).astype(np.float32)
+    assert np.isfinite(t).all() and np.isfinite(B).all()
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (t, w.m, w.M[:, 0], B)]
+    jb, js, jc, jo = (x.cpu().numpy() for x in ppo.ppo_place_baseline(*dev, ppo.PPO_BASELINE_JOINT))
+    torch.cuda.synchronize()
+    for i in range(w.n_inst):
+        with np.errstate(over="ignore"):
+            b, p, cuts, nodes = H.joint_baseline(t[i], w.m[i], w.M[i][0], B[i])
+        assert np.isinf(b) and p >= 2 and bits(jb[i]) == bits(b) and js[i] == p
+        assert list(jc[i][:p - 1]) == list(cuts) and list(jo[i][:p]) == list(nodes)
+
+
 def test_the_exact_optimum_is_never_beaten(ppo):
     """Sec. V's approximation ratio with the true optimum in place of Theorem 1's bound."""
     import torch

@@ -25,7 +25,7 @@ hipError_t launch_cluster_few_tables(const float*, const float*, const float*, c
                                      hipStream_t);
 hipError_t launch_cluster_few_solve(const float*, const float*, int, int, int, int, void*, void*, float*, int32_t*, int32_t*, int32_t*, hipStream_t);
 size_t cluster_rows_bytes(int L, int n);
-hipError_t launch_cluster_tables(const float*, const float*, const float*, const float*, int, int, int, void*,
+hipError_t launch_cluster_tables(const float*, const float*, const float*, const float*, int, int, int, int, void*,
                                  hipStream_t);
 hipError_t launch_cluster_solve(int, int, int, int, bool, const void*, void*, uint64_t*, float*, int32_t*, int32_t*,
                                 int32_t*, hipStream_t);
@@ -295,7 +295,7 @@ int ppo_solve_cluster(const float* t, const float* m, int L, const float* M, con
     for (int first = 0; first < n_inst; first += kInstPerLaunch) {
         const int cnt = n_inst - first < kInstPerLaunch ? n_inst - first : kInstPerLaunch;
         PPO_HIP(ppo::launch_cluster_tables(t + (size_t)first * L, m + (size_t)first * L, M + (size_t)first * n,
-                                           B + (size_t)first * n * n, L, n, cnt, ws + tables * (size_t)first, s),
+                                           B + (size_t)first * n * n, L, n, cnt, pmax, ws + tables * (size_t)first, s),
                 "cluster tables launch");
     }
     for (size_t first = 0; first < (size_t)n_inst; first += together) {

@@ -14,80 +14,14 @@
 // level in |R|, one launch per level, one wave per row, on 16-bit order codes of the quotients.  The
 // lexicographically smallest optimal sequence (a sequence before its extensions) is rebuilt position by
 // position from the cuts the prefix reaches within beta* and the rows of A, then the cuts by the fixed-k cut rule.
+// Where it pays, the search runs on the nodes and cuts that can matter alone (ppo_cluster_bound.hip); the kernels after it
+// take an instance's own number of nodes and layers from its tables.
 #include <array>
 #include <utility>
 
-#include "ppo_common.h"
+#include "ppo_cluster.h"
 
 namespace ppo {
-
-// Codes as in the fixed-k kernels: kCodeZero for the value 0, kCodeZero + 1 + #{smaller quotients}, kCodeInf for
-// +inf: positive normal binary16 patterns, so the three-input binary16 minimum acts as an integer minimum.
-// Everything these kernels read as a code is written by them as one (a stray pattern could win that minimum).
-constexpr uint32_t kClZero = kCodeZero, kClInf = kCodeInf;
-constexpr int kClPreThreads = 1024;
-static_assert((int)kClZero + (PPO_CLUSTER_MAX_N * (PPO_CLUSTER_MAX_N - 1) / 2) * (PPO_MAX_L - 1) + 1 < (int)kClInf,
-              "codes stay below +inf");
-static_assert(((unsigned long long)PPO_CLUSTER_MAX_N << (PPO_CLUSTER_MAX_N - 1)) * ((PPO_MAX_L + 1) / 2) < (1ull << 32),
-              "the dwords of one instance's rows are counted in 32 bits");
-
-// How the level kernel lays rows over lanes: chains of up to 63 layers (their rows with the entry of the chain's end fit 32
-// lanes of two entries) go two sets to a wave; up to 127 one set; 128 layers one set, with an entry beyond the lanes.
-enum { kClTwoSets = 0, kClOneSet = 1, kClWide = 2 };
-__host__ __device__ constexpr int cluster_mode(int L) { return L <= 63 ? kClTwoSets : L <= 127 ? kClOneSet : kClWide; }
-__host__ __device__ constexpr int cluster_sets_per_wave(int mode) { return mode == kClTwoSets ? 2 : 1; }
-// Run minima of a wave: rows of kClRunPitch dwords for runs of 2^0, 2^1 .. entries, then entries that are +inf, for windows
-// that are empty (two sets: the second one's lie 32 dwords on).
-__host__ __device__ constexpr int cluster_run_pitch(int mode) { return mode == kClWide ? 80 : 64; }
-__host__ __device__ constexpr int cluster_run_levels(int mode) { return mode == kClTwoSets ? 6 : 7; }
-__host__ __device__ constexpr int cluster_run_dwords(int mode) {
-    return cluster_run_levels(mode) * cluster_run_pitch(mode) + (mode == kClTwoSets ? 36 : 4);
-}
-
-struct ClusterLayout {
-    int L, n, npairs, nq, rs;                       // rs: entries per row of A: 0..L-1 (entry L is never finite
-                                                    // and not stored), rounded up to even
-    uint32_t hi_off, qc_off, dec_off, qv_off, ord_off, img_off, stride;   // bytes within one instance's tables
-
-    __host__ __device__ static ClusterLayout make(int L, int n) {
-        ClusterLayout y;
-        y.L = L;
-        y.n = n;
-        y.npairs = n * (n - 1) / 2;
-        y.nq = y.npairs * (L - 1);
-        y.rs = (L + 1) & ~1;
-        size_t off = 0;
-        y.hi_off = (uint32_t)off;
-        off = align_up(off + (size_t)n * (L + 1), 16);
-        y.qc_off = (uint32_t)off;
-        off = align_up(off + (size_t)y.npairs * L * 2, 16);
-        y.dec_off = (uint32_t)off;
-        off = align_up(off + ((size_t)y.nq + 1) * 4, 16);
-        y.qv_off = (uint32_t)off;
-        off = align_up(off + (size_t)y.nq * 4, 16);
-        y.ord_off = (uint32_t)off;   // the layers 0 .. L-2 in increasing order of t (one byte each)
-        off = align_up(off + (size_t)L, 256);
-        // what the level kernel keeps in LDS, ready to be copied: quotient rows (rs / 2 dwords each, the pitch of the rows
-        // of A), then the window queries of every (node, entry); and the longest run that a query asks for
-        y.img_off = (uint32_t)off;
-        off = align_up(off + y.q_image_bytes() + y.query_bytes() + 16, 256);
-        y.stride = (uint32_t)off;
-        return y;
-    }
-    // bytes of the quotient rows in the LDS image (the window queries follow, 16-byte aligned): two sets to a wave, of
-    // every ordered pair, so that a lane finds the row of (j, j'') by one addition; one set, of every pair a < b, at
-    // below(b) + a (half the space, and the offset is the wave's)
-    __host__ __device__ size_t q_image_bytes() const {
-        return align_up((size_t)(cluster_mode(L) == kClTwoSets ? n * n : npairs) * (rs / 2) * 4, 16);
-    }
-    __host__ __device__ size_t query_bytes() const { return (size_t)n * (128 / cluster_sets_per_wave(cluster_mode(L))) * 4; }
-    // pair a < b is row below(b) + a.  below(j) + m > below(m) + j for m < j, so that the larger of the two is the row of
-    // the pair in either order (the value for node 0, which is never the larger one, is chosen for that).
-    __host__ __device__ static constexpr int below(int b) { return b ? (int)((uint32_t)(b * (b - 1)) >> 1) : -2; }
-    // rows A[R][j] exist for j in R only: n 2^(n-1) of them per instance
-    __host__ __device__ size_t rows_per_instance() const { return (size_t)n << (n - 1); }
-    __host__ __device__ size_t rows_bytes() const { return rows_per_instance() * (size_t)rs * sizeof(uint16_t); }
-};
 
 // Row number of A[R][j], j in R: the rows of the sets before R in numeric order (the sum of their sizes),
 // then the members of R in increasing order.  The sum of the sizes of all sets below R: a member b of R
@@ -133,6 +67,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
             P[i + 1] = acc;
         }
         dec[0] = 0.0f;
+        *reinterpret_cast<uint32_t*>(base + y.flag_off()) = 0u;
     }
     __syncthreads();
     for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) {
@@ -174,10 +109,13 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const flo
 // search each).  Serial searches bound it, and slices are few (75 at 20 nodes and 100 layers): one thread per quotient
 // took 54 us there.
 constexpr int kClCountSlice = 256, kClCountParts = 4, kClCountThreads = kClCountSlice * kClCountParts;
-__global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterLayout y, unsigned char* __restrict__ ws) {
+__global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterLayout whole, unsigned char* __restrict__ ws) {
     extern __shared__ __align__(16) float cl_rows[];   // [npairs][L-1], then the sums of the slice
-    const int L = y.L, nq = y.nq, len = L - 1, inst = blockIdx.y, tid = threadIdx.x;
-    unsigned char* base = ws + (size_t)inst * y.stride;
+    const int inst = blockIdx.y, tid = threadIdx.x;
+    unsigned char* base = ws + (size_t)inst * whole.stride;
+    const ClusterLayout y = cluster_layout(whole, base);
+    const int L = y.L, nq = y.nq, len = L - 1;
+    if ((int)blockIdx.x * kClCountSlice >= nq) return;
     const float* __restrict__ qv = reinterpret_cast<const float*>(base + y.qv_off);
     int* below_s = reinterpret_cast<int*>(cl_rows + nq);
     for (int i = tid; i < nq; i += kClCountThreads) cl_rows[i] = qv[i];
@@ -186,14 +124,15 @@ __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterL
     const int mine = tid & (kClCountSlice - 1), idx = blockIdx.x * kClCountSlice + mine;
     const float x = cl_rows[idx < nq ? idx : nq - 1];
     int below = 0;
+    int widest = 64;
+    while (widest > len) widest >>= 1;
     // four links at a time, so that four reads are in flight at every step of the searches
     for (int p0 = 4 * (tid / kClCountSlice); p0 < y.npairs; p0 += 4 * kClCountParts) {
         int pos[4] = {0, 0, 0, 0};   // number of entries of each row below x
         const float* row[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) row[u] = cl_rows + (p0 + u < y.npairs ? p0 + u : p0) * len;
-#pragma unroll
-        for (int step = 64; step >= 1; step >>= 1) {
+        for (int step = widest; step >= 1; step >>= 1) {
             float v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -257,13 +196,14 @@ constexpr ClusterBinomials kClBinomialsHost = ClusterBinomials();
 __constant__ ClusterBinomials kClBinomials = ClusterBinomials();
 
 // also gives the set's first row (cluster_first_row), gathered on the way: members come out highest first
-__device__ __forceinline__ uint32_t cluster_set_at(uint32_t index, int size, int n, uint32_t& first_row) {
+template <typename Table>
+__device__ __forceinline__ uint32_t cluster_set_at(const Table& choose, uint32_t index, int size, int n, uint32_t& first_row) {
     uint32_t set = 0, rows = 0, above = 0;
     int b = n;
     for (int i = size; i >= 1; --i) {
-        do { --b; } while (kClBinomials.c[b][i] > index);
+        do { --b; } while (choose[b][i] > index);
         set |= 1u << b;
-        index -= kClBinomials.c[b][i];
+        index -= choose[b][i];
         rows += (above << b) + (((uint32_t)b << b) >> 1);
         ++above;
     }
@@ -301,6 +241,8 @@ __device__ __forceinline__ uint32_t cl_pk_min3(uint32_t a, uint32_t b, uint32_t 
     return r;
 }
 
+extern __shared__ __align__(16) unsigned char cl_smem[];   // of the level kernel
+
 // the next larger set of as many nodes, and its first row
 __device__ __forceinline__ uint32_t cluster_next_set(uint32_t set, uint32_t& first_row) {
     const uint32_t low = set & (0u - set), up = set + low;
@@ -315,12 +257,106 @@ __device__ __forceinline__ uint32_t cluster_next_set(uint32_t set, uint32_t& fir
     return set;
 }
 
+// The same for an instance on fewer nodes and cuts: G sets to a wave, 64 / G lanes of two entries each, with every set's
+// values in its lanes (C <= n - 1).  The parts of a wave take a run of consecutive sets each.  15 nodes of a paper-shaped
+// cluster keep 11 to 18 of their 50 layers: four or eight sets to a wave.
+template <int C, int G>
+__device__ __forceinline__ void cluster_level_parts(const ClusterLayout y, const uint32_t* query, uint32_t* run32, uint32_t* A32,
+                                                    const uint32_t (*choose)[PPO_CLUSTER_MAX_N + 1], bool more, int run_top, int lane,
+                                                    uint32_t wave_index, uint32_t total_waves) {
+    constexpr int CA = C > 0 ? C : 1, kLanes = 64 / G, kRuns = G == 2 ? 6 : G < 8 ? 5 : 4;
+    constexpr bool kRows16 = G == 4 || G == 8;   // a set's lanes lie in one row of 16
+    const bool spare = lane >= G * kLanes;       // five and six sets leave four lanes
+    const int part = spare ? G - 1 : lane / kLanes, hl = lane - part * kLanes, n = y.n, rd = y.rs / 2, L = y.L;
+    const uint32_t inf2 = kClInf | (kClInf << 16), all = (1u << n) - 1u;
+    const int e0 = 2 * hl, e1 = e0 + 1;
+    const uint32_t end_keep = (e0 == L ? 0u : 0xFFFFu) | (e1 == L ? 0u : 0xFFFF0000u);   // rest[L] = 0
+    const uint32_t end_set = (e0 == L ? kClZero : 0u) | (e1 == L ? kClZero << 16 : 0u);
+    const uint32_t nsets = (uint32_t)__builtin_amdgcn_readfirstlane((int)choose[n][C]);
+    const uint32_t per = (nsets + total_waves * (uint32_t)G - 1u) / (total_waves * (uint32_t)G);
+    const uint32_t u = (wave_index * (uint32_t)G + (uint32_t)part) * per;
+    const uint32_t u_end = spare ? u : u + per < nsets ? u + per : nsets;
+    uint32_t mp = (1u << C) - 1u, first_row = 0;
+    if (u < u_end) mp = cluster_set_at(choose, u, C, n, first_row);
+    const unsigned char* runb = reinterpret_cast<const unsigned char*>(run32) + part * (kLanes * 4);
+    const uint32_t q_node = (uint32_t)(rd * 4);
+    for (uint32_t it = 0; it < per; ++it) {
+        const bool mine = u + it < u_end;
+        if (__ballot(mine) == 0ull) break;
+        uint32_t a[CA], moff[CA];
+        {
+            const uint32_t* arow = A32 + first_row * (uint32_t)rd + (uint32_t)hl;
+            uint32_t bits = mp;
+#pragma unroll
+            for (int m = 0; m < C; ++m) {
+                moff[m] = __umul24((uint32_t)__builtin_ctz(bits), q_node) + (uint32_t)hl * 4u;
+                bits &= bits - 1u;
+                a[m] = (more && hl < rd) ? arow[m * rd] : inf2;
+            }
+        }
+        uint32_t jb = all & ~mp;
+        for (int left = n - C; left > 0; --left) {
+            const uint32_t j = (uint32_t)__builtin_ctz(jb);
+            jb &= jb - 1u;
+            const uint2 qd = *reinterpret_cast<const uint2*>(query + j * 64u + e0);
+            uint32_t v = inf2;
+            if (more) {
+                const uint32_t qj = __umul24(j, (uint32_t)n * q_node);
+                uint32_t x[CA];
+#pragma unroll
+                for (int m = 0; m < C; ++m) x[m] = cl_pk_max(*reinterpret_cast<const uint32_t*>(cl_smem + qj + moff[m]), a[m]);
+#pragma unroll
+                for (int m = 0; m + 1 < C; m += 2) v = cl_pk_min3(v, x[m], x[m + 1]);
+                if (C & 1) v = cl_pk_min(v, x[C - 1]);
+            }
+            v = (v & end_keep) | end_set;
+            // minima over runs (see cluster_level_kernel); four and eight sets: shifts within 16 lanes
+            run32[lane] = v;
+            constexpr int kUp1 = kRows16 ? 0x101 : 0x130;
+            const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kUp1, 0xF, 0xF, true);
+            uint32_t cur = cl_pk_min(v, (v >> 16) | (next << 16));
+            run32[64 + lane] = cur;
+            cur = cl_pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, kUp1, 0xF, 0xF, true));
+            run32[128 + lane] = cur;
+            if (kRows16) {
+                cur = cl_pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, 0x102, 0xF, 0xF, true));
+                run32[192 + lane] = cur;
+                if (G == 4) {
+                    cur = cl_pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, 0x104, 0xF, 0xF, true));
+                    run32[256 + lane] = cur;
+                }
+            } else {
+                const uint32_t up1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, 0x130, 0xF, 0xF, true);
+                cur = cl_pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)up1, 0x130, 0xF, 0xF, true));
+                run32[192 + lane] = cur;
+#pragma unroll
+                for (int r = 4; r < kRuns; ++r) {
+                    if (r > run_top) break;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    cur = cl_pk_min(cur, run32[(r - 1) * 64 + ((lane + (1 << (r - 2))) & 63)]);
+                    run32[r * 64 + lane] = cur;
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t r1 = *reinterpret_cast<const uint16_t*>(runb + (qd.x & 0xFFFFu)) | (uint32_t)*reinterpret_cast<const uint16_t*>(runb + (qd.y & 0xFFFFu)) << 16;
+            const uint32_t r2 = *reinterpret_cast<const uint16_t*>(runb + (qd.x >> 16)) | (uint32_t)*reinterpret_cast<const uint16_t*>(runb + (qd.y >> 16)) << 16;
+            // row of j within R' + j: see cluster_level_kernel
+            const uint32_t below = mp & ((1u << j) - 1u), above = (uint32_t)__popc((mp >> j) >> 1);
+            const uint32_t row = first_row + (above << j) + ((j << j) >> 1) + below + (uint32_t)__popc(below);
+            if (hl < rd && mine) A32[row * (uint32_t)rd + (uint32_t)hl] = cl_pk_min(r1, r2);
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (C > 0 && u + it + 1u < u_end) mp = cluster_next_set(mp, first_row);
+    }
+}
+
 // C = |R'| = level - 1: the rows of the set's members sit in C registers, in the order of the members
 template <int C, int MODE>
 __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
                                                                 const unsigned char* __restrict__ ws,
                                                                 uint16_t* __restrict__ rows, int pmax, int exact) {
-    extern __shared__ __align__(16) unsigned char cl_smem[];
     constexpr int level = C + 1, CA = C > 0 ? C : 1, G = cluster_sets_per_wave(MODE), kLanes = 64 / G;
     constexpr int kPitch = cluster_run_pitch(MODE), kRuns = cluster_run_levels(MODE);
     const int L = y.L, n = y.n, rd = y.rs / 2;
@@ -333,6 +369,34 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
     const uint32_t* query = reinterpret_cast<const uint32_t*>(cl_smem + lds.query_off);
     uint32_t* run32 = reinterpret_cast<uint32_t*>(cl_smem + lds.run_off) + wave * cluster_run_dwords(MODE);
     uint32_t* A32 = reinterpret_cast<uint32_t*>(rows) + (size_t)inst * (y.rows_per_instance() * rd);
+    if (cluster_reduced(y, base)) {
+        const ClusterLayout part = cluster_layout(y, base);
+        if (C >= part.n) return;
+        // as many waves as have a set to work on
+        // entries 0 .. L of a set in its lanes
+        const uint32_t G = part.L <= 15 ? 8u : part.L <= 19 ? 6u : part.L <= 23 ? 5u : part.L <= 31 ? 4u : 2u, nsets = kClBinomials.c[part.n][C];
+        if (blockIdx.x * (uint32_t)waves * G >= nsets) return;
+        const ClusterLds small = ClusterLds::make(part, waves);
+        const uint4* img = reinterpret_cast<const uint4*>(base + part.img_off);
+        for (int i = tid; i < (int)(small.run_off / 16u); i += threads) reinterpret_cast<uint4*>(cl_smem)[i] = img[i];
+        const int top = (int)*reinterpret_cast<const uint32_t*>(base + part.img_off + small.run_off);
+        // a set from its index is a chain of look-ups: the coefficients lie in LDS (read from memory they were half of a level)
+        uint32_t* choose = reinterpret_cast<uint32_t*>(cl_smem + small.run_off);
+        for (int i = tid; i < (int)(kClBinomialBytes / 4u); i += threads) choose[i] = kClBinomials.c[0][i];
+        uint32_t* run = reinterpret_cast<uint32_t*>(cl_smem + small.run_off + kClBinomialBytes) + wave * cluster_run_dwords(kClTwoSets);
+        run[6 * 64 + lane] = kClInf | (kClInf << 16);   // empty windows
+        __syncthreads();
+        const uint32_t* windows = reinterpret_cast<const uint32_t*>(cl_smem + small.query_off);
+        const uint32_t index = blockIdx.x * (uint32_t)waves + (uint32_t)wave, total = gridDim.x * (uint32_t)waves;
+        const bool goes_on = part.n - level + 1 < pmax;
+        const auto coefficients = reinterpret_cast<const uint32_t(*)[PPO_CLUSTER_MAX_N + 1]>(choose);
+        if (G == 8u) cluster_level_parts<C, 8>(part, windows, run, A32, coefficients, goes_on, top, lane, index, total);
+        else if (G == 6u) cluster_level_parts<C, 6>(part, windows, run, A32, coefficients, goes_on, top, lane, index, total);
+        else if (G == 5u) cluster_level_parts<C, 5>(part, windows, run, A32, coefficients, goes_on, top, lane, index, total);
+        else if (G == 4u) cluster_level_parts<C, 4>(part, windows, run, A32, coefficients, goes_on, top, lane, index, total);
+        else cluster_level_parts<C, 2>(part, windows, run, A32, coefficients, goes_on, top, lane, index, total);
+        return;
+    }
     const bool more = n - level + 1 < pmax;   // segments up to and including this row's: n - level + 1
     // quotient rows and window queries: a straight copy of the image the tables kernels left (16 bytes a thread)
     {
@@ -365,7 +429,7 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
     uint32_t u = (blockIdx.x * waves + wave) * per_wave;
     const uint32_t u_end = u + per_wave < nsets ? u + per_wave : nsets;
     uint32_t mp = 0, first_row = 0;
-    if (u < u_end) mp = cluster_set_at(u, C, n, first_row);
+    if (u < u_end) mp = cluster_set_at(kClBinomials.c, u, C, n, first_row);
     for (; u < u_end; u += (uint32_t)G) {
         const bool pair = G == 2 && u + 1u < u_end;
         uint32_t mp2 = mp, first_row2 = first_row;
@@ -495,7 +559,7 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
 // ---------------------------------------------------------------------------------------------
 constexpr int kClTraceWaves = 16;   // at most; a launch uses min(n, 16) waves per workgroup
 
-__global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(ClusterLayout y,
+__global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(ClusterLayout whole,
                                                                           const unsigned char* __restrict__ ws,
                                                                           const uint16_t* __restrict__ rows, int pmax,
                                                                           int exact,
@@ -509,22 +573,36 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
     __shared__ unsigned long long start_s[PPO_CLUSTER_MAX_N][2];   // G of the node chosen at every position
     __shared__ uint32_t ok_s[PPO_CLUSTER_MAX_N];
     __shared__ int seq[PPO_CLUSTER_MAX_N];
-    const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int inst = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned char* base = ws + (size_t)inst * y.stride;
+    const unsigned char* base = ws + (size_t)inst * whole.stride;
+    const ClusterLayout y = cluster_layout(whole, base);
+    const int L = y.L, n = y.n;
     const uint16_t* __restrict__ qc = reinterpret_cast<const uint16_t*>(base + y.qc_off);
     const float* __restrict__ dec = reinterpret_cast<const float*>(base + y.dec_off);
-    const uint16_t* A = rows + (size_t)inst * (y.rows_per_instance() * y.rs);
+    const uint16_t* A = rows + (size_t)inst * (whole.rows_per_instance() * whole.rs);
+    __shared__ unsigned char cut_s[PPO_MAX_L + 1], node_s[PPO_CLUSTER_MAX_N];   // the whole instance's
+    if (cluster_reduced(whole, base)) {
+        const ClusterRecord r = *reinterpret_cast<const ClusterRecord*>(base + whole.record_off());
+        for (int e = tid; e < 128; e += (int)blockDim.x)
+            if ((r.cuts[e >> 6] >> (e & 63)) & 1ull)
+                cut_s[1 + (e >= 64 ? __popcll(r.cuts[0]) : 0) + __popcll(r.cuts[e >> 6] & ((1ull << (e & 63)) - 1ull))] = (unsigned char)e;
+        for (int j = tid; j < whole.n; j += (int)blockDim.x)
+            if ((r.nodes >> j) & 1u) node_s[__popc(r.nodes & ((1u << j) - 1u))] = (unsigned char)j;
+    } else {
+        for (int e = tid; e <= L; e += (int)blockDim.x) cut_s[e] = (unsigned char)e;
+        for (int j = tid; j < n; j += (int)blockDim.x) node_s[j] = (unsigned char)j;
+    }
     // either the key alone (exact: bits of beta, rank of the permutation) or beta, segments, cuts, order
     float* beta = beta_out ? beta_out + inst : nullptr;
-    int32_t* order = order_out ? order_out + (size_t)inst * n : nullptr;
-    int32_t* cuts = cuts_out ? cuts_out + (size_t)inst * (n - 1) : nullptr;
+    int32_t* order = order_out ? order_out + (size_t)inst * whole.n : nullptr;
+    int32_t* cuts = cuts_out ? cuts_out + (size_t)inst * (whole.n - 1) : nullptr;
     const int threads = blockDim.x, waves = threads >> 6;
     for (int i = tid; i < n * (L + 1); i += threads) hi_s[i] = base[y.hi_off + i];
     if (order)
-        for (int i = tid; i < n; i += threads) order[i] = -1;
+        for (int i = tid; i < whole.n; i += threads) order[i] = -1;
     if (cuts)
-        for (int i = tid; i < n - 1; i += threads) cuts[i] = -1;
+        for (int i = tid; i < whole.n - 1; i += threads) cuts[i] = -1;
     __syncthreads();
     auto wave_min = [&](uint32_t v) -> uint32_t {
         for (int off = 32; off >= 1; off >>= 1) {
@@ -572,13 +650,12 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int e = lane + 64 * h;
-                bool in_g = false, in_ok = false;
-                if ((((h ? F1 : F0) >> lane) & 1ull) && e < L) {
-                    in_g = s == 0 || (uint32_t)q[e - 1] <= best;   // beyond the first position F holds no cut 0
-                    in_ok = in_g && (uint32_t)a[e] <= best;
-                }
+                // both requested before either is waited for
+                const uint32_t link = q[e >= 1 && e < L ? e - 1 : 0], row = a[e < L ? e : 0];
+                const bool in_f = (((h ? F1 : F0) >> lane) & 1ull) && e < L;
+                const bool in_g = in_f && (s == 0 || link <= best);   // beyond the first position F holds no cut 0
                 g[h] = __ballot(in_g);
-                ok[h] = __ballot(in_ok);
+                ok[h] = __ballot(in_g && row <= best);
             }
             if (lane == 0) {
                 cand_s[j][0] = g[0];
@@ -587,9 +664,8 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
             }
         }
         __syncthreads();
-        int chosen = -1;
-        for (int j = n - 1; j >= 0; --j)
-            if (ok_s[j]) chosen = j;
+        const unsigned long long ok = __ballot(lane < n && ok_s[lane < n ? lane : 0] != 0u);
+        const int chosen = ok ? __ffsll((long long)ok) - 1 : -1;
         if (chosen < 0) break;   // cannot happen: some completion of the prefix reaches `best`
         const unsigned long long G0 = cand_s[chosen][0], G1 = cand_s[chosen][1];
         if (tid == 0) {
@@ -628,14 +704,14 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
             __ballot(((start_s[s][1] >> lane) & 1ull) && lane + 64 < e && hi(js, lane + 64 < L ? lane + 64 : L) >= e);
         if (!(m0 | m1)) break;   // cannot happen: e was reached from such a start
         const int first = m0 ? __ffsll((long long)m0) - 1 : 63 + __ffsll((long long)m1);
-        if (lane == 0) cuts[s - 1] = (int32_t)first;
+        if (lane == 0) cuts[s - 1] = (int32_t)cut_s[first];
         e = first;
     }
     if (lane == 0) {
         if (beta) *beta = dec[best - kClZero];
         if (segs_out) segs_out[inst] = p;
         if (order)
-            for (int s = 0; s < p; ++s) order[s] = seq[s];
+            for (int s = 0; s < p; ++s) order[s] = node_s[seq[s]];
     }
 }
 
@@ -649,6 +725,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_from_prepared_ke
     const unsigned char* src = fixed_ws + (size_t)inst * f.stride;
     unsigned char* dst = ws + (size_t)inst * y.stride;
     __shared__ unsigned char lo[PPO_MAX_K * (PPO_MAX_L + 1)];
+    if (tid == 0) *reinterpret_cast<uint32_t*>(dst + y.flag_off()) = 0u;
     for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) lo[idx] = src[f.lo_off + idx];
     __syncthreads();
     for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) {
@@ -677,11 +754,13 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_tables_from_prepared_ke
 //   largest with 2^k <= its length: the one starting at e + 1 and the one ending at hi.  The table holds the byte
 //   offsets of their minima within a wave's run minima, 16 bits each; no window: twice an entry that is +inf;
 //   last, the largest k.
-__global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLayout y, unsigned char* __restrict__ ws) {
+__global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLayout whole, unsigned char* __restrict__ ws) {
     __shared__ int top_s;
-    const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x, mode = cluster_mode(L);
+    const int inst = blockIdx.x, tid = threadIdx.x;
+    unsigned char* base = ws + (size_t)inst * whole.stride;
+    const ClusterLayout y = cluster_layout(whole, base);
+    const int L = y.L, n = y.n, mode = cluster_mode(L);
     const int pitch = cluster_run_pitch(mode), per_node = 128 / cluster_sets_per_wave(mode);
-    unsigned char* base = ws + (size_t)inst * y.stride;
     const uint16_t* __restrict__ qc = reinterpret_cast<const uint16_t*>(base + y.qc_off);
     uint16_t* q16 = reinterpret_cast<uint16_t*>(base + y.img_off);
     uint32_t* query = reinterpret_cast<uint32_t*>(base + y.img_off + y.q_image_bytes());
@@ -729,12 +808,27 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
     if (tid == 0) query[n * per_node] = (uint32_t)top_s;
 }
 
+// Whether a search is confined to the nodes and cuts that can matter (ppo_cluster_bound.hip).  That costs about 45 us before
+// the levels and, where little can be left out, saves less: paper-shaped clusters of 16 MB devices keep all their nodes.
+// Measured in us, without and with it: one cluster of 16 such nodes 239 / 234, 16 of 13 nodes 236 / 224, 128 of 11 nodes 277 /
+// 229, but 128 of 10 nodes 177 / 185, 16 of 12 nodes 162 / 187, one of 14 nodes 176 / 193.  (Mixed capacities, 100 layers: one of
+// 20 nodes 2040 / 135, one of 16 nodes 309 / 178, 128 of 11 nodes 418 / 218.)  With fewer segments allowed than nodes the upper
+// levels are not searched, and those that are start from the nodes' number, which the host would not know.
+static bool cluster_confined(int n, int n_inst, int pmax) {
+    return pmax == n && (n >= 16 || (n >= 11 && ((unsigned long long)n_inst * (unsigned long long)n << (n - 1)) >= 800000ull));
+}
+
 hipError_t launch_cluster_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
-                                 int n_inst, void* ws, hipStream_t stream) {
+                                 int n_inst, int pmax, void* ws, hipStream_t stream) {
     const ClusterLayout y = ClusterLayout::make(L, n);
     unsigned char* w = static_cast<unsigned char*>(ws);
-    hipLaunchKernelGGL(cluster_tables_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, t, m, M, B, y, w);
-    hipError_t e = hipGetLastError();
+    hipError_t e;
+    if (cluster_confined(n, n_inst, pmax)) {
+        e = launch_cluster_reduce(t, m, M, B, y, n_inst, w, stream);
+    } else {
+        hipLaunchKernelGGL(cluster_tables_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, t, m, M, B, y, w);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
     if (y.nq > 0) {
         const int slices = (y.nq + kClCountSlice - 1) / kClCountSlice;

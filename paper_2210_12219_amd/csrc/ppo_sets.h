@@ -33,6 +33,21 @@ constexpr SetTables kSetsHost = SetTables();
 static __constant__ SetTables kSets = SetTables();   // one for each file that includes this
 static_assert((PPO_MAX_K << (PPO_MAX_K - 1)) < 65536, "a row's number fits 16 bits");
 
+// The same by the value of a set: its first row | its place among the sets of its size << 16; and where the sets of every
+// size start, in increasing order of size, among those of k nodes.
+struct SetValues {
+    uint32_t row_and_place[1 << PPO_MAX_K];
+    uint32_t level[PPO_MAX_K + 1][PPO_MAX_K + 2];
+    constexpr SetValues() : row_and_place{}, level{} {
+        const SetTables by_size;
+        for (int c = 0; c <= PPO_MAX_K; ++c)
+            for (int i = by_size.first[c]; i < by_size.first[c + 1]; ++i)
+                row_and_place[by_size.order[i] & 0xFFFFu] = (by_size.order[i] >> 16) | ((uint32_t)(i - by_size.first[c]) << 16);
+        for (int k = 0; k <= PPO_MAX_K; ++k)
+            for (int c = 0; c <= k; ++c) level[k][c + 1] = level[k][c] + by_size.choose[k][c];
+    }
+};
+
 __device__ __forceinline__ uint32_t row_of(uint32_t set_first_row, uint32_t mp, uint32_t j) {
     // first row of R' + j from the first row of R' (j not in R'), then j's place among the members
     const uint32_t below = mp & ((1u << j) - 1u);

@@ -1,0 +1,63 @@
+"""ppo_solve_cluster on the nodes and cuts that can matter: batches large enough for that are compared element by element
+with the same instances one at a time, which are searched whole.  The number of cuts left decides how many sets share a
+wave, so it is set here: `cheap` of the transfer sizes are 1, the rest far above."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import ppo_cluster_oracle as O
+from paper_2210_12219_amd import workloads as W
+
+
+def check(w, oracle=0):
+    import torch
+    from paper_2210_12219_amd import binding as ppo
+    dev = ppo.to_device(w)
+    got = [x.cpu().numpy() for x in ppo.ppo_solve_cluster(*dev)]
+    for i in range(w.n_inst):
+        one = [x.cpu().numpy()[0] for x in ppo.ppo_solve_cluster(*(x[i:i + 1].contiguous() for x in dev))]
+        assert got[0][i].view(np.uint32) == one[0].view(np.uint32) and got[1][i] == one[1], i
+        assert np.array_equal(got[2][i], one[2]) and np.array_equal(got[3][i], one[3]), i
+    for i in range(oracle):
+        b, p, cuts, order = O.subset_dp(w.t[i], w.m[i], w.M[i], w.B[i])
+        assert got[0][i].view(np.uint32) == np.float32(b).view(np.uint32) and got[1][i] == p
+        assert np.array_equal(got[2][i], cuts) and np.array_equal(got[3][i], order)
+    return got
+
+
+def batch(n):
+    """instances of n nodes that are searched on what can matter"""
+    return -(-800000 // (n << (n - 1)))
+
+
+@pytest.mark.parametrize("cheap", [1, 5, 14, 15, 18, 19, 22, 23, 30, 31, 32, 60, 61, 62, 63, 99])
+def test_cuts_left(cheap):
+    w = W.cluster_mixed(13, L=100, n_inst=batch(13), seed=900 + cheap, capacity_factor=0.4)
+    rng = np.random.default_rng(cheap)
+    for i in range(w.n_inst):
+        w.t[i] = 1e6 * (1 + rng.random(w.L))
+        w.t[i, rng.permutation(w.L - 1)[:cheap]] = 1.0 + (rng.random(cheap) if i % 2 else 0.0)
+        w.m[i] = 1.0
+        w.M[i] = rng.choice([12.0, 25.0, 50.0], w.k) if i % 3 else 30.0
+        if i % 4 < 2:
+            w.B[i] = np.where(np.eye(w.k, dtype=bool), 0, 2.0)
+    check(w, oracle=1)
+
+
+@pytest.mark.parametrize("n,L", [(11, 2), (11, 64), (12, 128), (13, 63), (14, 127), (15, 17)])
+def test_ties_zeros_and_capacities(n, L):
+    w = W.random_instances(950 + n, batch(n), L, n, capacity_factor=1.5, quantised=L % 2 == 0)
+    rng = np.random.default_rng(n)
+    w.M[...] *= np.exp(rng.uniform(np.log(0.1), np.log(20.0), (w.n_inst, 1))).astype(np.float32)   # from none that fits to any
+    for i in range(0, w.n_inst, 3):
+        w.t[i, rng.random(L) < 0.4] = 0.0
+        w.t[i, rng.random(L) < 0.2] = -0.0
+    check(w, oracle=2 if n < 13 else 0)
+
+
+def test_paper_shaped_clusters():
+    """one capacity, many ties: nine nodes may be too few to hold the chain, and no node is left out"""
+    for capacity in (10.0, 16.0, 64.0, 200.0):
+        check(W.cluster_geometric(12, capacity, n_inst=batch(12), seed=int(capacity)), oracle=1)
+    check(W.cluster_mixed(16, L=100, n_inst=2, seed=3))

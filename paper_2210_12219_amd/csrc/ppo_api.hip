@@ -27,9 +27,10 @@ hipError_t launch_cluster_few_solve(const float*, const float*, int, int, int, i
 size_t cluster_rows_bytes(int L, int n);
 hipError_t launch_cluster_tables(const float*, const float*, const float*, const float*, int, int, int, int, void*,
                                  hipStream_t);
-hipError_t launch_cluster_solve(int, int, int, int, bool, const void*, void*, uint64_t*, float*, int32_t*, int32_t*,
-                                int32_t*, hipStream_t);
-hipError_t launch_cluster_tables_from_prepared(const Layout&, const void*, int, void*, hipStream_t);
+hipError_t launch_cluster_solve(int, int, int, int, const void*, void*, float*, int32_t*, int32_t*, int32_t*, hipStream_t);
+size_t bands_slot_bytes(int L, int k);
+int bands_resident(int k);
+hipError_t launch_bands_keys(const Layout&, const void*, int, uint64_t*, void*, size_t, hipStream_t);
 hipError_t launch_min_sum_partition(const float*, const float*, int, const float*, int, int32_t*, int32_t*, double*,
                                     hipStream_t);
 hipError_t launch_valu_probe(int, int, uint32_t*, hipStream_t);
@@ -122,9 +123,9 @@ int run_subset_solve(const float* t, const float* m, int L, const float* M, cons
 
 // Row areas that keep every compute unit busy: one per instance, at most as many as workgroups stay resident at once,
 // at most 1 GiB of them.
-size_t wanted_slots(size_t slot, int n_inst) {
+size_t wanted_slots(size_t slot, int n_inst, int resident = 1024) {
     size_t want = ((size_t)1 << 30) / slot;
-    if (want > 1024) want = 1024;
+    if (want > (size_t)resident) want = (size_t)resident;
     if (want > (size_t)n_inst) want = (size_t)n_inst;
     return want;
 }
@@ -234,26 +235,13 @@ int ppo_solve_subsets(int L, int k, int n_inst, const void* workspace, size_t wo
     if (bad_keys(best_key) || bad_workspace(workspace)) return PPO_EINVAL;
     if (workspace_bytes < ppo_workspace_bytes(L, k, n_inst)) return PPO_ENOSPC;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const ppo::Layout y = ppo::Layout::make(L, k);
-    // the engine of the cluster form with every node to be used: its own copy of the tables and the DP rows,
-    // for as many instances at a time as fit in 1 GiB
-    const size_t tables = ppo::cluster_tables_bytes(L, k), rows = ppo::cluster_rows_bytes(L, k);
-    size_t batch = ((size_t)1 << 30) / (tables + rows);
-    if (batch < 1) batch = 1;
-    if (batch > (size_t)n_inst) batch = (size_t)n_inst;
-    if (batch > (size_t)kInstPerLaunch) batch = (size_t)kInstPerLaunch;
-    unsigned char* scratch = nullptr;
-    PPO_HIP(hipMallocAsync(reinterpret_cast<void**>(&scratch), (tables + rows) * batch, s), "hipMallocAsync (subset DP rows)");
-    hipError_t e = hipSuccess;
-    for (size_t first = 0; first < (size_t)n_inst && e == hipSuccess; first += batch) {
-        const int n = (int)(((size_t)n_inst - first < batch) ? (size_t)n_inst - first : batch);
-        e = ppo::launch_cluster_tables_from_prepared(y, static_cast<const unsigned char*>(workspace) + first * y.stride, n,
-                                                     scratch, s);
-        if (e == hipSuccess)
-            e = ppo::launch_cluster_solve(L, k, n, k, true, scratch, scratch + tables * batch, best_key + first, nullptr,
-                                          nullptr, nullptr, nullptr, s);
-    }
-    const hipError_t e2 = hipFreeAsync(scratch, s);
+    // rows in LDS, or in areas for as many instances at a time as stay resident and as there is memory for
+    const size_t slot = ppo::bands_slot_bytes(L, k);
+    void* areas = nullptr;
+    size_t count = 0;
+    if (slot) PPO_HIP(alloc_areas(slot, wanted_slots(slot, n_inst, ppo::bands_resident(k)), &areas, &count, s), "hipMallocAsync (subset DP rows)");
+    const hipError_t e = ppo::launch_bands_keys(ppo::Layout::make(L, k), workspace, n_inst, best_key, areas, count, s);
+    const hipError_t e2 = slot ? hipFreeAsync(areas, s) : hipSuccess;
     PPO_HIP(e, "subset DP launch");
     PPO_HIP(e2, "hipFreeAsync (subset DP rows)");
     return PPO_OK;
@@ -300,7 +288,7 @@ int ppo_solve_cluster(const float* t, const float* m, int L, const float* M, con
     }
     for (size_t first = 0; first < (size_t)n_inst; first += together) {
         const int cnt = (int)(((size_t)n_inst - first < together) ? (size_t)n_inst - first : together);
-        PPO_HIP(ppo::launch_cluster_solve(L, n, cnt, pmax, false, ws + tables * first, row_area, nullptr, beta_out + first,
+        PPO_HIP(ppo::launch_cluster_solve(L, n, cnt, pmax, ws + tables * first, row_area, beta_out + first,
                                           segs_out + first, cuts_out ? cuts_out + first * (size_t)(n - 1) : nullptr,
                                           order_out + first * (size_t)n, s),
                 "cluster DP launch");

@@ -356,7 +356,7 @@ __device__ __forceinline__ void cluster_level_parts(const ClusterLayout y, const
 template <int C, int MODE>
 __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
                                                                 const unsigned char* __restrict__ ws,
-                                                                uint16_t* __restrict__ rows, int pmax, int exact) {
+                                                                uint16_t* __restrict__ rows, int pmax) {
     constexpr int level = C + 1, CA = C > 0 ? C : 1, G = cluster_sets_per_wave(MODE), kLanes = 64 / G;
     constexpr int kPitch = cluster_run_pitch(MODE), kRuns = cluster_run_levels(MODE);
     const int L = y.L, n = y.n, rd = y.rs / 2;
@@ -406,11 +406,9 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
         for (int i = first + tid; i < count; i += threads) dst[i] = img[i];
     }
     const int run_top = (int)*reinterpret_cast<const uint32_t*>(base + y.img_off + lds.run_off);
-    // with every node to be used (exact), the chain may end (rest[L] = 0) only after the last node
-    const bool may_end = !exact || C == 0;
     const uint32_t inf2 = kClInf | (kClInf << 16);
     // 128 layers: entry 128 of rest follows the lanes' in every run row, +inf after it; these never change
-    const uint32_t after_last = may_end ? kClZero | (kClInf << 16) : inf2;
+    const uint32_t after_last = kClZero | (kClInf << 16);
     if (MODE == kClWide)
         for (int i = lane; i < kRuns * (kPitch - 64); i += 64)
             run32[i / (kPitch - 64) * kPitch + 64 + i % (kPitch - 64)] = i % (kPitch - 64) ? inf2 : after_last;
@@ -419,8 +417,8 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
     const uint32_t all = (1u << n) - 1u;
     const int e0 = 2 * hl, e1 = e0 + 1;
     // rest[L] = 0: the half of entry L is cleared and set to the code of 0
-    const uint32_t end_keep = !may_end ? ~0u : (e0 == L ? 0u : 0xFFFFu) | (e1 == L ? 0u : 0xFFFF0000u);
-    const uint32_t end_set = !may_end ? 0u : (e0 == L ? kClZero : 0u) | (e1 == L ? kClZero << 16 : 0u);
+    const uint32_t end_keep = (e0 == L ? 0u : 0xFFFFu) | (e1 == L ? 0u : 0xFFFF0000u);
+    const uint32_t end_set = (e0 == L ? kClZero : 0u) | (e1 == L ? kClZero << 16 : 0u);
     // A wave takes a run of consecutive sets: the first from its index (binomial table, a chain of dependent
     // scalar loads), each further one from the one before (the next larger number with as many bits set).
     const uint32_t nsets = kClBinomials.c[n][C];
@@ -562,8 +560,6 @@ constexpr int kClTraceWaves = 16;   // at most; a launch uses min(n, 16) waves p
 __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(ClusterLayout whole,
                                                                           const unsigned char* __restrict__ ws,
                                                                           const uint16_t* __restrict__ rows, int pmax,
-                                                                          int exact,
-                                                                          unsigned long long* __restrict__ key_out,
                                                                           float* __restrict__ beta_out,
                                                                           int32_t* __restrict__ segs_out,
                                                                           int32_t* __restrict__ cuts_out,
@@ -593,14 +589,12 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
         for (int e = tid; e <= L; e += (int)blockDim.x) cut_s[e] = (unsigned char)e;
         for (int j = tid; j < n; j += (int)blockDim.x) node_s[j] = (unsigned char)j;
     }
-    // either the key alone (exact: bits of beta, rank of the permutation) or beta, segments, cuts, order
-    float* beta = beta_out ? beta_out + inst : nullptr;
-    int32_t* order = order_out ? order_out + (size_t)inst * whole.n : nullptr;
+    float* beta = beta_out + inst;
+    int32_t* order = order_out + (size_t)inst * whole.n;
     int32_t* cuts = cuts_out ? cuts_out + (size_t)inst * (whole.n - 1) : nullptr;
     const int threads = blockDim.x, waves = threads >> 6;
     for (int i = tid; i < n * (L + 1); i += threads) hi_s[i] = base[y.hi_off + i];
-    if (order)
-        for (int i = tid; i < whole.n; i += threads) order[i] = -1;
+    for (int i = tid; i < whole.n; i += threads) order[i] = -1;
     if (cuts)
         for (int i = tid; i < whole.n - 1; i += threads) cuts[i] = -1;
     __syncthreads();
@@ -617,9 +611,8 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
     const uint32_t best = wave_min(lane < n ? (uint32_t)A[((size_t)cluster_first_row(all, n) + lane) * y.rs] : kClInf);
     if (best >= kClInf) {
         if (tid == 0) {
-            if (key_out) key_out[inst] = (unsigned long long)kInfBits << 32;
-            if (beta) *beta = __uint_as_float(kInfBits);
-            if (segs_out) segs_out[inst] = 0;
+            *beta = __uint_as_float(kInfBits);
+            segs_out[inst] = 0;
         }
         return;
     }
@@ -673,8 +666,8 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
             start_s[s][0] = G0;
             start_s[s][1] = G1;
         }
-        // the prefix itself is optimal: it sorts before its extensions (exact: only a full permutation ends)
-        const bool complete = exact ? s == n - 1 : covered(G0, G1, chosen, L);
+        // the prefix itself is optimal: it sorts before its extensions
+        const bool complete = covered(G0, G1, chosen, L);
         F0 = __ballot(lane >= 1 && lane < L && covered(G0, G1, chosen, lane));
         F1 = __ballot(lane + 64 < L && covered(G0, G1, chosen, lane + 64));
         __syncthreads();
@@ -684,16 +677,6 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
         if (complete) break;
     }
     if (wave != 0) return;
-    if (key_out && lane == 0) {
-        // lexicographic rank of the permutation: digit s counts the smaller nodes not used before position s
-        uint32_t rank = 0, seen = 0;
-        for (int s = 0; s < p; ++s) {
-            rank += (uint32_t)__popc(~seen & ((1u << seq[s]) - 1u)) * factorial_u32(n - 1 - s);
-            seen |= 1u << seq[s];
-        }
-        key_out[inst] = ((unsigned long long)__float_as_uint(dec[best - kClZero]) << 32) | rank;
-    }
-    if (!cuts && !beta) return;
     // cuts: latest segment first, each time the smallest start (reached by the prefix, link at most beta*)
     // whose window covers the end
     int e = L;
@@ -708,44 +691,10 @@ __global__ __launch_bounds__(kClTraceWaves * 64) void cluster_trace_kernel(Clust
         e = first;
     }
     if (lane == 0) {
-        if (beta) *beta = dec[best - kClZero];
-        if (segs_out) segs_out[inst] = p;
-        if (order)
-            for (int s = 0; s < p; ++s) order[s] = node_s[seq[s]];
+        *beta = dec[best - kClZero];
+        segs_out[inst] = p;
+        for (int s = 0; s < p; ++s) order[s] = node_s[seq[s]];
     }
-}
-
-// ---------------------------------------------------------------------------------------------
-// The tables of this file from those of the fixed-k precompute kernel (window starts lo, quotient codes from
-// kCodeZero + 1 up): hi[j][e] = last e' with lo[j][e'] <= e; codes and dec are the same.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kClPreThreads) void cluster_tables_from_prepared_kernel(Layout f, const unsigned char* __restrict__ fixed_ws,
-                                                                           ClusterLayout y, unsigned char* __restrict__ ws) {
-    const int L = y.L, n = y.n, inst = blockIdx.x, tid = threadIdx.x;
-    const unsigned char* src = fixed_ws + (size_t)inst * f.stride;
-    unsigned char* dst = ws + (size_t)inst * y.stride;
-    __shared__ unsigned char lo[PPO_MAX_K * (PPO_MAX_L + 1)];
-    if (tid == 0) *reinterpret_cast<uint32_t*>(dst + y.flag_off()) = 0u;
-    for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) lo[idx] = src[f.lo_off + idx];
-    __syncthreads();
-    for (int idx = tid; idx < n * (L + 1); idx += kClPreThreads) {
-        const int j = idx / (L + 1), e = idx - j * (L + 1);
-        int e2 = e, top = L;   // window starts do not decrease
-        while (e2 < top) {
-            const int mid = (e2 + top + 1) >> 1;
-            if (lo[j * (L + 1) + mid] <= e) e2 = mid; else top = mid - 1;
-        }
-        dst[y.hi_off + idx] = (unsigned char)e2;
-    }
-    const uint16_t* qsrc = reinterpret_cast<const uint16_t*>(src + f.qc_off);
-    uint16_t* qdst = reinterpret_cast<uint16_t*>(dst + y.qc_off);
-    for (int idx = tid; idx < y.npairs * L; idx += kClPreThreads) {
-        const int i = idx % L;
-        qdst[idx] = (uint16_t)(i < L - 1 ? qsrc[idx] : kClInf);
-    }
-    const float* dsrc = reinterpret_cast<const float*>(src + f.dec_off);
-    float* ddst = reinterpret_cast<float*>(dst + y.dec_off);
-    for (int idx = tid; idx <= y.nq; idx += kClPreThreads) ddst[idx] = dsrc[idx];
 }
 
 // The image of the level kernel's LDS tables (needs hi and the codes): one workgroup per instance.
@@ -847,23 +796,23 @@ hipError_t launch_cluster_tables(const float* t, const float* m, const float* M,
 // rows of `n_inst` instances (tables at ws, rows at `rows`), levels n - pmax + 1 .. n, then the trace
 // one instantiation of the level kernel per set size
 using ClLevelLaunch = hipError_t (*)(dim3, dim3, uint32_t, hipStream_t, const ClusterLayout&, const unsigned char*,
-                                     uint16_t*, int, int);
+                                     uint16_t*, int);
 template <int C, int MODE>
 static hipError_t cluster_launch_mode(dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, const ClusterLayout& y,
-                                      const unsigned char* ws, uint16_t* rows, int pmax, int exact) {
+                                      const unsigned char* ws, uint16_t* rows, int pmax) {
     static std::atomic<uint64_t> lds_allowed{0};
     const hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&cluster_level_kernel<C, MODE>), lds_allowed);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((cluster_level_kernel<C, MODE>), grid, block, lds_bytes, stream, y, ws, rows, pmax, exact);
+    hipLaunchKernelGGL((cluster_level_kernel<C, MODE>), grid, block, lds_bytes, stream, y, ws, rows, pmax);
     return hipGetLastError();
 }
 template <int C>
 static hipError_t cluster_launch_level(dim3 grid, dim3 block, uint32_t lds_bytes, hipStream_t stream, const ClusterLayout& y,
-                                       const unsigned char* ws, uint16_t* rows, int pmax, int exact) {
+                                       const unsigned char* ws, uint16_t* rows, int pmax) {
     const int mode = cluster_mode(y.L);
-    return mode == kClTwoSets ? cluster_launch_mode<C, kClTwoSets>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact)
-           : mode == kClOneSet ? cluster_launch_mode<C, kClOneSet>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact)
-                               : cluster_launch_mode<C, kClWide>(grid, block, lds_bytes, stream, y, ws, rows, pmax, exact);
+    return mode == kClTwoSets ? cluster_launch_mode<C, kClTwoSets>(grid, block, lds_bytes, stream, y, ws, rows, pmax)
+           : mode == kClOneSet ? cluster_launch_mode<C, kClOneSet>(grid, block, lds_bytes, stream, y, ws, rows, pmax)
+                               : cluster_launch_mode<C, kClWide>(grid, block, lds_bytes, stream, y, ws, rows, pmax);
 }
 template <int... Cs>
 static constexpr std::array<ClLevelLaunch, sizeof...(Cs)> cluster_level_table(std::integer_sequence<int, Cs...>) {
@@ -872,10 +821,8 @@ static constexpr std::array<ClLevelLaunch, sizeof...(Cs)> cluster_level_table(st
 static const std::array<ClLevelLaunch, PPO_CLUSTER_MAX_N> kClLevelLaunch =
     cluster_level_table(std::make_integer_sequence<int, PPO_CLUSTER_MAX_N>{});
 
-// exact: every node has to be used (pmax = n); key_out (may be null): bits of beta and rank of the permutation
-hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, bool exact, const void* ws, void* rows,
-                                uint64_t* key_out, float* beta_out, int32_t* segs_out, int32_t* cuts_out,
-                                int32_t* order_out, hipStream_t stream) {
+hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, const void* ws, void* rows, float* beta_out,
+                                int32_t* segs_out, int32_t* cuts_out, int32_t* order_out, hipStream_t stream) {
     const ClusterLayout y = ClusterLayout::make(L, n);
     const unsigned char* w = static_cast<const unsigned char*>(ws);
     uint16_t* r = static_cast<uint16_t*>(rows);
@@ -888,25 +835,12 @@ hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, bool exact, 
         uint32_t blocks = (kClBinomialsHost.c[n][level - 1] + sets_each - 1u) / sets_each;
         const uint32_t cap = (resident + (uint32_t)n_inst - 1u) / (uint32_t)n_inst;
         if (blocks > cap) blocks = cap;
-        e = kClLevelLaunch[level - 1](dim3(blocks, n_inst), dim3(lds.waves * 64), lds.total, stream, y, w, r, pmax,
-                                      exact ? 1 : 0);
+        e = kClLevelLaunch[level - 1](dim3(blocks, n_inst), dim3(lds.waves * 64), lds.total, stream, y, w, r, pmax);
         if (e != hipSuccess) return e;
     }
     const int trace_waves = n < kClTraceWaves ? n : kClTraceWaves;   // one wave per candidate node
     hipLaunchKernelGGL(cluster_trace_kernel, dim3(n_inst), dim3(trace_waves * 64), 0, stream, y, w, r, pmax,
-                       exact ? 1 : 0, reinterpret_cast<unsigned long long*>(key_out), beta_out, segs_out, cuts_out,
-                       order_out);
-    return hipGetLastError();
-}
-
-hipError_t launch_cluster_tables_from_prepared(const Layout& f, const void* fixed_ws, int n_inst, void* ws,
-                                               hipStream_t stream) {
-    const ClusterLayout y = ClusterLayout::make(f.L, f.k);
-    hipLaunchKernelGGL(cluster_tables_from_prepared_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, f,
-                       static_cast<const unsigned char*>(fixed_ws), y, static_cast<unsigned char*>(ws));
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cluster_image_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, y, static_cast<unsigned char*>(ws));
+                       beta_out, segs_out, cuts_out, order_out);
     return hipGetLastError();
 }
 

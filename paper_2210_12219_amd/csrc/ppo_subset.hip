@@ -25,12 +25,18 @@
 // does everything for an instance in one workgroup (no tables in HBM, no launch gaps); the answer is walked by one wave,
 // because run by all of them (redundantly, with barriers) it issued more instructions than the rows did (50 layers on 6
 // nodes: 65 us for 1024 instances, 43 with one wave).
+// Many instances of long chains on six to eight nodes go by the ranges of cuts that a set can meet (ppo_bands.hip).
 // Measured on one MI355X, per call with scratch and outputs kept (in brackets with the call's own scratch; the enumeration
-// before): 256 x (L 12, k 4) 18 us (21; 58), 1024 x (50, 6) 44 us (43; 163), 4096 x (96, 8) 0.61 ms (0.62; 23.1 ms),
-// 37 x (127, 9) 87 us (91; 97 ms), 1 x (64, 11) 76 us (92; 3.2 ms).
+// before): 256 x (L 12, k 4) 18 us (21; 58), 1024 x (50, 6) 44 us (43; 163), 37 x (127, 9) 87 us (91; 97 ms), 1 x (64, 11) 76 us
+// (92; 3.2 ms).
 #include "ppo_sets.h"
 
 namespace ppo {
+
+// ppo_bands.hip
+bool bands_apply(int L, int k, int n_inst, size_t slot, size_t slot_count);
+hipError_t launch_bands_solve(const float*, const float*, const float*, const float*, int, int, int, float*, int32_t*, int32_t*, void*,
+                              size_t, size_t, hipStream_t);
 
 namespace {
 
@@ -671,6 +677,8 @@ hipError_t launch_subset_solve(const float* t, const float* m, const float* M, c
                                hipStream_t stream) {
     const int G = subset_sets_per_wave(L);
     const size_t slot = subset_slot_bytes(L, k);
+    if (bands_apply(L, k, n_inst, slot, slot_count))
+        return launch_bands_solve(t, m, M, B, L, k, n_inst, beta_out, cuts_out, order_out, slots, slot, slot_count, stream);
     if (slot != 0 && slot_count > (size_t)n_inst) slot_count = (size_t)n_inst;
     auto launch = [&](auto kernel, std::atomic<uint64_t>& lds_allowed, int first, int cnt, uint32_t grid, int part = kWhole) -> hipError_t {
         const int waves = k > kSmallK ? kSubsetMaxWaves : subset_waves(L, k);

@@ -102,4 +102,17 @@ __device__ __forceinline__ ClusterLayout cluster_layout(const ClusterLayout& who
 hipError_t launch_cluster_reduce(const float* t, const float* m, const float* M, const float* B, const ClusterLayout& y, int n_inst,
                                  unsigned char* ws, hipStream_t stream);
 
+// The same for the search for few segments: two bounds, then whether the search is confined, and to which nodes and cuts.
+struct FewConfined {
+    union {
+        uint32_t bounds[2];
+        unsigned long long nodes;
+    };
+    unsigned long long cuts[2];
+    uint32_t in, bound;   // no value above the bound matters (+inf: none is known)
+};
+// `out`: of the first instance, `stride` bytes to that of the next
+hipError_t launch_few_confine(const float* t, const float* m, const float* M, const float* B, int L, int n, int pmax, int n_inst,
+                              FewConfined* out, size_t stride, hipStream_t stream);
+
 }  // namespace ppo

@@ -14,6 +14,9 @@
 // 100 layers become 9 to 16 nodes and 10 to 18 layers, 10.5 million rows of 100 entries 2 to 520 thousand of 10 to 18.  An
 // instance without a placement on the nine nodes, or with more than 62 cuts left, is searched whole.
 //
+// The search for few segments (ppo_cluster_few.hip) goes the same way, with up to 64 nodes, segments counted, and the bound
+// itself handed on.
+//
 // What bounds these two: the one workgroup's instruction issue in the levels of the first (2304 rows, 22 of its 30 us) and
 // chains of LDS reads and barriers in the second (24 to 28 us).  One cluster of 20 nodes and 100 layers: 2040 us a call without
 // them, 135 with them; 32 of 15 devices and 50 layers: 827 and 501 (no node and two thirds of the layers left out).
@@ -47,8 +50,9 @@ static_assert(bound_level_rows(5) == kBoundOddRows && bound_level_rows(3) <= kBo
 
 struct BoundShared {
     double P[PPO_MAX_L + 64 + 1];                  // written 64 at a time
-    float t[PPO_MAX_L], m[PPO_MAX_L], M[PPO_CLUSTER_MAX_N], B[PPO_CLUSTER_MAX_N * PPO_CLUSTER_MAX_N];
+    float t[PPO_MAX_L], m[PPO_MAX_L], M[PPO_CLUSTER_FEW_MAX_N], B[PPO_CLUSTER_FEW_MAX_N * PPO_CLUSTER_FEW_MAX_N];
     unsigned long long cuts[2];                    // bit e: the cut e is one of the 31
+    uint32_t best;
     int level[kBoundNodes + 2];
     unsigned char node[16], pos[kBoundEntries];    // cluster nodes and cuts of the small search; pos[0] = 0
     uint16_t order[1 << kBoundNodes], place[1 << kBoundNodes];
@@ -153,10 +157,11 @@ static __constant__ SetValues kSetValues = SetValues();
 
 __global__ __launch_bounds__(kBoundThreads) void cluster_bound_kernel(const float* __restrict__ t, const float* __restrict__ m,
                                                                      const float* __restrict__ M, const float* __restrict__ B,
-                                                                     ClusterLayout y, unsigned char* __restrict__ ws) {
+                                                                     int L, int n, int pmax, unsigned char* __restrict__ out,
+                                                                     size_t stride) {
     extern __shared__ __align__(16) unsigned char bound_sm[];
     BoundShared& s = *reinterpret_cast<BoundShared*>(bound_sm);
-    const int L = y.L, n = y.n, inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < L) {
         const float x = t[(size_t)inst * L + tid];
@@ -164,6 +169,7 @@ __global__ __launch_bounds__(kBoundThreads) void cluster_bound_kernel(const floa
         s.m[tid] = m[(size_t)inst * L + tid];
     }
     if (tid < n) s.M[tid] = M[(size_t)inst * n + tid];
+    if (tid == 0) s.best = kBoundInf;
     for (int i = tid; i < n * n; i += kBoundThreads) {
         const int a = i / n, b = i - a * n;   // the element with the smaller row index is the one read
         s.B[i] = B[(size_t)inst * n * n + (a < b ? i : b * n + a)];
@@ -250,39 +256,45 @@ __global__ __launch_bounds__(kBoundThreads) void cluster_bound_kernel(const floa
         s.q[a][b][e] = (uint16_t)c;
     }
     __syncthreads();
-    bound_level<1>(s, lane, wave);
-    bound_level<2>(s, lane, wave);
-    bound_level<3>(s, lane, wave);
-    bound_level<4>(s, lane, wave);
-    bound_level<5>(s, lane, wave);
-    bound_level<6>(s, lane, wave);
-    bound_level<7>(s, lane, wave);
-    bound_level<8>(s, lane, wave);
-    if (tid == 0) {
-        uint32_t best = kBoundInf;
-        for (int j = 0; j < kBoundNodes; ++j) {
-            const uint32_t x = s.rows[j * kBoundRow] & 0xFFFFu;   // nine nodes: rows of an odd size
-            best = x < best ? x : best;
-        }
-        *reinterpret_cast<uint32_t*>(ws + (size_t)inst * y.stride + y.img_off + 4 * blockIdx.x) = best << 16;
+    const int most = pmax < kBoundNodes ? pmax : kBoundNodes;   // sets of as many nodes stand for all smaller ones
+    if (most > 1) bound_level<1>(s, lane, wave);
+    if (most > 2) bound_level<2>(s, lane, wave);
+    if (most > 3) bound_level<3>(s, lane, wave);
+    if (most > 4) bound_level<4>(s, lane, wave);
+    if (most > 5) bound_level<5>(s, lane, wave);
+    if (most > 6) bound_level<6>(s, lane, wave);
+    if (most > 7) bound_level<7>(s, lane, wave);
+    if (most > 8) bound_level<8>(s, lane, wave);
+    const uint32_t* rows = s.rows + (most & 1 ? 0 : kBoundOddRows * kBoundRow);
+    const int count_rows = (s.level[most + 1] - s.level[most]) * most;
+    uint32_t best = kBoundInf;
+    for (int i = tid; i < count_rows; i += kBoundThreads) {
+        const uint32_t x = rows[i * kBoundRow] & 0xFFFFu;
+        best = x < best ? x : best;
     }
+    if (best < kBoundInf) atomicMin(&s.best, best);
+    __syncthreads();
+    if (tid == 0) reinterpret_cast<uint32_t*>(out + (size_t)inst * stride)[blockIdx.x] = s.best << 16;
 }
 
 // ---------------------------------------------------------------------------------------------
 // Tables of one instance, as cluster_tables_kernel makes them, of the nodes and cuts that can matter; one workgroup.
 // ---------------------------------------------------------------------------------------------
 namespace {
-struct ReduceShared {
+template <int MAXN>
+struct ConfineShared {
     double P[PPO_MAX_L + 64 + 1];
-    float t[PPO_MAX_L], m[PPO_MAX_L], M[PPO_CLUSTER_MAX_N], B[PPO_CLUSTER_MAX_N * PPO_CLUSTER_MAX_N];
-    unsigned char hi[PPO_CLUSTER_MAX_N][PPO_MAX_L + 4];
-    unsigned long long cuts[2];                                     // bit e: the cut e
-    unsigned long long link[PPO_CLUSTER_MAX_N][PPO_CLUSTER_MAX_N];  // by positions, as the following
-    unsigned long long ends[PPO_CLUSTER_MAX_N], back[2][PPO_CLUSTER_MAX_N], fore[2][PPO_CLUSTER_MAX_N], reach[PPO_CLUSTER_MAX_N];
-    unsigned char top[PPO_CLUSTER_MAX_N][64];                       // last position inside the window
-    unsigned char pos[PPO_MAX_L + 1], node[PPO_CLUSTER_MAX_N], ord[PPO_MAX_L];
-    int changed[2][PPO_CLUSTER_MAX_N];
+    float t[PPO_MAX_L], m[PPO_MAX_L], M[MAXN], B[MAXN * MAXN];
+    unsigned char hi[MAXN][PPO_MAX_L + 4];
+    unsigned long long cuts[2];                                    // bit e: the cut e
+    unsigned long long link[MAXN][MAXN];                           // by positions, as the following
+    unsigned long long ends[MAXN], back[2][MAXN], fore[2][MAXN], reach[MAXN];
+    unsigned char top[MAXN][64];                                   // last position inside the window
+    unsigned char pos[PPO_MAX_L + 1], node[MAXN], ord[PPO_MAX_L];
+    int changed[2][MAXN];
 };
+// t / B <= bound, and a little more: no quotient at most `bound` is missed, and no division is needed
+__device__ __forceinline__ float link_limit(uint32_t bound, float bandwidth) { return __uint_as_float(bound) * bandwidth * 1.000001f + 1.2e-38f; }
 // all lanes' bits, in all lanes: shifts within rows of 16, then the last lane of a row to the next row, of two rows to the
 // next two
 __device__ __forceinline__ uint32_t or_lanes(uint32_t v) {
@@ -297,17 +309,14 @@ __device__ __forceinline__ uint32_t or_lanes(uint32_t v) {
 __device__ __forceinline__ unsigned long long or_lanes(unsigned long long v) {
     return (unsigned long long)or_lanes((uint32_t)v) | (unsigned long long)or_lanes((uint32_t)(v >> 32)) << 32;
 }
-}  // namespace
-
-__global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const float* __restrict__ t, const float* __restrict__ m,
-                                                                      const float* __restrict__ M, const float* __restrict__ B,
-                                                                      ClusterLayout whole, unsigned char* __restrict__ ws) {
-    __shared__ ReduceShared s;
-    const int L = whole.L, n = whole.n, inst = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+// Inputs, prefix sums and windows (hi) of an instance; then, if there is a bound and few enough cuts are within it, the nodes
+// and cuts that lie on a walk of up to `rounds` segments: true.  All threads of the workgroup, in step.
+template <int MAXN>
+__device__ __forceinline__ bool confine(ConfineShared<MAXN>& s, const float* __restrict__ t, const float* __restrict__ m,
+                                        const float* __restrict__ M, const float* __restrict__ B, int L, int n, int rounds, int inst,
+                                        uint32_t bound, unsigned long long& cuts0, unsigned long long& cuts1, unsigned long long& nodes) {
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = kClPreThreads / 64;
-    unsigned char* base = ws + (size_t)inst * whole.stride;
-    const uint32_t* bounds = reinterpret_cast<const uint32_t*>(base + whole.img_off);
-    const uint32_t u0 = bounds[0], u1 = bounds[1], bound = u0 < u1 ? u0 : u1;
     if (tid < L) {
         const float x = t[(size_t)inst * L + tid];
         s.t[tid] = x == 0.0f ? 0.0f : x;   // -0 is a size of zero: +0
@@ -328,9 +337,10 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
             const float o = __shfl_xor(most, off, 64);
             most = o > most ? o : most;
         }
+        const float limit = link_limit(bound, most);
         for (int h = 0; h < 2; ++h) {
             const int e = lane + 64 * h;
-            const bool in = e >= 1 && e < L && __float_as_uint(__fdiv_rn(s.t[e >= 1 && e < L ? e - 1 : 0], most)) <= bound;
+            const bool in = e >= 1 && e < L && s.t[e >= 1 && e < L ? e - 1 : 0] <= limit;
             const unsigned long long some = __ballot(in);
             if (lane == 0) s.cuts[h] = some;
         }
@@ -340,23 +350,22 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
         const int j = i / (L + 1), e = i - j * (L + 1);
         s.hi[j][e] = (unsigned char)window_end(s.P, L, (double)s.M[j], e);
     }
-    unsigned long long c0 = s.cuts[0], c1 = s.cuts[1];
+    const unsigned long long c0 = s.cuts[0], c1 = s.cuts[1];
     const int count = __popcll(c0) + __popcll(c1);
-    uint32_t nodes = (1u << n) - 1u;
-    bool reduced = bound < kInfBits && count <= 62;
-    if (reduced) {
+    if (bound >= kInfBits || count > 62) return false;
+    {
         // positions: 0 the start of the chain, then the cuts
         if (tid >= 1 && tid < L && ((tid < 64 ? c0 >> tid : c1 >> (tid - 64)) & 1ull)) s.pos[cuts_upto(c0, c1, tid)] = (unsigned char)tid;
         if (tid == 0) s.pos[0] = 0;
-        if (tid < 2 * PPO_CLUSTER_MAX_N) s.changed[tid / PPO_CLUSTER_MAX_N][tid % PPO_CLUSTER_MAX_N] = 0;   // one for every round
+        if (tid < 2 * MAXN) s.changed[tid / MAXN][tid % MAXN] = 0;   // one for every round
         __syncthreads();
-        for (int p = wave; p < n * n; p += waves) {
-            const int a = p / n, b = p - a * n;
-            const bool in = a != b && lane >= 1 && lane <= count &&
-                            __float_as_uint(__fdiv_rn(s.t[lane >= 1 && lane <= count ? s.pos[lane] - 1 : 0], s.B[p])) <= bound;
-            const unsigned long long some = __ballot(in);
-            if (lane == 0) s.link[a][b] = some;
-        }
+        const bool is_cut = lane >= 1 && lane <= count;
+        const float size = s.t[is_cut ? s.pos[lane] - 1 : 0];
+        for (int a = wave; a < n; a += waves)
+            for (int b = a; b < n; ++b) {
+                const unsigned long long some = a < b ? __ballot(is_cut && size <= link_limit(bound, s.B[a * n + b])) : 0ull;
+                if (lane == 0) s.link[a][b] = s.link[b][a] = some;
+            }
         for (int j = wave; j < n; j += waves) {
             const int end = lane <= count ? (int)s.hi[j][s.pos[lane <= count ? lane : 0]] : 0;
             const unsigned long long ends = __ballot(lane <= count && end == L);
@@ -367,9 +376,9 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
             }
         }
         __syncthreads();
-        // a placement has at most n segments: n rounds find every cut that matters
+        // a placement has at most that many segments: as many rounds find every cut that matters
         int now = 0;
-        for (int round = 0; round < n; ++round) {
+        for (int round = 0; round < rounds; ++round) {
             for (int j = wave; j < n; j += waves) {
                 const unsigned long long rest = or_lanes(lane < n ? s.link[j][lane < n ? lane : 0] & s.back[now][lane < n ? lane : 0] : 0ull);
                 // a start whose window holds a cut from which it goes on
@@ -387,7 +396,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
         }
         const int done = now;
         now = 0;
-        for (int round = 0; round < n; ++round) {
+        for (int round = 0; round < rounds; ++round) {
             for (int j = wave; j < n; j += waves) {
                 // cuts that a window starting in fore & back covers: the latest start before a cut decides
                 const unsigned long long start = s.fore[now][j] & s.back[done][j], before = start & ((1ull << lane) - 1ull);
@@ -409,24 +418,40 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
             if (!s.changed[1][round]) break;
         }
         const unsigned long long mine = lane < n ? s.fore[now][lane < n ? lane : 0] & s.back[done][lane < n ? lane : 0] : 0ull;
-        const uint32_t left = (uint32_t)__ballot(mine != 0ull);
+        const unsigned long long left = __ballot(mine != 0ull);
         const unsigned long long at = or_lanes(mine);
         // back to cuts: position i is the i-th one
         const int e0 = lane, e1 = lane + 64;
         const bool k0 = ((c0 >> lane) & 1ull) && ((at >> cuts_upto(c0, c1, e0)) & 1ull);
         const bool k1 = ((c1 >> lane) & 1ull) && ((at >> cuts_upto(c0, c1, e1)) & 1ull);
         const unsigned long long n0 = __ballot(k0), n1 = __ballot(k1);
-        const ClusterLayout y2 = ClusterLayout::make(__popcll(n0) + __popcll(n1) + 1, __popc(left));
-        // the smaller tables leave room for the record, and with the binomial coefficients take no more LDS than the levels are given
-        reduced = left != 0u && y2.stride <= whole.record_off() &&
-                  y2.q_image_bytes() + y2.query_bytes() + kClBinomialBytes <= whole.q_image_bytes() + whole.query_bytes();
-        if (reduced) {
-            c0 = n0;
-            c1 = n1;
-            nodes = left;
-        }
         __syncthreads();
+        cuts0 = n0;
+        cuts1 = n1;
+        nodes = left;
+        return left != 0ull;
     }
+}
+}  // namespace
+
+__global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const float* __restrict__ t, const float* __restrict__ m,
+                                                                      const float* __restrict__ M, const float* __restrict__ B,
+                                                                      ClusterLayout whole, unsigned char* __restrict__ ws) {
+    __shared__ ConfineShared<PPO_CLUSTER_MAX_N> s;
+    const int L = whole.L, n = whole.n, inst = blockIdx.x, tid = threadIdx.x;
+    unsigned char* base = ws + (size_t)inst * whole.stride;
+    const uint32_t* bounds = reinterpret_cast<const uint32_t*>(base + whole.img_off);
+    const uint32_t u0 = bounds[0], u1 = bounds[1];
+    unsigned long long c0 = 0ull, c1 = 0ull, left = 0ull;
+    bool reduced = confine(s, t, m, M, B, L, n, n, inst, u0 < u1 ? u0 : u1, c0, c1, left);
+    __syncthreads();
+    if (reduced) {
+        // the smaller tables leave room for the record, and with the binomial coefficients take no more LDS than the levels are given
+        const ClusterLayout y2 = ClusterLayout::make(__popcll(c0) + __popcll(c1) + 1, __popcll(left));
+        reduced = y2.stride <= whole.record_off() &&
+                  y2.q_image_bytes() + y2.query_bytes() + kClBinomialBytes <= whole.q_image_bytes() + whole.query_bytes();
+    }
+    const uint32_t nodes = reduced ? (uint32_t)left : (1u << n) - 1u;
     if (!reduced) {   // every cut
         c0 = (L >= 64 ? ~0ull : (1ull << L) - 1ull) & ~1ull;
         c1 = L <= 64 ? 0ull : L >= 128 ? ~0ull : (1ull << (L - 64)) - 1ull;
@@ -475,15 +500,52 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_reduce_kernel(const flo
     }
 }
 
+// Nodes and cuts of an instance of the search for few segments (ppo_cluster_few.hip), which makes its tables of them.
+__global__ __launch_bounds__(kClPreThreads) void few_confine_kernel(const float* __restrict__ t, const float* __restrict__ m,
+                                                                   const float* __restrict__ M, const float* __restrict__ B, int L,
+                                                                   int n, int pmax, FewConfined* __restrict__ out, size_t stride) {
+    extern __shared__ __align__(16) unsigned char bound_sm[];
+    ConfineShared<PPO_CLUSTER_FEW_MAX_N>& s = *reinterpret_cast<ConfineShared<PPO_CLUSTER_FEW_MAX_N>*>(bound_sm);
+    FewConfined* mine = reinterpret_cast<FewConfined*>(reinterpret_cast<unsigned char*>(out) + (size_t)blockIdx.x * stride);
+    const uint32_t u0 = mine->bounds[0], u1 = mine->bounds[1];
+    unsigned long long c0 = 0ull, c1 = 0ull, left = 0ull;
+    const bool in = confine(s, t, m, M, B, L, n, pmax, (int)blockIdx.x, u0 < u1 ? u0 : u1, c0, c1, left);
+    if (threadIdx.x == 0) {
+        mine->in = in ? 1u : 0u;
+        mine->bound = u0 < u1 ? u0 : u1;
+        mine->nodes = left;
+        mine->cuts[0] = c0;
+        mine->cuts[1] = c1;
+    }
+}
+
+static hipError_t launch_bound(const float* t, const float* m, const float* M, const float* B, int L, int n, int pmax, int n_inst,
+                               unsigned char* out, size_t stride, hipStream_t stream) {
+    static std::atomic<uint64_t> lds_allowed{0};
+    const hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&cluster_bound_kernel), lds_allowed);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(cluster_bound_kernel, dim3(2, n_inst), dim3(kBoundThreads), sizeof(BoundShared), stream, t, m, M, B, L, n, pmax,
+                       out, stride);
+    return hipGetLastError();
+}
+
 hipError_t launch_cluster_reduce(const float* t, const float* m, const float* M, const float* B, const ClusterLayout& y, int n_inst,
                                  unsigned char* ws, hipStream_t stream) {
-    static std::atomic<uint64_t> lds_allowed{0};
-    hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&cluster_bound_kernel), lds_allowed);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cluster_bound_kernel, dim3(2, n_inst), dim3(kBoundThreads), sizeof(BoundShared), stream, t, m, M, B, y, ws);
-    e = hipGetLastError();
+    const hipError_t e = launch_bound(t, m, M, B, y.L, y.n, y.n, n_inst, ws + y.img_off, y.stride, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cluster_reduce_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, t, m, M, B, y, ws);
+    return hipGetLastError();
+}
+
+hipError_t launch_few_confine(const float* t, const float* m, const float* M, const float* B, int L, int n, int pmax, int n_inst,
+                              FewConfined* out, size_t stride, hipStream_t stream) {
+    hipError_t e = launch_bound(t, m, M, B, L, n, pmax, n_inst, reinterpret_cast<unsigned char*>(out), stride, stream);
+    if (e != hipSuccess) return e;
+    static std::atomic<uint64_t> lds_allowed{0};
+    e = allow_full_lds(reinterpret_cast<const void*>(&few_confine_kernel), lds_allowed);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(few_confine_kernel, dim3(n_inst), dim3(kClPreThreads), sizeof(ConfineShared<PPO_CLUSTER_FEW_MAX_N>), stream, t, m,
+                       M, B, L, n, pmax, out, stride);
     return hipGetLastError();
 }
 

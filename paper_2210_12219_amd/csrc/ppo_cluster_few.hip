@@ -17,7 +17,7 @@
 // position as in ppo_cluster.hip: F = cuts the prefix reaches within beta*, G_j = those whose link into
 // candidate j is within beta*; j qualifies iff some row G[S][j], S disjoint from the prefix and small enough,
 // is within beta* at a cut of G_j (one pass over the rows per position); cuts by the fixed-k cut rule.
-#include "ppo_common.h"
+#include "ppo_cluster.h"
 
 namespace ppo {
 
@@ -39,8 +39,9 @@ __constant__ FewBinomials kFewBinomials = FewBinomials();
 
 struct FewState {
     // (the gaps: with the least values 32 bytes earlier 4 x (128 layers, 64 nodes, 3 segments) took 120 us in place of 118)
-    uint32_t best, chosen, done, gap0[5];
-    unsigned long long used, gap1[2];
+    uint32_t best, chosen, done, gap;
+    FewConfined confined;
+    unsigned long long used;
     union {
         uint32_t first_best[kFewMaxN];           // per node j, until position 0 is settled: the least G[S][j][0] of all sets so far
         unsigned long long cand[kFewMaxN][2];    // then G_j of every candidate of the current position
@@ -52,13 +53,14 @@ struct FewState {
 struct FewLayout {
     int L, n, pmax, rs;                    // rs: entries per row (0 .. L-1), rounded up to even
     uint32_t hi_off, qs_off, state_off, stride;   // bytes within one instance's tables
-    unsigned long long level_off[kFewMaxP + 1];   // first full row of level c (1 <= c <= full levels)
-    unsigned long long full_rows, top_rows;       // rows kept whole; entries of the last level (0 if pmax = 1)
+    unsigned long long level_off[kFewMaxP + 1];   // first full row of level c (1 <= c <= full levels + 1: of the words after all rows)
     size_t rows_bytes;                            // of one instance
+    bool confined;                                // instances may be confined to some nodes and cuts: see FewDims
 
     __host__ __device__ int full_levels() const { return pmax > 1 ? pmax - 1 : 1; }
-    __host__ static FewLayout make(int L, int n, int pmax) {
+    __host__ static FewLayout make(int L, int n, int pmax, bool confined = false) {
         FewLayout y{};
+        y.confined = confined;
         y.L = L;
         y.n = n;
         y.pmax = pmax;
@@ -71,17 +73,57 @@ struct FewLayout {
         y.state_off = (uint32_t)off;
         off = align_up(off + sizeof(FewState), 256);
         y.stride = (uint32_t)off;
+        // rows of the levels that are kept whole (1 <= c <= full levels), then entries of the last level (none if pmax = 1)
         unsigned long long rows = 0;
         for (int c = 1; c <= y.full_levels(); ++c) {
             y.level_off[c] = rows;
             rows += kFewBinomialsHost.c[n][c] * (unsigned long long)c;
         }
-        y.full_rows = rows;
-        y.top_rows = pmax > 1 ? kFewBinomialsHost.c[n][pmax] * (unsigned long long)pmax : 0ull;
-        y.rows_bytes = align_up((size_t)(y.full_rows * (unsigned long long)y.rs + y.top_rows) * 4, 256);
+        if (pmax > 1) y.level_off[pmax] = rows;
+        const unsigned long long top = pmax > 1 ? kFewBinomialsHost.c[n][pmax] * (unsigned long long)pmax : 0ull;
+        y.rows_bytes = align_up((size_t)(rows * (unsigned long long)y.rs + top) * 4, 256);
         return y;
     }
 };
+
+// What the tables of an instance are made of: everything, or the nodes and cuts that can matter (the parts of its slices lie
+// where they always do).
+struct FewDims {
+    int L, n, rs;
+    __device__ __forceinline__ FewDims(const FewLayout& y, const unsigned char* base) : L(y.L), n(y.n), rs(y.rs) {
+        if (!y.confined) return;
+        const FewConfined& c = reinterpret_cast<const FewState*>(base + y.state_off)->confined;
+        if (__builtin_amdgcn_readfirstlane((int)c.in) == 0) return;
+        L = __builtin_amdgcn_readfirstlane(__popcll(c.cuts[0]) + __popcll(c.cuts[1]) + 1);
+        n = __builtin_amdgcn_readfirstlane(__popcll(c.nodes));
+        rs = (L + 1) & ~1;
+    }
+    // first row of level c
+    __device__ __forceinline__ unsigned long long first_row(const FewLayout& y, int c) const {
+        if (!y.confined) return y.level_off[c];
+        unsigned long long rows = 0;
+        for (int k = 1; k < c; ++k) rows += kFewBinomials.c[n][k] * (unsigned long long)k;
+        return rows;
+    }
+};
+// no value above this one matters
+__device__ __forceinline__ uint32_t few_bound(const FewLayout& y, const FewState* st) {
+    return y.confined ? (uint32_t)__builtin_amdgcn_readfirstlane((int)st->confined.bound) : kInfBits;
+}
+// the node and the cut of the instance that place i among those left stands for (cut 0 is the start of the chain)
+__device__ inline int few_node(const FewLayout& y, const FewConfined& c, int i) {
+    if (!y.confined || !c.in) return i;
+    unsigned long long bits = c.nodes;
+    for (; i > 0; --i) bits &= bits - 1ull;
+    return __ffsll((long long)bits) - 1;
+}
+__device__ inline int few_cut(const FewLayout& y, const FewConfined& c, int i) {
+    if (!y.confined || !c.in || i == 0) return i;
+    const int low = __popcll(c.cuts[0]);
+    unsigned long long bits = i <= low ? c.cuts[0] : c.cuts[1];
+    for (int left = i <= low ? i : i - low; left > 1; --left) bits &= bits - 1ull;
+    return (i <= low ? 0 : 64) + __ffsll((long long)bits) - 1;
+}
 
 // Shapes this formulation takes: the rows of one instance are counted in 31 bits.
 bool cluster_few_supported(int L, int n, int pmax) {
@@ -142,15 +184,23 @@ __global__ __launch_bounds__(kFewTableThreads) void few_tables_kernel(const floa
     __shared__ double P[PPO_MAX_L + 1];
     __shared__ float t_s[PPO_MAX_L], m_s[PPO_MAX_L];
     __shared__ unsigned char hi_s[PPO_MAX_L + 1];
-    const int L = y.L, n = y.n, rs = y.rs, j = blockIdx.x, inst = blockIdx.y, tid = threadIdx.x;
-    const float* ti = t + (size_t)inst * L;
-    const float* mi = m + (size_t)inst * L;
-    const float* Bi = B + ((size_t)inst * n + j) * n;
+    __shared__ unsigned char pos_s[PPO_MAX_L + 1], node_s[kFewMaxN];
+    const int j = blockIdx.x, inst = blockIdx.y, tid = threadIdx.x;
     unsigned char* base = ws + (size_t)inst * y.stride;
+    const FewDims d(y, base);
+    const int L = d.L, n = d.n, rs = d.rs;
+    if (j >= n) return;
+    if (y.confined) {
+        const FewConfined& in = reinterpret_cast<const FewState*>(base + y.state_off)->confined;
+        if (tid < n) node_s[tid] = (unsigned char)few_node(y, in, tid);
+        for (int e = tid; e <= L; e += kFewTableThreads) pos_s[e] = (unsigned char)(e == L ? y.L : few_cut(y, in, e));
+    }
+    const float* ti = t + (size_t)inst * y.L;
+    const float* mi = m + (size_t)inst * y.L;
     uint32_t* qs = reinterpret_cast<uint32_t*>(base + y.qs_off) + (size_t)j * n * rs;
     FewState* st = reinterpret_cast<FewState*>(base + y.state_off);
     uint32_t* R = rows + (size_t)inst * (y.rows_bytes / 4);
-    for (int i = tid; i < L; i += kFewTableThreads) {
+    for (int i = tid; i < y.L; i += kFewTableThreads) {
         t_s[i] = ti[i] == 0.0f ? 0.0f : ti[i];   // -0 is a size of zero: +0
         m_s[i] = mi[i];
     }
@@ -158,7 +208,7 @@ __global__ __launch_bounds__(kFewTableThreads) void few_tables_kernel(const floa
     if (tid == 0) {
         double acc = 0.0;
         P[0] = 0.0;
-        for (int i = 0; i < L; ++i) {
+        for (int i = 0; i < y.L; ++i) {
             acc = acc + (double)m_s[i];
             P[i + 1] = acc;
         }
@@ -169,21 +219,24 @@ __global__ __launch_bounds__(kFewTableThreads) void few_tables_kernel(const floa
             st->used = 0ull;
         }
     }
+    const int node = y.confined ? node_s[j] : j;
+    const float* Bi = B + ((size_t)inst * y.n + node) * y.n;
     for (int b = tid >> 5; b < n; b += kFewTableThreads >> 5) {
-        const float bw = b != j ? Bi[b] : 1.0f;
+        const float bw = b != j ? Bi[y.confined ? node_s[b] : b] : 1.0f;
         for (int e = tid & 31; e < rs; e += 32) {
             uint32_t v = kInfBits;
-            if (b != j && e >= 1 && e < L) v = __float_as_uint(__fdiv_rn(t_s[e - 1], bw));
+            if (b != j && e >= 1 && e < L) v = __float_as_uint(__fdiv_rn(t_s[y.confined ? pos_s[e] - 1 : e - 1], bw));
             qs[b * rs + e] = v;
         }
     }
     __syncthreads();
-    const double cap = (double)M[(size_t)inst * n + j];
+    const double cap = (double)M[(size_t)inst * y.n + node];
     for (int e = tid; e <= L; e += kFewTableThreads) {
         int lo = e, hi = L;   // the last end that fits; P does not decrease
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if ((P[mid] - P[e]) <= cap) lo = mid; else hi = mid - 1;
+            const double part = y.confined ? P[pos_s[mid]] - P[pos_s[e]] : P[mid] - P[e];   // of the cuts left
+            if (part <= cap) lo = mid; else hi = mid - 1;
         }
         hi_s[e] = (unsigned char)lo;
         base[y.hi_off + j * (L + 1) + e] = (unsigned char)lo;
@@ -192,7 +245,7 @@ __global__ __launch_bounds__(kFewTableThreads) void few_tables_kernel(const floa
     // level 1: the rest of the chain on node j alone
     for (int e = tid; e < rs; e += kFewTableThreads) {
         const bool fits = e < L && hi_s[e] >= L;
-        R[(size_t)(y.level_off[1] + (unsigned long long)j) * rs + e] = fits ? 0u : kInfBits;
+        R[(size_t)j * rs + e] = fits ? 0u : kInfBits;
         if (e == 0) st->first_best[j] = fits ? 0u : kInfBits;
     }
 }
@@ -208,8 +261,10 @@ constexpr int kFewRunLevels = 7;     // runs of 2^0 .. 2^6 entries
 constexpr int kFewRunRow = 160;      // entries per run-minimum row: 128 computed per row, then +inf
 static_assert(kFewRunRow / 2 >= 64 + (1 << (kFewRunLevels - 3)), "the longest runs are built from pairs up to 2^(levels-3) beyond a lane's own");
 
+// of a wave that works several nodes at a time: the least values at the start of the chain, and the nodes outside the set
+constexpr int kFewPackDwords = kFewMaxN + kFewMaxN / 4;
 static size_t few_level_lds(const FewLayout& y) {
-    return ((size_t)y.n * y.rs + (size_t)kFewLevelWaves * kFewRunLevels * kFewRunRow + 1) * 4;
+    return ((size_t)y.n * y.rs + (size_t)kFewLevelWaves * (kFewRunLevels * kFewRunRow + kFewPackDwords) + 4) * 4;
 }
 
 // the value of the next lane; `last` in lane 63
@@ -224,16 +279,24 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
     // the LDS there is, which leaves no room for a static part)
     extern __shared__ __align__(16) uint32_t few_smem[];
     constexpr int c = C + 1;
-    const int L = y.L, n = y.n, rs = y.rs, rd = rs / 2;
     const int inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned char* base = ws + (size_t)inst * y.stride;
+    const FewDims dims(y, base);
+    const int L = dims.L, n = dims.n, rs = dims.rs, rd = rs / 2;
+    if ((unsigned long long)blockIdx.x * kFewLevelWaves >= kFewBinomials.c[n][C] * parts) return;
     const uint32_t* __restrict__ qs = reinterpret_cast<const uint32_t*>(base + y.qs_off);
     FewState* st = reinterpret_cast<FewState*>(base + y.state_off);
     uint32_t* R = rows + (size_t)inst * (y.rows_bytes / 4);
     uint32_t* query = few_smem;
     uint32_t* run = few_smem + (size_t)n * rs + wave * (kFewRunLevels * kFewRunRow);
     int& longest_s = reinterpret_cast<int*>(few_smem)[n * rs + kFewLevelWaves * kFewRunLevels * kFewRunRow];
+    uint32_t* least_s = few_smem + (size_t)n * rs + kFewLevelWaves * kFewRunLevels * kFewRunRow + 4 + wave * kFewPackDwords;
+    unsigned char* out_s = reinterpret_cast<unsigned char*>(least_s + kFewMaxN);
+    // short rows: as many nodes at a time as have room beside each other, 8, 16 or 32 lanes each (one cluster of 50 nodes and
+    // 5 segments, 12 to 17 of 100 layers left: the level of three nodes 120 us with a node at a time, 34 with four)
+    const int shift = rd <= 8 ? 3 : rd <= 16 ? 4 : rd <= 32 ? 5 : 6, lanes = 1 << shift, hl = lane & (lanes - 1);
+    least_s[lane] = kInfBits;
     if (tid == 0) longest_s = 1;
     __syncthreads();
     {
@@ -265,8 +328,9 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
     unsigned long long w = ((unsigned long long)blockIdx.x * kFewLevelWaves + (unsigned long long)wave) * per_wave;
     const unsigned long long w_end = w + per_wave < units ? w + per_wave : units;
     const unsigned long long all = n == 64 ? ~0ull : (1ull << n) - 1ull;
-    const unsigned long long in_off = y.level_off[C], out_off = y.level_off[c];
+    const unsigned long long in_off = dims.first_row(y, C), out_off = dims.first_row(y, c);
     uint32_t first_best = kInfBits;   // lane j: of the rows of node j at e = 0
+    const uint32_t bound = few_bound(y, st);
     unsigned long long set = 0, u = w / parts;
     uint32_t part = (uint32_t)(w - u * parts);
     if (w < w_end) set = few_set_at(u, C, n);
@@ -276,13 +340,13 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
         int b[C];
         {
             unsigned long long bits = set;
-            const uint32_t* arow = R + (size_t)(in_off + u * (unsigned long long)C) * rs + 2 * lane;
+            const uint32_t* arow = R + (size_t)(in_off + u * (unsigned long long)C) * rs + 2 * hl;
 #pragma unroll
             for (int mm = 0; mm < C; ++mm) {
                 b[mm] = __ffsll((long long)bits) - 1;
                 bits &= bits - 1ull;
                 uint2 v = make_uint2(kInfBits, kInfBits);
-                if (lane < rd) v = *reinterpret_cast<const uint2*>(arow + (size_t)mm * rs);
+                if (hl < rd) v = *reinterpret_cast<const uint2*>(arow + (size_t)mm * rs);
                 a[mm][0] = v.x;
                 a[mm][1] = v.y;
             }
@@ -303,7 +367,72 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
             my_row = rank * (unsigned long long)c + (unsigned long long)pos;
         }
         const unsigned long long mine = parts == 1u ? ~0ull : __ballot((uint32_t)lane % parts == part);
-        for (unsigned long long jb = all & ~set & mine; jb; jb &= jb - 1ull) {
+        const unsigned long long outside = all & ~set & mine;
+        if (shift < 6) {
+            const int count = __popcll(outside), part = lane >> shift;
+            if ((outside >> lane) & 1ull) out_s[__popcll(outside & ((1ull << lane) - 1ull))] = (unsigned char)lane;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int first = 0; first < count; first += 64 >> shift) {
+                const bool in = first + part < count;
+                const int j = out_s[in ? first + part : 0];
+                const uint32_t row = (uint32_t)__shfl((int)(uint32_t)my_row, j, 64);   // rows are counted in 31 bits
+                uint2* to = reinterpret_cast<uint2*>(R + ((size_t)out_off + row) * rs + 2 * hl);
+                uint32_t v0 = kInfBits, v1 = kInfBits;
+                if (hl < rd) {
+#pragma unroll
+                    for (int mm = 0; mm < C; ++mm) {
+                        const uint2 q = *reinterpret_cast<const uint2*>(qs + (j * n + b[mm]) * rs + 2 * hl);
+                        const uint32_t x0 = q.x > a[mm][0] ? q.x : a[mm][0], x1 = q.y > a[mm][1] ? q.y : a[mm][1];
+                        v0 = x0 < v0 ? x0 : v0;
+                        v1 = x1 < v1 ? x1 : v1;
+                    }
+                }
+                // links within the bound are few: most rows hold nothing within it
+                if (__ballot(v0 <= bound || v1 <= bound) == 0ull) {
+                    if (in && hl < rd) *to = make_uint2(kInfBits, kInfBits);
+                    continue;
+                }
+                // as below; a run that passes the end of a row is never asked for
+                run2[lane] = make_uint2(v0, v1);
+                if (top_run >= 1) {
+                    const uint32_t n0 = few_next_lane(v0, kInfBits);
+                    v0 = v1 < v0 ? v1 : v0;
+                    v1 = n0 < v1 ? n0 : v1;
+                    run2[kFewRunRow / 2 + lane] = make_uint2(v0, v1);
+                }
+                if (top_run >= 2) {
+                    const uint32_t n0 = few_next_lane(v0, kInfBits), n1 = few_next_lane(v1, kInfBits);
+                    v0 = n0 < v0 ? n0 : v0;
+                    v1 = n1 < v1 ? n1 : v1;
+                    run2[2 * (kFewRunRow / 2) + lane] = make_uint2(v0, v1);
+                }
+                for (int k = 3; k <= top_run; ++k) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    const uint2 f = run2[(k - 1) * (kFewRunRow / 2) + lane + (1 << (k - 2))];
+                    v0 = f.x < v0 ? f.x : v0;
+                    v1 = f.y < v1 ? f.y : v1;
+                    run2[k * (kFewRunRow / 2) + lane] = make_uint2(v0, v1);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const uint2 d = *reinterpret_cast<const uint2*>(query + j * rs + 2 * (hl < rd ? hl : 0));
+                const unsigned char* runb = reinterpret_cast<const unsigned char*>(run);
+                constexpr uint32_t kNone = (kFewRunRow - 1) * 4u;
+                auto at = [&](uint32_t off) -> uint32_t {   // the row of a part starts 2 * lanes entries after the one before
+                    const uint32_t v = *reinterpret_cast<const uint32_t*>(runb + (off == kNone ? 0u : off + (uint32_t)part * (uint32_t)lanes * 8u));
+                    return off == kNone ? kInfBits : v;
+                };
+                const uint32_t a0 = at(d.x & 0xFFFFu), b0 = at(d.x >> 16), a1 = at(d.y & 0xFFFFu), b1 = at(d.y >> 16);
+                const uint32_t res0 = a0 < b0 ? a0 : b0, res1 = a1 < b1 ? a1 : b1;
+                if (in && hl < rd) *to = make_uint2(res0, res1);
+                if (in && hl == 0) atomicMin(&least_s[j], res0);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else
+        for (unsigned long long jb = outside; jb; jb &= jb - 1ull) {
             const int j = __ffsll((long long)jb) - 1;
             const unsigned long long row = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(my_row >> 32), j) << 32) |
                                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_row, j);
@@ -316,6 +445,11 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
                     v0 = x0 < v0 ? x0 : v0;
                     v1 = x1 < v1 ? x1 : v1;
                 }
+            }
+            // links within the bound are few: most rows hold nothing within it
+            if (__ballot(v0 <= bound || v1 <= bound) == 0ull) {
+                if (lane < rd) *reinterpret_cast<uint2*>(R + (size_t)(out_off + row) * rs + 2 * lane) = make_uint2(kInfBits, kInfBits);
+                continue;
             }
             // minima over runs of 2^k entries starting at each entry
             run2[lane] = make_uint2(v0, v1);
@@ -360,6 +494,11 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
             set = few_next_set(set);
         }
     }
+    if (shift < 6) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        first_best = least_s[lane];
+    }
     if (first_best < kInfBits) atomicMin(&st->first_best[lane], first_best);
 }
 
@@ -381,27 +520,45 @@ __global__ __launch_bounds__(kFewTopWaves * 64) void few_top_kernel(FewLayout y,
                                                                    const float* __restrict__ B) {
     extern __shared__ __align__(16) uint32_t few_smem[];   // bandwidths transposed: [b][j] = B[j][b]
     __shared__ float t_s[PPO_MAX_L];
-    const int L = y.L, n = y.n, rs = y.rs, rd = rs / 2;
     const int inst = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     unsigned char* base = ws + (size_t)inst * y.stride;
+    const FewDims dims(y, base);
+    const int L = dims.L, n = dims.n, rs = dims.rs, rd = rs / 2;
+    if ((unsigned long long)blockIdx.x * kFewTopWaves >= kFewBinomials.c[n][C]) return;
     const uint32_t* __restrict__ qs = reinterpret_cast<const uint32_t*>(base + y.qs_off);
     FewState* st = reinterpret_cast<FewState*>(base + y.state_off);
     uint32_t* R = rows + (size_t)inst * (y.rows_bytes / 4);
-    uint32_t* marks = R + (size_t)y.full_rows * rs;   // one word per set of level C
+    const unsigned long long in_off = dims.first_row(y, C);
+    uint32_t* marks = R + (size_t)dims.first_row(y, C + 1) * rs;   // one word per set of level C, after all rows
     float* Bt = reinterpret_cast<float*>(few_smem);
-    for (int i = tid; i < n * n; i += kFewTopWaves * 64) {
-        const int j = i / n, b = i - j * n;
-        Bt[b * n + j] = B[(size_t)inst * n * n + i];
-    }
-    for (int i = tid; i < L; i += kFewTopWaves * 64) {
-        const float x = t[(size_t)inst * L + i];
-        t_s[i] = x == 0.0f ? 0.0f : x;   // -0 is a size of zero: +0
+    __shared__ unsigned char node_s[kFewMaxN];
+    if (y.confined) {
+        if (tid < n) node_s[tid] = (unsigned char)few_node(y, st->confined, tid);
+        __syncthreads();
+        for (int i = tid; i < n * n; i += kFewTopWaves * 64) {
+            const int j = i / n, b = i - j * n;
+            Bt[b * n + j] = B[((size_t)inst * y.n + node_s[j]) * y.n + node_s[b]];
+        }
+        for (int i = tid; i < L - 1; i += kFewTopWaves * 64) {
+            const float x = t[(size_t)inst * y.L + few_cut(y, st->confined, i + 1) - 1];
+            t_s[i] = x == 0.0f ? 0.0f : x;   // -0 is a size of zero: +0
+        }
+    } else {
+        for (int i = tid; i < n * n; i += kFewTopWaves * 64) {
+            const int j = i / n, b = i - j * n;
+            Bt[b * n + j] = B[(size_t)inst * n * n + i];
+        }
+        for (int i = tid; i < L; i += kFewTopWaves * 64) {
+            const float x = t[(size_t)inst * L + i];
+            t_s[i] = x == 0.0f ? 0.0f : x;
+        }
     }
     // lane j: last cut of a first segment on node j (another node follows)
     int my_hi0 = lane < n ? (int)base[y.hi_off + lane * (L + 1)] : 0;
     my_hi0 = my_hi0 < L - 1 ? my_hi0 : L - 1;
     const int max_hi0 = (int)~few_wave_min(~(uint32_t)my_hi0);
+    const uint32_t known = few_bound(y, st);
     __syncthreads();
     const unsigned long long nsets = kFewBinomials.c[n][C];
     const unsigned long long total_waves = (unsigned long long)gridDim.x * kFewTopWaves;
@@ -417,7 +574,7 @@ __global__ __launch_bounds__(kFewTopWaves * 64) void few_top_kernel(FewLayout y,
         const uint32_t mine = lane < n ? __hip_atomic_load(&st->first_best[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kInfBits;
         {
             unsigned long long bits = set;
-            const uint32_t* arow = R + (size_t)(y.level_off[C] + u * (unsigned long long)C) * rs + 2 * lane;
+            const uint32_t* arow = R + (size_t)(in_off + u * (unsigned long long)C) * rs + 2 * lane;
 #pragma unroll
             for (int mm = 0; mm < C; ++mm) {
                 b[mm] = __ffsll((long long)bits) - 1;
@@ -428,7 +585,7 @@ __global__ __launch_bounds__(kFewTopWaves * 64) void few_top_kernel(FewLayout y,
                 a[mm][1] = v.y;
             }
         }
-        const uint32_t bound = few_wave_min(mine);
+        const uint32_t least = few_wave_min(mine), bound = least < known ? least : known;
         const unsigned long long outside = all & ~set;
         // a value of node j is wanted if it is below my_limit
         const uint32_t my_limit = mine == bound ? bound : bound + 1u;
@@ -499,14 +656,16 @@ constexpr int kFewStepWaves = 16;
 __global__ __launch_bounds__(kFewStepWaves * 64) void few_step_kernel(FewLayout y, unsigned char* __restrict__ ws, int s,
                                                       float* __restrict__ beta_out, int32_t* __restrict__ segs_out,
                                                       int32_t* __restrict__ cuts_out, int32_t* __restrict__ order_out) {
-    const int L = y.L, n = y.n, rs = y.rs, inst = blockIdx.x, lane = threadIdx.x & 63;
+    const int inst = blockIdx.x, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     unsigned char* base = ws + (size_t)inst * y.stride;
+    const FewDims dims(y, base);
+    const int L = dims.L, n = dims.n, rs = dims.rs;
     const unsigned char* __restrict__ hi_t = base + y.hi_off;
     const uint32_t* __restrict__ qs = reinterpret_cast<const uint32_t*>(base + y.qs_off);
     FewState* st = reinterpret_cast<FewState*>(base + y.state_off);
-    int32_t* order = order_out + (size_t)inst * n;
-    int32_t* cuts = cuts_out ? cuts_out + (size_t)inst * (n - 1) : nullptr;
+    int32_t* order = order_out + (size_t)inst * y.n;
+    int32_t* cuts = cuts_out ? cuts_out + (size_t)inst * (y.n - 1) : nullptr;
     auto hi = [&](int j, int e) -> int { return hi_t[j * (L + 1) + e]; };
     // is cut e2 (1 <= e2 <= L) inside the window of node j that starts at the latest cut of (g0, g1) below e2?
     auto covered = [&](unsigned long long g0, unsigned long long g1, int j, int e2) -> bool {
@@ -527,9 +686,9 @@ __global__ __launch_bounds__(kFewStepWaves * 64) void few_step_kernel(FewLayout 
         best = few_wave_min(mine);
         chosen = (uint32_t)(__ffsll((long long)__ballot(mine == best)) - 1);
         if (wave == 0) {
-            for (int i = lane; i < n; i += 64) order[i] = -1;
+            for (int i = lane; i < y.n; i += 64) order[i] = -1;
             if (cuts)
-                for (int i = lane; i < n - 1; i += 64) cuts[i] = -1;
+                for (int i = lane; i < y.n - 1; i += 64) cuts[i] = -1;
             if (lane == 0) st->best = best;
         }
         if (best >= kInfBits) {
@@ -580,13 +739,13 @@ __global__ __launch_bounds__(kFewStepWaves * 64) void few_step_kernel(FewLayout 
             const unsigned long long m1 = __ballot(((g1 >> lane) & 1ull) && lane + 64 < e && hi(jq, lane + 64 < L ? lane + 64 : L) >= e);
             if (!(m0 | m1)) break;   // cannot happen: e was reached from such a start
             const int first = m0 ? __ffsll((long long)m0) - 1 : 63 + __ffsll((long long)m1);
-            if (lane == 0) cuts[q - 1] = (int32_t)first;
+            if (lane == 0) cuts[q - 1] = (int32_t)few_cut(y, st->confined, first);
             e = first;
         }
         if (lane == 0) {
             beta_out[inst] = __uint_as_float(best);
             segs_out[inst] = p;
-            for (int q = 0; q < p; ++q) order[q] = q == s - 1 ? last : st->seq[q];
+            for (int q = 0; q < p; ++q) order[q] = few_node(y, st->confined, q == s - 1 ? last : st->seq[q]);
             st->done = 1u;
         }
         return;
@@ -614,17 +773,19 @@ __global__ __launch_bounds__(kFewStepWaves * 64) void few_step_kernel(FewLayout 
 constexpr int kFewScanWaves = 4;
 __global__ __launch_bounds__(kFewScanWaves * 64) void few_scan_kernel(FewLayout y, unsigned char* __restrict__ ws,
                                                                       const uint32_t* __restrict__ rows, int s) {
-    const int n = y.n, rs = y.rs, rd = rs / 2;
     const int c = (int)blockIdx.y + 1, inst = blockIdx.z, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     unsigned char* base = ws + (size_t)inst * y.stride;
+    const FewDims dims(y, base);
+    const int n = dims.n, rs = dims.rs, rd = rs / 2;
     FewState* st = reinterpret_cast<FewState*>(base + y.state_off);
     if (st->done) return;
     const uint32_t best = st->best;
     const unsigned long long used = st->used;
     const uint32_t* R = rows + (size_t)inst * (y.rows_bytes / 4);
     // level pmax - 1 is most of the rows: those without a mark hold nothing within beta*
-    const uint32_t* marks = c == y.pmax - 1 ? R + (size_t)y.full_rows * rs : nullptr;
+    const unsigned long long in_off = dims.first_row(y, c);
+    const uint32_t* marks = c == y.pmax - 1 ? R + (size_t)dims.first_row(y, y.pmax) * rs : nullptr;
     const unsigned long long nsets = kFewBinomials.c[n][c];
     const unsigned long long total_waves = (unsigned long long)gridDim.x * kFewScanWaves;
     const unsigned long long per_wave = (nsets + total_waves - 1ull) / total_waves;
@@ -641,7 +802,7 @@ __global__ __launch_bounds__(kFewScanWaves * 64) void few_scan_kernel(FewLayout 
             const unsigned long long g0 = st->cand[j][0], g1 = st->cand[j][1];
             bool ok = false;
             if (lane < rd) {
-                const uint2 v = *reinterpret_cast<const uint2*>(R + (size_t)(y.level_off[c] + at * (unsigned long long)c + (unsigned long long)i) * rs + 2 * lane);
+                const uint2 v = *reinterpret_cast<const uint2*>(R + (size_t)(in_off + at * (unsigned long long)c + (unsigned long long)i) * rs + 2 * lane);
                 const int e0 = 2 * lane, e1 = e0 + 1;
                 const bool in0 = ((e0 < 64 ? g0 >> e0 : g1 >> (e0 - 64)) & 1ull) != 0ull;
                 const bool in1 = ((e1 < 64 ? g0 >> e1 : g1 >> (e1 - 64)) & 1ull) != 0ull;
@@ -683,9 +844,24 @@ __global__ __launch_bounds__(kFewScanWaves * 64) void few_scan_kernel(FewLayout 
 // ---------------------------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------------------------
+// Whether the search is confined to the nodes and cuts that can matter (ppo_cluster_bound.hip), and to values within the bound
+// found there.  That costs about 70 us (the bound 27, the walks 25 to 45).  Measured in us, without and with it: one cluster of
+// 50 nodes, 100 layers and 5 segments 480 / 259, of 40 nodes 273 / 204, 8 of 64 nodes, 30 layers and 4 segments 516 / 321, 4
+// paper-shaped ones of 50 nodes and 4 segments 945 / 206; but 8 of 21 nodes, 40 layers and 5 segments (230 thousand rows)
+// 200 / 214 and one of 60 layers, 30 nodes and 5 segments (120 thousand) 138 / 162.
+static bool few_confined(int n, int pmax, int n_inst) {
+    unsigned long long rows = 0;
+    for (int c = 1; c < pmax; ++c) rows += kFewBinomialsHost.c[n][c] * (unsigned long long)c;
+    return n >= 9 && pmax >= 2 && rows * (unsigned long long)n_inst >= 300000ull;
+}
 hipError_t launch_cluster_few_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
                                      int pmax, int n_inst, void* ws, void* rows, hipStream_t stream) {
-    const FewLayout y = FewLayout::make(L, n, pmax);
+    const FewLayout y = FewLayout::make(L, n, pmax, few_confined(n, pmax, n_inst));
+    if (y.confined) {
+        FewState* state = reinterpret_cast<FewState*>(static_cast<unsigned char*>(ws) + y.state_off);
+        const hipError_t e = launch_few_confine(t, m, M, B, L, n, pmax, n_inst, &state->confined, y.stride, stream);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(few_tables_kernel, dim3(n, n_inst), dim3(kFewTableThreads), 0, stream, t, m, M, B, y,
                        static_cast<unsigned char*>(ws), static_cast<uint32_t*>(rows));
     return hipGetLastError();
@@ -737,7 +913,7 @@ static hipError_t few_launch_levels(int n_inst, hipStream_t stream, const FewLay
 static uint32_t few_grid(unsigned long long sets, int waves_per_block) {
     // enough workgroups to fill the chip several times over, never more than there are sets
     unsigned long long blocks = (sets + (unsigned long long)waves_per_block - 1ull) / (unsigned long long)waves_per_block;
-    const unsigned long long cap = 256ull * 32ull;
+    const unsigned long long cap = 256ull * 8ull;
     if (blocks > cap) blocks = cap;
     return (uint32_t)(blocks ? blocks : 1ull);
 }
@@ -746,7 +922,7 @@ static uint32_t few_grid(unsigned long long sets, int waves_per_block) {
 hipError_t launch_cluster_few_solve(const float* t, const float* B, int L, int n, int pmax, int n_inst, void* ws_, void* rows_,
                                     float* beta_out, int32_t* segs_out, int32_t* cuts_out, int32_t* order_out,
                                     hipStream_t stream) {
-    const FewLayout y = FewLayout::make(L, n, pmax);
+    const FewLayout y = FewLayout::make(L, n, pmax, few_confined(n, pmax, n_inst));
     unsigned char* ws = static_cast<unsigned char*>(ws_);
     uint32_t* rows = static_cast<uint32_t*>(rows_);
     hipError_t e = few_launch_levels<1>(n_inst, stream, y, ws, rows, t, B);

@@ -10,17 +10,22 @@ from oracle import ppo_cluster_oracle as O
 from paper_2210_12219_amd import workloads as W
 
 
-def check(w, oracle=0):
+def check(w, oracle=0, segments=None):
     import torch
     from paper_2210_12219_amd import binding as ppo
     dev = ppo.to_device(w)
-    got = [x.cpu().numpy() for x in ppo.ppo_solve_cluster(*dev)]
+
+    def solve(a):
+        out = ppo.ppo_solve_cluster(*a) if segments is None else ppo.ppo_solve_cluster_few(*a, max_segments=segments)
+        return [x.cpu().numpy() for x in out]
+
+    got = solve(dev)
     for i in range(w.n_inst):
-        one = [x.cpu().numpy()[0] for x in ppo.ppo_solve_cluster(*(x[i:i + 1].contiguous() for x in dev))]
+        one = [x[0] for x in solve([x[i:i + 1].contiguous() for x in dev])]
         assert got[0][i].view(np.uint32) == one[0].view(np.uint32) and got[1][i] == one[1], i
         assert np.array_equal(got[2][i], one[2]) and np.array_equal(got[3][i], one[3]), i
     for i in range(oracle):
-        b, p, cuts, order = O.subset_dp(w.t[i], w.m[i], w.M[i], w.B[i])
+        b, p, cuts, order = O.subset_dp(w.t[i], w.m[i], w.M[i], w.B[i], segments)
         assert got[0][i].view(np.uint32) == np.float32(b).view(np.uint32) and got[1][i] == p
         assert np.array_equal(got[2][i], cuts) and np.array_equal(got[3][i], order)
     return got
@@ -61,3 +66,30 @@ def test_paper_shaped_clusters():
     for capacity in (10.0, 16.0, 64.0, 200.0):
         check(W.cluster_geometric(12, capacity, n_inst=batch(12), seed=int(capacity)), oracle=1)
     check(W.cluster_mixed(16, L=100, n_inst=2, seed=3))
+
+
+def few_batch(n, segments):
+    """instances that ppo_solve_cluster_few searches on what can matter"""
+    from math import comb
+    return -(-300000 // sum(comb(n, c) * c for c in range(1, segments)))
+
+
+@pytest.mark.parametrize("n,L,segments", [(12, 100, 6), (14, 33, 5), (30, 100, 5), (30, 17, 5), (50, 64, 4), (50, 128, 4), (64, 40, 4),
+                                          (64, 100, 3)])
+def test_few_segments(n, L, segments):
+    batch = few_batch(n, segments)
+    w = W.cluster_mixed(n, L=L, n_inst=batch, seed=n + L, capacity_factor=0.8 / segments)
+    rng = np.random.default_rng(n + L)
+    for i in range(w.n_inst):
+        if i % 4 == 1:
+            w.t[i, rng.random(L) < 0.3] = -0.0 if i % 8 == 1 else 0.0
+        if i % 4 == 2:   # ties
+            w.t[i] = np.round(w.t[i]) + 1
+            w.B[i] = np.where(np.eye(n, dtype=bool), 0, np.round(w.B[i]) + 1)
+        if i % 4 == 3:   # short of memory, down to none that fits
+            w.M[i] *= np.float32(rng.uniform(0.2, 0.9))
+    check(w, oracle=2 if n < 15 else 0, segments=segments)
+
+
+def test_few_segments_of_one_capacity():
+    check(W.cluster_geometric(40, 32.0, n_inst=few_batch(40, 4), seed=4), segments=4)

@@ -133,23 +133,27 @@ __global__ __launch_bounds__(kPreThreads) void precompute_kernel(const float* __
 // Order codes of the quotients (needs L >= 2): grid.x slices of whole node pairs, grid.y = instance.  All
 // sorted rows are staged in LDS; a thread adds up, over the links, how many of a link's quotients are strictly
 // below its own (a binary search each, four links at a time); the block then writes the aligned quotient
-// rows `qa` of its pairs.
-constexpr int kMaxQuot = (PPO_MAX_K * (PPO_MAX_K - 1) / 2) * (PPO_MAX_L - 1);
+// rows `qa` of its pairs.  Bound by issue: rows padded with +inf to a power of two let a step of the search be a read at a
+// constant offset, a comparison and an addition (ppo_prepare of 64 x (100, 10): 77 us with its ends checked, 66 now; 4096 x (96, 8):
+// 847 and 723).
+constexpr int kMaxPairs = PPO_MAX_K * (PPO_MAX_K - 1) / 2;
+constexpr int kCodeRow = 128;   // a search adds 64, 32 .. 1: it looks at places 0 .. 126
+static_assert(PPO_MAX_L - 1 < kCodeRow, "a row and its padding");
 __global__ __launch_bounds__(kPreThreads) void codes_kernel(Layout y, unsigned char* __restrict__ ws) {
-    __shared__ float rows_s[kMaxQuot];           // [npairs][L-1], each row in increasing order
+    __shared__ float rows_s[kMaxPairs * kCodeRow];   // [npairs][kCodeRow], each row in increasing order, +inf beyond L-1
     __shared__ uint16_t code_s[kPreThreads];     // codes of this block's pairs, by layer
     const int L = y.L, len = L - 1, inst = blockIdx.y, tid = threadIdx.x;
     const int ppb = kPreThreads / len;   // pairs per block
-    const int nq = y.npairs * len;
     unsigned char* base = ws + (size_t)inst * y.stride;
     uint16_t* qc = reinterpret_cast<uint16_t*>(base + y.qc_off);
     float* dec = reinterpret_cast<float*>(base + y.dec_off);
     const float* __restrict__ qv = reinterpret_cast<const float*>(base + y.qv_off);
-    for (int j = tid; j < nq; j += kPreThreads) rows_s[j] = qv[j];
+    for (int row = tid >> 6; row < y.npairs; row += kPreThreads / 64)
+        for (int c = tid & 63; c < kCodeRow; c += 64) rows_s[row * kCodeRow + c] = c < len ? qv[row * len + c] : __uint_as_float(kInfBits);
     __syncthreads();
     const int pl = tid / len, r = tid - pl * len, p = blockIdx.x * ppb + pl;
     const bool mine = pl < ppb && p < y.npairs;
-    const float x = mine ? rows_s[p * len + r] : 0.0f;
+    const float x = mine ? rows_s[p * kCodeRow + r] : 0.0f;
     const int i = mine ? (int)base[y.ord_off + r] : 0;   // the layer whose quotient this is
     int below = 0;
     if (mine) {
@@ -157,20 +161,14 @@ __global__ __launch_bounds__(kPreThreads) void codes_kernel(Layout y, unsigned c
             int pos[4] = {0, 0, 0, 0};   // number of entries of each row below x
             const float* row[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) row[u] = rows_s + (p0 + u < y.npairs ? p0 + u : p0) * len;
+            for (int u = 0; u < 4; ++u) row[u] = rows_s + (p0 + u < y.npairs ? p0 + u : p0) * kCodeRow;
 #pragma unroll
             for (int step = 64; step >= 1; step >>= 1) {
                 float v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int np = pos[u] + step;
-                    v[u] = row[u][(np <= len ? np : len) - 1];
-                }
+                for (int u = 0; u < 4; ++u) v[u] = row[u][pos[u] + step - 1];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int np = pos[u] + step;
-                    if (np <= len && v[u] < x) pos[u] = np;
-                }
+                for (int u = 0; u < 4; ++u) pos[u] += v[u] < x ? step : 0;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) below += p0 + u < y.npairs ? pos[u] : 0;
@@ -285,11 +283,13 @@ __global__ __launch_bounds__(kEnumThreads) void enumerate_kernel(Layout y, const
 }
 
 // ---------------------------------------------------------------------------------------------
-// traceback: one block per instance, lane 0 works.  Decodes the winning rank, reruns its DP with all
+// traceback: one wave per instance.  Decodes the winning rank, reruns its DP with all
 // k rows kept, then walks back from e = L: for s = k-1 .. 1 the cut c_s is the smallest legal start
 // i whose candidate max(D_{s-1}[i], q[i-1]) does not exceed beta, and e <- c_s.  Because
 // D_{s-1}[i] <= beta exactly when some feasible prefix ends at i within the bottleneck, this yields
 // the cut vector that minimises c_{k-1}, then c_{k-2}, ..., then c_1.
+// What bounds it: the latency of one wave's LDS reads, row after row.  Windows are answered from minima over runs of
+// 2, 4, .. candidates: 64 x (100, 10) 36 us a call with a scan of each window, 24 now; 37 x (127, 9) 36 and 22.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned char* __restrict__ ws,
                                                        const unsigned long long* __restrict__ best_key,
@@ -298,6 +298,7 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
     __shared__ uint16_t rows[PPO_MAX_K][PPO_MAX_L + 1];
     __shared__ uint16_t q_s[PPO_MAX_K][PPO_MAX_L];              // [s]: link into the node at position s
     __shared__ unsigned char lo_s[PPO_MAX_K][PPO_MAX_L + 1];   // [s]: window starts of the node at position s
+    __shared__ uint16_t runs[8][PPO_MAX_L];                     // [d][i]: least of the 2^d candidates from cut i on
     const int L = y.L, k = y.k, inst = blockIdx.x, lane = threadIdx.x;
     const unsigned char* base = ws + (size_t)inst * y.stride;
     const unsigned char* lo_t = base + y.lo_off;
@@ -332,14 +333,55 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
     for (int s = 1; s < k; ++s) {
         const uint16_t* q = q_s[s];
         const unsigned char* lo = lo_s[s];
+        int longest = 0;   // of the windows that this lane answers
+        for (int e = lane; e <= L; e += 64)
+            if (e >= s + 1 && e <= L - (k - 1 - s)) {
+                const int len = e - (lo[e] > s ? lo[e] : s);
+                longest = len > longest ? len : longest;
+            }
+        if (!__any(longest > 8)) {
+            // short windows: one candidate after the other (300 x (20, 10): 13 us a call, by runs 15)
+            for (int e = lane; e <= L; e += 64) {
+                uint32_t acc = kCodeInf;
+                if (e >= s + 1 && e <= L - (k - 1 - s)) {
+                    const int first = lo[e] > s ? lo[e] : s;
+                    for (int i = first; i < e; ++i) {
+                        const uint32_t d = rows[s - 1][i], g = q[i - 1];
+                        const uint32_t c = d > g ? d : g;
+                        acc = c < acc ? c : acc;
+                    }
+                }
+                rows[s][e] = (uint16_t)acc;
+            }
+            __syncthreads();
+            continue;
+        }
+        // minima over runs of candidates (runs that pass the chain's end stop there), then two runs cover a window
+        for (int i = lane; i < L; i += 64) {
+            uint32_t c = kCodeInf;
+            if (i >= s) {
+                const uint32_t d = rows[s - 1][i], g = q[i - 1];
+                c = d > g ? d : g;
+            }
+            runs[0][i] = (uint16_t)c;
+        }
+        for (int d = 1; __any((longest >> d) != 0); ++d) {
+            __syncthreads();
+            const int half = 1 << (d - 1);
+            for (int i = lane; i < L; i += 64) {
+                const uint32_t a = runs[d - 1][i], b = runs[d - 1][i + half < L ? i + half : L - 1];
+                runs[d][i] = (uint16_t)(a < b ? a : b);
+            }
+        }
+        __syncthreads();
         for (int e = lane; e <= L; e += 64) {
             uint32_t acc = kCodeInf;
             if (e >= s + 1 && e <= L - (k - 1 - s)) {
                 const int first = lo[e] > s ? lo[e] : s;
-                for (int i = first; i < e; ++i) {
-                    const uint32_t d = rows[s - 1][i], g = q[i - 1];
-                    const uint32_t c = d > g ? d : g;
-                    acc = c < acc ? c : acc;
+                if (first < e) {
+                    const int d = 31 - __clz(e - first);
+                    const uint32_t a = runs[d][first], b = runs[d][e - (1 << d)];
+                    acc = a < b ? a : b;
                 }
             }
             rows[s][e] = (uint16_t)acc;

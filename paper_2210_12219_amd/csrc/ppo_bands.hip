@@ -30,7 +30,7 @@
 // what every wave of a workgroup works out for itself in each phase, and it grows with the waves.  The phases that one wave
 // or a few work alone (sums, windows, answer) overlap with those of the other workgroups of the compute unit.
 // Measured, before and now: 4096 x (96, 8) of transformers 624 / 354 us, of random chains 739 / 583, 1024 x (65, 8) 218 / 143;
-// staged (tables and final stage included) 64 x (100, 10) 260 / 214, 1024 x (50, 6) 180 / 125, 300 x (20, 10) 313 / 159.
+// staged (tables and final stage included) 64 x (100, 10) 260 / 197, 1024 x (50, 6) 180 / 125, 300 x (20, 10) 313 / 159.
 #include "ppo_sets.h"
 
 namespace ppo {
@@ -133,6 +133,9 @@ struct BandsLds {
 
 // dwords of the rows of an instance in global memory, a multiple of 256 bytes
 __host__ __device__ inline uint32_t row_dwords(int k, int rd) { return (((uint32_t)k << (k - 1)) * (uint32_t)rd + 63u) & ~63u; }
+// ... of an area: no range is longer.  Sets of c < k nodes are met at cuts from k - c to L - c, the set of all at up to L - k, and
+// a row starts at an even cut.
+__host__ __device__ inline uint32_t area_dwords(int k, int L) { return row_dwords(k, (L - k + 3 < L + 1 ? L - k + 3 : L + 1) / 2); }
 
 // What the levels of an instance work on.
 struct BandsCtx {
@@ -894,7 +897,7 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
     for (uint32_t inst = blockIdx.x; inst < (uint32_t)task.n_inst; inst += gridDim.x) {
         if (PART == kTail) {
             const BandsLds lds = BandsLds::make(task.L, task.k);
-            const uint4* image = reinterpret_cast<const uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + row_dwords(task.k, (task.L + 1) / 2));
+            const uint4* image = reinterpret_cast<const uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + area_dwords(task.k, task.L));
             for (uint32_t i = threadIdx.x; i < lds.run_off / 16u; i += blockDim.x) reinterpret_cast<uint4*>(sm)[i] = image[i];
         } else {
             bands_inputs<KMAX, PART>(sm, task, inst, fresh, sets);
@@ -917,7 +920,7 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
         if (PART == kHead) {
             bands_levels<KMAX, PART>(sm, task, inst, 1, task.from);
             const BandsLds lds = BandsLds::make(task.L, task.k);
-            uint4* image = reinterpret_cast<uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + row_dwords(task.k, (task.L + 1) / 2));
+            uint4* image = reinterpret_cast<uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + area_dwords(task.k, task.L));
             for (uint32_t i = threadIdx.x; i < lds.run_off / 16u; i += blockDim.x) image[i] = reinterpret_cast<const uint4*>(sm)[i];
             __syncthreads();
             continue;
@@ -972,7 +975,7 @@ __global__ __launch_bounds__(kLevelWaves * 64, 6) void bands_level_kernel(const 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const BandsLds lds = BandsLds::make(L, k);
     uint32_t* slot = task.slots + (size_t)blockIdx.y * task.slot_dwords;
-    const unsigned char* image = reinterpret_cast<const unsigned char*>(slot + row_dwords(k, (L + 1) / 2));
+    const unsigned char* image = reinterpret_cast<const unsigned char*>(slot + area_dwords(k, L));
     const BandsShared& shg = *reinterpret_cast<const BandsShared*>(image);
     {
         // four sets to a wave need fewer workgroups than the grid has room for
@@ -1124,9 +1127,11 @@ hipError_t launch_bands_solve(const float* t, const float* m, const float* M, co
 }
 
 // Bytes of an area for one instance of the staged search by subsets; 0 if rows of the whole chain fit into LDS.
+// Areas are as small as can be told beforehand: the stream-ordered allocator hands out up to 64 MiB in 60 us and more in 340 (the
+// memory goes back to the system after each call that is waited for).  64 x (100, 10) takes 60 MiB; with rows of L entries it would be 65.
 size_t bands_slot_bytes(int L, int k) {
     if (k <= kSmallK && longest_lds(L, k) <= whole_lds(L, k)) return 0;
-    return (size_t)row_dwords(k, (L + 1) / 2) * 4 + (k <= kSmallK ? 0 : BandsLds::make(L, k).run_off);
+    return (size_t)area_dwords(k, L) * 4 + (k <= kSmallK ? 0 : BandsLds::make(L, k).run_off);
 }
 int bands_resident(int k) { return k <= kSmallK ? 1024 : 256; }
 

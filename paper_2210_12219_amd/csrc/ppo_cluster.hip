@@ -166,8 +166,8 @@ __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterL
 // 1, 2, 4 .. entries of it in LDS, as far as the longest window needs them, from which the minimum over the
 // window (e, hi[j][e]] is two reads.  grid.x workgroups share the sets, grid.y = instance.
 //
-// What bounds it: instruction issue of all kinds.  One cluster of 20 nodes and 100 layers takes 67 scalar, 56 vector and
-// 21 LDS instructions a row, which fills 0.65, 0.54 and 0.46 of these units' time; of the time of its five to six waves on
+// What bounds it: instruction issue of all kinds.  One cluster of 20 nodes and 100 layers searched whole takes 67 scalar, 56
+// vector and 21 LDS instructions a row, which fills 0.65, 0.54 and 0.46 of these units' time; of the time of its five to six waves on
 // a SIMD 0.38 is spent ready and waiting for a turn, 0.32 waiting for data.  The quotients of unordered pairs and run
 // tables without padding let two workgroups of 16 waves share a compute unit there (level 11: 367 us before, 340 now,
 // under the profiler); two sets to a wave nearly halve the levels of 50 layers (15 nodes, 32 instances: 253 us to 137).

@@ -5,8 +5,8 @@
 
 namespace ppo {
 
-// Codes as in the fixed-k kernels: kCodeZero for the value 0, kCodeZero + 1 + #{smaller quotients}, kCodeInf for
-// +inf: positive normal binary16 patterns, so the three-input binary16 minimum acts as an integer minimum.
+// Codes as in the fixed-k kernels: kCodeZero for the value 0 (also that of a link: with the number of segments free it ties
+// with a segment that needs none), kCodeZero + 1 + #{smaller quotients}, kCodeInf for +inf: positive normal binary16 patterns, so the three-input binary16 minimum acts as an integer minimum.
 // Everything these kernels read as a code is written by them as one (a stray pattern could win that minimum).
 constexpr uint32_t kClZero = kCodeZero, kClInf = kCodeInf;
 constexpr int kClPreThreads = 1024;

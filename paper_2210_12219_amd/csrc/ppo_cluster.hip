@@ -42,7 +42,7 @@ size_t cluster_rows_bytes(int L, int n) { return ClusterLayout::make(L, n).rows_
 // ---------------------------------------------------------------------------------------------
 // Tables of one instance: hi[j][e] = last e' such that layers [e, e') fit node j (e if none; the memory
 // rule with binary64 prefix sums) and the quotients of Eq. 3; then, in a second kernel over slices of
-// the quotients, their order codes (1 + the number of strictly smaller quotients of the instance).
+// the quotients, their order codes (1 + the number of strictly smaller quotients of the instance; 0 for the value 0).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kClPreThreads) void cluster_tables_kernel(const float* __restrict__ t,
                                                                       const float* __restrict__ m,
@@ -154,7 +154,8 @@ __global__ __launch_bounds__(kClCountThreads) void cluster_count_kernel(ClusterL
     below = below_s[mine];
     const int p = idx / len, r = idx - p * len;
     const int i = base[y.ord_off + r];
-    reinterpret_cast<uint16_t*>(base + y.qc_off)[p * L + i] = (uint16_t)(kClZero + 1 + below);
+    // a link that takes no time ties with no link at all
+    reinterpret_cast<uint16_t*>(base + y.qc_off)[p * L + i] = (uint16_t)(x == 0.0f ? kClZero : kClZero + 1 + below);
     reinterpret_cast<float*>(base + y.dec_off)[1 + below] = x;
 }
 

@@ -316,3 +316,19 @@ def test_cluster_rows_at_the_edges_of_a_wave(ppo, L):
         for pmax in (2, w.k):
             print(f"cluster edges L={L} n={w.k} pmax={pmax}", flush=True)
             assert_same(solve(ppo, w, pmax), oracle(w, pmax, CO.exhaustive), f"cluster edges L={L} n={w.k} pmax={pmax}")
+
+
+@pytest.mark.parametrize("n,L", [(2, 2), (5, 12), (7, 70), (9, 128)])
+def test_links_that_take_no_time_tie_with_none(ppo, n, L):
+    """Transfers of size 0 and nodes that hold the whole chain: a segment more costs nothing, and the smaller node sequence
+    wins whether it crosses links or not."""
+    rng = np.random.default_rng(100 * n + L)
+    w = W.random_instances(40 + n, 6, L, n, capacity_factor=1.5)
+    w.t[:, rng.random(L) < 0.5] = 0.0
+    w.t[:, :1] = -0.0
+    for i in range(w.n_inst):
+        w.M[i, rng.integers(1, n):] = 1.01 * w.m[i].sum()
+    for pmax in (1, n):
+        ref = oracle(w, pmax, CO.subset_dp)
+        assert_same(solve(ppo, w, pmax), ref, f"no time n={n} L={L} pmax={pmax}")
+    assert (ref[0] == 0).all() and (ref[1] > 1).any()

@@ -293,8 +293,13 @@ struct ConfineShared {
     unsigned char pos[PPO_MAX_L + 1], node[MAXN], ord[PPO_MAX_L];
     int changed[2][MAXN];
 };
-// t / B <= bound, and a little more: no quotient at most `bound` is missed, and no division is needed
-__device__ __forceinline__ float link_limit(uint32_t bound, float bandwidth) { return __uint_as_float(bound) * bandwidth * 1.000001f + 1.2e-38f; }
+// t / B <= bound, and a little more: no quotient whose binary32 value is at most `bound` is missed, and no division is needed.
+// A normal quotient is off by 2^-24 of itself.  Below the normal range it is off by up to 2^-150 whatever its size (and t / B
+// rounds to 0 for t up to 2^-150 B), so every t / B that is not normal is taken for one within a bound that is not: 2^-126 B.
+__device__ __forceinline__ float link_limit(uint32_t bound, float bandwidth) {
+    constexpr uint32_t kLeastNormal = 0x00800000u;
+    return __uint_as_float(bound > kLeastNormal ? bound : kLeastNormal) * bandwidth * 1.000001f + 1.2e-38f;
+}
 // all lanes' bits, in all lanes: shifts within rows of 16, then the last lane of a row to the next row, of two rows to the
 // next two
 __device__ __forceinline__ uint32_t or_lanes(uint32_t v) {

@@ -93,3 +93,45 @@ def test_few_segments(n, L, segments):
 
 def test_few_segments_of_one_capacity():
     check(W.cluster_geometric(40, 32.0, n_inst=few_batch(40, 4), seed=4), segments=4)
+
+
+def equal_links(n):
+    return np.where(np.eye(n, dtype=bool), 0.0, 1.0)
+
+
+def vanishing(kind, n, L, n_inst, segments, seed):
+    """Quotients t / B that round to 0 or to a value below the normal range, in clusters whose optimum is such a value: what
+    counts as within the bound has to be told by the rounded quotient, not by t against bound * B."""
+    w = W.random_instances(seed, n_inst, L, n, capacity_factor=1.0)
+    rng = np.random.default_rng(seed)
+    w.m[...] = 1.0
+    w.M[...] = np.ceil(1.2 * L / segments)
+    if kind == "to zero":   # the last node holds everything: 0 without a link, and every link is 0
+        w.M[:, -1] = L
+        w.t[...], w.B[...] = 1e-16, 1e30 * equal_links(n)
+    elif kind == "some to zero":   # zero transfers beside those that vanish and those that do not
+        w.t[...] = rng.choice([0.0, -0.0, 3e-16, 6e-16, 1e-14], w.t.shape)
+        w.B[...] = 1e30 * equal_links(n)
+    elif kind == "one value below the normal range":   # 2^-133 for every t, which differ by less than its rounding
+        w.t[...] = 2.0 ** -123 * (1.0 + rng.choice([0.0, 3e-6, 6e-6], w.t.shape))
+        w.B[...] = 1024.0 * equal_links(n)
+    else:   # few values each, from 2^-149 on
+        w.t[...] = 2.0 ** -139 * rng.integers(1, 2000, w.t.shape) * (1.0 + rng.choice([0.0, 1e-4], w.t.shape))
+        w.B[...] = 2.0 ** np.triu(rng.integers(4, 11, w.B.shape), 1)
+        w.B[...] = np.triu(w.B, 1) + np.triu(w.B, 1).transpose(0, 2, 1)
+    assert np.isfinite(w.t).all()
+    return w
+
+
+VANISHING = ["to zero", "some to zero", "one value below the normal range", "few values below it"]
+
+
+@pytest.mark.parametrize("kind", VANISHING)
+def test_quotients_that_vanish(kind):
+    check(vanishing(kind, 11, 24, batch(11), 6, 5), oracle=6)
+    check(vanishing(kind, 16, 8, 1, 5, 6), oracle=1)
+
+
+@pytest.mark.parametrize("kind", VANISHING)
+def test_quotients_that_vanish_few_segments(kind):
+    check(vanishing(kind, 12, 24, few_batch(12, 6), 5, 7), oracle=6, segments=6)

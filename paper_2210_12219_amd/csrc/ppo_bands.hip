@@ -44,9 +44,14 @@ constexpr int kSubsetMaxWaves = 16;
 constexpr int kSmallK = 8;   // up to as many nodes one workgroup does the whole search of an instance
 
 // G sets share a wave, 64 / G lanes of two entries each.  Minima over runs of 2^r entries of a wave's rows: a row of 64
-// dwords per r, up to half the entries of a set.
+// dwords per r, up to half the entries of a set.  One set: runs of 64 are asked for at the first 65 of its entries only, so the
+// last row is shorter, with a dword for what the other lanes write; then entries that are +inf, for windows that are empty.
 __host__ __device__ constexpr int run_levels(int G) { return G == 1 ? 7 : G == 2 ? 6 : G == 4 ? 5 : 4; }
-__host__ __device__ constexpr uint32_t run_dwords(int G) { return (uint32_t)run_levels(G) * 64u; }
+constexpr uint32_t kLastRun = 33u, kRunNone = 6u * 64u + kLastRun + 1u;   // the dword, and the first of those entries
+__host__ __device__ constexpr uint32_t run_dwords(int G) { return G == 1 ? kRunNone + 8u : (uint32_t)run_levels(G) * 64u; }
+// A search on whole rows (bands_whole_rows) answers windows from a table of queries.
+__host__ __device__ constexpr uint32_t query_pitch(int L) { return (uint32_t)(L + 2) & ~1u; }   // dwords of a node
+__host__ __device__ constexpr uint32_t query_bytes(int L, int k) { return L - k + 2 > 64 ? (uint32_t)k * query_pitch(L) * 4u : 0u; }
 
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 typedef short ss2 __attribute__((ext_vector_type(2)));
@@ -85,6 +90,7 @@ struct BandsShared {
     uint32_t bucket_lo, bucket_hi;
     uint32_t over16, over32, over64;           // bit c: a set of c nodes has a range of more than 16 (32, 64) entries
     uint32_t widest;                           // entries of the widest range
+    uint32_t whole, longest;                   // whole rows; log2 of the longest run that a window is then made of
     uint32_t level[PPO_MAX_K + 2];             // first entry of the sets of every size in `order`
 };
 
@@ -103,7 +109,7 @@ __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umu
 struct BandsLds {
     uint32_t info_off, order_off, P_off, t_off, B_off, M_off, hi_off, lo_off, q_off, run_off;
     int hp, qp;                                // pitch of a row of hi and lo (bytes), of quotient codes (dwords)
-    __host__ __device__ static BandsLds make(int L, int k) {
+    __host__ __device__ static BandsLds make(int L, int k, bool raw) {
         BandsLds s;
         size_t off = align_up(sizeof(BandsShared), 16);
         s.info_off = (uint32_t)off;                      // [2^k] u32
@@ -122,7 +128,7 @@ struct BandsLds {
         s.hi_off = (uint32_t)off;
         off = align_up(off + (size_t)k * s.hp, 16);
         s.lo_off = (uint32_t)off;
-        off = align_up(off + (size_t)k * s.hp + 128, 16);   // lanes beyond a row read on, and drop what they read
+        off = align_up(off + (raw ? 0 : (size_t)k * s.hp) + 128, 16);   // lanes beyond a row of hi read on, and drop what they read
         s.qp = (L + 1) / 2;
         s.q_off = (uint32_t)off;                         // [k][k] rows: entry e of (j, j'') belongs to the cut e
         off = align_up(off + ((size_t)k * k * s.qp + 64) * 4, 256);
@@ -160,6 +166,7 @@ __device__ __forceinline__ void bands_level(const BandsCtx c, int lane, int wave
     const int items = (int)((nsets + (uint32_t)G - 1u) / (uint32_t)G) << split;
     // a lane's place in a row of hi, of the links and of its run minima
     const uint32_t hi_at = 2u * (uint32_t)hl;
+    const int last_at = lane < (int)kLastRun ? lane : (int)kLastRun;   // in the row of the longest runs
     unsigned char* runb = reinterpret_cast<unsigned char*>(run32) + part * (kLanes * 4);
     auto put_row = [&](uint32_t up, uint32_t set, uint32_t j, uint32_t value) {   // a byte offset of 32 bits
         const uint32_t row = info_row(up) + (uint32_t)__popc(set & ((1u << j) - 1u));
@@ -249,7 +256,7 @@ __device__ __forceinline__ void bands_level(const BandsCtx c, int lane, int wave
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     cur = pk_min(cur, run32[(r - 1) * 64 + ((lane + (1 << (r - 2))) & 63)]);
-                    run32[r * 64 + lane] = cur;
+                    run32[r * 64 + (r == 6 ? last_at : lane)] = cur;
                 }
             }
             // The window of entry e (of R' + j's rows) in entries of R's: from max(e + 1, base) to min(hi, last); two
@@ -278,18 +285,138 @@ __device__ __forceinline__ void bands_level(const BandsCtx c, int lane, int wave
     }
 }
 
+// First cut of a row of a set of c nodes, with whole rows.
+__device__ __forceinline__ int whole_base(int k, int c) { return (k - c) & ~1; }
+
+// The same with whole rows, one set to a wave: all rows of a level start at the same cut, so windows are looked up in a table
+// (`query`, see bands_queries).
+template <int C>
+__device__ __forceinline__ void bands_level_whole(const BandsCtx c, int lane, int wave, int waves, int split, uint32_t nsets,
+                                                   const uint32_t* query, int run_top, uint32_t* __restrict__ run32, uint32_t* rows) {
+    constexpr uint32_t kInf2 = kCodeInf | (kCodeInf << 16);
+    const int rd = c.rd, k = c.k;
+    const bool in_row = lane < rd;
+    const int hq = in_row ? lane : rd - 1;     // lanes beyond a row look up its last window, and drop the answer
+    const int base = whole_base(k, C), ubase = whole_base(k, C + 1);
+    const uint32_t all = (1u << k) - 1u;
+    const int outside = k - C, per = (outside + (1 << split) - 1) >> split;
+    const int items = (int)nsets << split;
+    const int last_at = lane < (int)kLastRun ? lane : (int)kLastRun;
+    if (lane < 8) run32[kRunNone + (uint32_t)lane] = kInf2;
+    // the table holds places among entries that start at the cut 0
+    const unsigned char* runb = reinterpret_cast<const unsigned char*>(run32) - 2 * base;
+    const uint32_t* my_query = query + ubase + 2 * hq;
+    const uint32_t query_node = query_pitch(c.L), q_node = (uint32_t)c.qp * 4u;
+    // A row that starts two cuts before those it is made of has a first entry that no placement reaches (too few layers
+    // come before it); what it looks up is not one of the entries.
+    const uint32_t unreached = lane == 0 && base != ubase ? kCodeInf : 0u;
+    for (int it = wave; it < items; it += waves) {
+        const int skip = (it & ((1 << split) - 1)) * per;
+        const int count = outside - skip < per ? outside - skip : per;
+        if (count <= 0) continue;
+        const uint32_t mp = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.order[it >> split]);
+        const uint32_t first_row = info_row((uint32_t)__builtin_amdgcn_readfirstlane((int)c.info[mp]));
+        uint32_t jb = all & ~mp;
+        for (int i = 0; i < skip; ++i) jb &= jb - 1u;
+        uint32_t a[C], qoff[C];
+        {
+            const uint32_t* arow = rows + first_row * (uint32_t)rd + (uint32_t)hq;
+            uint32_t bits = mp;
+#pragma unroll
+            for (int m = 0; m < C; ++m) {
+                qoff[m] = (uint32_t)(__ffs(bits) - 1) * (uint32_t)k * q_node + (uint32_t)((base >> 1) + lane) * 4u;
+                asm volatile("" : "+v"(qoff[m]));   // one addition per row and member: the scalar unit has enough to do
+                bits &= bits - 1u;
+                const uint32_t x = arow[m * rd];
+                a[m] = in_row ? x : kInf2;
+            }
+        }
+        // where the rows of this set go: lane j works it out for the node j (the scalar unit has enough to do)
+        const uint32_t out_off = mul24(row_of(first_row, mp, (uint32_t)lane & 15u), (uint32_t)rd);
+        for (int i = 0; i < count; ++i, jb &= jb - 1u) {
+            const uint32_t j = (uint32_t)__ffs(jb) - 1u;
+            const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)out_off, (int)j);
+            const uint2 qd = *reinterpret_cast<const uint2*>(my_query + j * query_node);
+            uint32_t v;
+            {
+                uint32_t x[C];
+                const unsigned char* qj = reinterpret_cast<const unsigned char*>(c.q32) + j * q_node;
+#pragma unroll
+                for (int m = 0; m < C; ++m) x[m] = pk_max(*reinterpret_cast<const uint32_t*>(qj + qoff[m]), a[m]);
+                v = x[0];
+#pragma unroll
+                for (int m = 1; m + 1 < C; m += 2) v = pk_min3(v, x[m], x[m + 1]);
+                if (C % 2 == 0) v = pk_min(v, x[C - 1]);
+            }
+            run32[lane] = v;
+            const uint32_t next = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x130, 0xF, 0xF, true);
+            uint32_t cur = pk_min(v, (v >> 16) | (next << 16));
+            run32[64 + lane] = cur;
+            cur = pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, 0x130, 0xF, 0xF, true));
+            run32[128 + lane] = cur;
+            const uint32_t s1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)cur, 0x130, 0xF, 0xF, true);
+            cur = pk_min(cur, (uint32_t)__builtin_amdgcn_mov_dpp((int)s1, 0x130, 0xF, 0xF, true));
+            run32[192 + lane] = cur;
+#pragma unroll
+            for (int r = 4; r < run_levels(1); ++r) {
+                if (r > run_top) break;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                cur = pk_min(cur, run32[(r - 1) * 64 + ((lane + (1 << (r - 2))) & 63)]);
+                run32[r * 64 + (r == 6 ? last_at : lane)] = cur;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            uint32_t res[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t d = h ? qd.y : qd.x;
+                const uint32_t r1 = *reinterpret_cast<const uint16_t*>(runb + (d & 0xFFFFu));
+                const uint32_t r2 = *reinterpret_cast<const uint16_t*>(runb + (d >> 16));
+                res[h] = r1 < r2 ? r1 : r2;
+            }
+            if (in_row)   // a byte offset of 32 bits
+                *reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(rows) + ((row + (uint32_t)lane) << 2)) =
+                    (unreached ? kCodeInf : res[0]) | (res[1] << 16);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+}
+
+// Where an instance comes from and where its answer goes: arrays of the problem, and beta, cuts and order; or the tables
+// of ppo_prepare (window starts, exact codes, the codes' values), and the key.
+struct BandsTask {
+    const float *t, *m, *M, *B;
+    const unsigned char* prepared;
+    Layout y;
+    float* beta;
+    int32_t *cuts, *order;
+    unsigned long long* key;
+    uint32_t* slots;            // row areas in global memory
+    uint32_t slot_dwords;
+    uint32_t lds_bytes;         // of the launch
+    uint32_t query_bytes;       // of the levels that are launches: for the table of whole rows; 0: there is no room for it
+    int L, k, n_inst, from, to;
+    // log2 of the parts of the nodes outside, by level: 4 bits, two sets to a wave (or one), then four; 2 bits, whole rows
+    unsigned long long splits;
+    uint32_t whole_splits;
+};
+
 // A level with as many sets to a wave as its ranges allow.
 template <int C>
 __device__ __forceinline__ void bands_level_any(const BandsShared& sh, BandsCtx c, const uint16_t* order, int lane, int wave,
-                                                 int waves, unsigned long long splits, uint32_t* run32, uint32_t* rows) {
+                                                 int waves, const BandsTask& task, const uint32_t* query, uint32_t* run32,
+                                                 uint32_t* rows) {
     // nothing of a level is worked out before it: values of all levels and forms, hoisted, do not fit the registers
     asm volatile("" : "+v"(lane), "+s"(wave), "+s"(c.k), "+s"(c.rd), "+s"(c.qp));
     const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.level[C]);
     const uint32_t nsets = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.level[C + 1]) - first;
     const uint32_t here = 3u << C;   // the rows read and the rows written
     c.order = order + first;
-    const int s = (int)(splits >> (4 * C));
-    if (sh.over64 & here)
+    const int s = (int)(task.splits >> (4 * C));
+    if (sh.whole)
+        bands_level_whole<C>(c, lane, wave, waves, (int)(task.whole_splits >> (2 * C)) & 3, nsets, query, (int)sh.longest, run32, rows);
+    else if (sh.over64 & here)
         bands_level<C, 1>(c, lane, wave, waves, s & 3, nsets, run32, rows);
     else if (sh.over32 & here)
         bands_level<C, 2>(c, lane, wave, waves, s & 3, nsets, run32, rows);
@@ -318,22 +445,6 @@ __device__ __forceinline__ void put_code(uint16_t* q16, int k, int qp, int a, in
 // their own, see launch_bands_keys) the tables and the levels up to `from`, or those from `to` on and what follows them.
 enum { kWhole = 0, kHead = 1, kTail = 2 };
 
-// Where an instance comes from and where its answer goes: arrays of the problem, and beta, cuts and order; or the tables
-// of ppo_prepare (window starts, exact codes, the codes' values), and the key.
-struct BandsTask {
-    const float *t, *m, *M, *B;
-    const unsigned char* prepared;
-    Layout y;
-    float* beta;
-    int32_t *cuts, *order;
-    unsigned long long* key;
-    uint32_t* slots;            // row areas in global memory
-    uint32_t slot_dwords;
-    uint32_t lds_bytes;         // of the launch
-    int L, k, n_inst, from, to;
-    unsigned long long splits;  // 4 bits per level: log2 of the parts of the nodes outside, one or two sets to a wave, then four
-};
-
 // What the phases of the kernel share: an instance's tables in LDS.  Every phase works its own view out, from values that
 // are opaque to the compiler, so that nothing is held in registers from one phase to the next: hoisted out of the loop
 // over instances, the addresses and comparisons of all phases do not fit them, and what is then reloaded from scratch memory
@@ -349,7 +460,7 @@ struct BandsView {
     unsigned char *hi_s, *lo_s;
     uint16_t* q16;
     unsigned char* scratch;     // before the levels
-    uint32_t *run32, *lds_rows, *slot;
+    uint32_t *run32, *query, *lds_rows, *slot;
     bool raw, in_lds;
     const unsigned char* prep;
 
@@ -361,11 +472,11 @@ struct BandsView {
         asm volatile("" : "+v"(x));
         return x;
     }
-    __device__ __forceinline__ BandsView(unsigned char* sm, const BandsTask& task, uint32_t inst, bool may_be_raw, bool may_use_lds)
+    __device__ __forceinline__ BandsView(unsigned char* sm, const BandsTask& task, uint32_t inst, bool is_raw, bool may_use_lds)
         : tid(opaque_lane((int)threadIdx.x)), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)),
           waves(opaque((int)blockDim.x >> 6)), threads(waves * 64), L(opaque(task.L)), k(opaque(task.k)),
           sh(*reinterpret_cast<BandsShared*>(sm)) {
-        const BandsLds lds = BandsLds::make(L, k);
+        const BandsLds lds = BandsLds::make(L, k, is_raw);
         hp = lds.hp;
         qp = lds.qp;
         npairs = k * (k - 1) / 2;
@@ -380,7 +491,7 @@ struct BandsView {
         lo_s = sm + lds.lo_off;
         q16 = reinterpret_cast<uint16_t*>(sm + lds.q_off);
         scratch = sm + lds.run_off;
-        raw = may_be_raw && task.prepared == nullptr;
+        raw = is_raw;
         prep = raw ? nullptr : task.prepared + (size_t)inst * task.y.stride;
         slot = task.slots + (size_t)blockIdx.x * task.slot_dwords;
         // valid once the ranges are known: the run minima of a wave, and the rows behind those if they fit
@@ -390,7 +501,9 @@ struct BandsView {
         const uint32_t over64 = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.over64);
         const uint32_t run_pitch = over64 ? run_dwords(1) : over32 ? run_dwords(2) : over16 ? run_dwords(4) : run_dwords(8);
         run32 = reinterpret_cast<uint32_t*>(sm + lds.run_off) + (uint32_t)wave * run_pitch;
-        const uint32_t row_off = lds.run_off + (uint32_t)waves * run_pitch * 4u;
+        const uint32_t runs_end = lds.run_off + (uint32_t)waves * run_pitch * 4u;
+        query = reinterpret_cast<uint32_t*>(sm + runs_end);
+        const uint32_t row_off = runs_end + (__builtin_amdgcn_readfirstlane((int)sh.whole) ? query_bytes(L, k) : 0u);
         lds_rows = reinterpret_cast<uint32_t*>(sm + row_off);
         in_lds = may_use_lds && row_off + row_dwords(k, rd) * 4u <= task.lds_bytes;
     }
@@ -399,17 +512,19 @@ struct BandsView {
     }
 };
 #define PPO_BANDS_VIEW                                                                                                    \
-    const BandsView view(sm, task, inst, KMAX <= kSmallK, PART == kWhole);                                                \
+    const BandsView view(sm, task, inst, RAW, PART == kWhole);                                                \
     [[maybe_unused]] const int tid = view.tid, lane = view.lane, wave = view.wave, waves = view.waves, threads = view.threads; \
     [[maybe_unused]] const int L = view.L, k = view.k, hp = view.hp, qp = view.qp, npairs = view.npairs, rd = view.rd;     \
     [[maybe_unused]] const uint32_t all = view.all;                                                                        \
     [[maybe_unused]] BandsShared& sh = view.sh;                                                                           \
     [[maybe_unused]] uint32_t *info = view.info, *lds_rows = view.lds_rows, *slot = view.slot, *run32 = view.run32;        \
+    [[maybe_unused]] uint32_t* query = view.query;                                                                        \
     [[maybe_unused]] uint16_t *set_order = view.set_order, *q16 = view.q16;                                                \
     [[maybe_unused]] double* P = view.P;                                                                                   \
     [[maybe_unused]] float *t_s = view.t_s, *B_s = view.B_s, *M_s = view.M_s;                                              \
     [[maybe_unused]] unsigned char *hi_s = view.hi_s, *lo_s = view.lo_s, *scratch = view.scratch;                          \
-    [[maybe_unused]] const bool raw = view.raw, in_lds = view.in_lds;                                                      \
+    [[maybe_unused]] constexpr bool raw = RAW;                                                                             \
+    [[maybe_unused]] const bool in_lds = view.in_lds;                                                      \
     [[maybe_unused]] const unsigned char* prep = view.prep;
 
 // The sets' rows and places, requested by the kernel before anything else.
@@ -419,7 +534,7 @@ struct BandsFirst {
     uint32_t value[kEach], level;
 };
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_inputs(unsigned char* sm, const BandsTask& task, uint32_t inst, bool fresh,
                                               const BandsFirst<KMAX>& sets) {
     PPO_BANDS_VIEW
@@ -452,11 +567,12 @@ __device__ __forceinline__ void bands_inputs(unsigned char* sm, const BandsTask&
     if (tid == 0) {
         sh.over16 = sh.over32 = sh.over64 = 0u;
         sh.widest = 1u;
+        sh.whole = sh.longest = 0u;
         sh.lo_bits = sh.hi_bits = 0u;
     }
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_prefix(unsigned char* sm, const BandsTask& task, uint32_t inst, bool fresh,
                                               const BandsFirst<KMAX>& sets) {
     PPO_BANDS_VIEW
@@ -521,7 +637,7 @@ __device__ __forceinline__ void bands_prefix(unsigned char* sm, const BandsTask&
     }
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_windows(unsigned char* sm, const BandsTask& task, uint32_t inst) {
     PPO_BANDS_VIEW
     // hi[j][e] does not shrink as e grows (sums of weights >= 0), so a binary search finds what a scan would
@@ -531,7 +647,7 @@ __device__ __forceinline__ void bands_windows(unsigned char* sm, const BandsTask
             const int j = item / chunks, e = (item - j * chunks) * 64 + lane;
             if (e > L) continue;
             int end = e;
-            if (raw) {
+            if (RAW) {
                 const double cap = (double)M_s[j], at = P[e];
                 int step = 1;
                 while (step < L) step <<= 1;
@@ -551,7 +667,7 @@ __device__ __forceinline__ void bands_windows(unsigned char* sm, const BandsTask
     }
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_ranges(unsigned char* sm, const BandsTask& task, uint32_t inst) {
     PPO_BANDS_VIEW
     // Ranges of the sets: from the capacities together (a little wider than the sets need, by up to a layer and a half a
@@ -655,7 +771,63 @@ __device__ __forceinline__ void bands_ranges(unsigned char* sm, const BandsTask&
     }
 }
 
-template <int KMAX, int PART>
+// Window queries of whole rows: (e, min(hi, L-1)] is covered by two runs of 2^r entries, the one that starts at e + 1 and the
+// one that ends at its end; their byte offsets in a wave's run minima, 16 bits each, as if those started at the cut 0 (they
+// start at up to 12: the entries for empty windows, behind the run minima, are pointed at in their middle).
+__device__ __forceinline__ void bands_queries(BandsShared& sh, const unsigned char* hi_s, uint32_t* query, int L, int k, int hp, int threads) {
+    constexpr uint32_t kNone = kRunNone * 4u + 2u * (uint32_t)PPO_MAX_K;
+    const int pitch = (int)query_pitch(L);
+    uint32_t longest = 0;
+    for (int j = (int)threadIdx.x >> 6; j < k; j += threads >> 6)
+    for (int e = (int)threadIdx.x & 63; e < pitch; e += 64) {
+        uint32_t d = kNone | (kNone << 16);
+        const int hi = e < L ? (int)hi_s[j * hp + e] : 0, top = hi < L - 1 ? hi : L - 1;
+        if (top > e) {
+            const int r = 31 - __clz(top - e) < run_levels(1) - 1 ? 31 - __clz(top - e) : run_levels(1) - 1;
+            d = (uint32_t)(r * 256 + (e + 1) * 2) | (uint32_t)(r * 256 + (top - (1 << r) + 1) * 2) << 16;
+            longest = (uint32_t)r > longest ? (uint32_t)r : longest;
+        }
+        query[j * pitch + e] = d;
+    }
+    longest = wave_max(longest);
+    if ((threadIdx.x & 63u) == 0u) atomicMax(&sh.longest, longest);
+}
+static_assert((run_dwords(1) - kRunNone) * 4u >= 2u * PPO_MAX_K + 2u && PPO_MAX_L == 128, "entries for empty windows, and the runs of a row");
+
+// Whether an instance's rows are better worked as long as they can be.  Ranges of more than 64 entries take a set to a wave, and a
+// row by bands_level is then longer than one whose windows are looked up in a table: 75 vector instructions, for up to eight
+// sets at a time, against 47.  In the staged search whole rows have to win by a fifth (narrow ones may fit LDS), and by a half
+// where the levels are launches of their own, each of which makes the table (one search of 100 layers on 11 nodes: 83 us by
+// ranges, 91 so).
+// Ample memory, in us without ranges / with them / so: 4096 x (96, 8) of random chains with four times what they need 1067 / 1483 /
+// 1104, with twice 994 / 1467 / 1037; 1024 x (80, 7) 157 / 215 / 156; staged 300 x (100, 10) 422 / 566 / 416.
+template <int KMAX, int PART, bool RAW>
+__device__ __forceinline__ void bands_whole_rows(unsigned char* sm, const BandsTask& task, uint32_t inst) {
+    PPO_BANDS_VIEW
+    const uint32_t over16 = sh.over16, over32 = sh.over32, over64 = sh.over64;
+    uint32_t by_range = 0, by_rows = 0;   // vector instructions
+    for (int C = 1; C < k; ++C) {
+        const uint32_t here = 3u << C, count = (sh.level[C + 1] - sh.level[C]) * (uint32_t)(k - C);
+        by_range += count * (over64 & here ? 75u : over32 & here ? 38u : over16 & here ? 19u : 10u);
+        by_rows += count * 47u;
+    }
+    if (10u * by_range <= (RAW ? 10u : PART == kHead ? 15u : 12u) * by_rows || (PART == kHead && !task.query_bytes)) return;
+    __syncthreads();
+    // a range is all cuts that leave a layer to every node
+    for (uint32_t set = (uint32_t)tid; set <= all; set += (uint32_t)threads) {
+        const int c = __popc(set);
+        info[set] = c ? make_info(info_row(info[set]), whole_base(k, c), L - c) : info_row(info[set]) | kEmptySet;
+    }
+    if (tid == 0) {
+        sh.whole = 1u;
+        sh.over64 = ~0u;
+        sh.widest = (uint32_t)(k > 1 ? L - k + 2 : L);
+    }
+    bands_queries(sh, hi_s, query, L, k, hp, threads);
+    __syncthreads();
+}
+
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_codes(unsigned char* sm, const BandsTask& task, uint32_t inst) {
     PPO_BANDS_VIEW
     const uint32_t lo_bits = sh.lo_bits, hi_bits = sh.hi_bits;
@@ -683,7 +855,7 @@ __device__ __forceinline__ void bands_codes(unsigned char* sm, const BandsTask& 
     }
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_singles(unsigned char* sm, const BandsTask& task, uint32_t inst) {
     PPO_BANDS_VIEW
     // sets of one node: its segment runs to the end of the chain
@@ -703,14 +875,14 @@ __device__ __forceinline__ void bands_singles(unsigned char* sm, const BandsTask
     }
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_levels(unsigned char* sm, const BandsTask& task, uint32_t inst, int from, int to) {
 #define PPO_BANDS_LEVEL(C_)                                                                                            \
     if (C_ < KMAX && C_ >= from && C_ <= to) {                                                                          \
         {                                                                                                               \
             PPO_BANDS_VIEW                                                                                             \
-            if (in_lds) bands_level_any<C_>(sh, view.ctx(), set_order, lane, wave, waves, task.splits, run32, lds_rows); \
-            else bands_level_any<C_>(sh, view.ctx(), set_order, lane, wave, waves, task.splits, run32, slot);          \
+            if (in_lds) bands_level_any<C_>(sh, view.ctx(), set_order, lane, wave, waves, task, query, run32, lds_rows); \
+            else bands_level_any<C_>(sh, view.ctx(), set_order, lane, wave, waves, task, query, run32, slot);          \
         }                                                                                                               \
         __syncthreads();                                                                                                \
     }
@@ -729,7 +901,7 @@ __device__ __forceinline__ void bands_levels(unsigned char* sm, const BandsTask&
 }
 
 // The least entry of the full set's rows (the last k ones; their range is the cut 0 alone); kCodeInf: none.
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ uint32_t bands_best(unsigned char* sm, const BandsTask& task, uint32_t inst) {
     PPO_BANDS_VIEW
     uint32_t best = kCodeInf;
@@ -741,7 +913,7 @@ __device__ __forceinline__ uint32_t bands_best(unsigned char* sm, const BandsTas
 }
 
 // Range of the quotients with the code `best`.
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_bucket(unsigned char* sm, const BandsTask& task, uint32_t inst, uint32_t best) {
     PPO_BANDS_VIEW
     uint32_t least = ~0u, most = 0u;
@@ -769,7 +941,7 @@ __device__ __forceinline__ void bands_bucket(unsigned char* sm, const BandsTask&
 // the next position is the set of cuts that a window of that node starting in G covers (hi[j][.] does not decrease, so the
 // latest start below a cut decides).  F and G by entries of the unused set's rows; a wave per candidate, then every wave takes
 // the same step (walked by one wave, four candidates at a time, a position took 1.4 us, three times as long).
-template <int KMAX, int PART, bool WIDE>
+template <int KMAX, int PART, bool RAW, bool WIDE>
 __device__ __forceinline__ void bands_trace(unsigned char* sm, const BandsTask& task, uint32_t inst, uint32_t best,
                                              uint32_t best_bits) {
     PPO_BANDS_VIEW
@@ -842,7 +1014,7 @@ __device__ __forceinline__ void bands_trace(unsigned char* sm, const BandsTask& 
         if (WIDE) F1 = __ballot(covered(lane + 64));
     }
     if (wave != 0) return;
-    if (task.key) {
+    if (!RAW) {
         if (lane == 0) task.key[inst] = ((unsigned long long)best_bits << 32) | rank;
         return;
     }
@@ -868,10 +1040,10 @@ __device__ __forceinline__ void bands_trace(unsigned char* sm, const BandsTask& 
 }
 
 // No ordering is feasible.
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __device__ __forceinline__ void bands_infeasible(const BandsTask& task, uint32_t inst) {
     const int tid = threadIdx.x, k = task.k;
-    if (task.key) {
+    if (!RAW) {
         if (tid == 0) task.key[inst] = (unsigned long long)kInfBits << 32;
         return;
     }
@@ -880,7 +1052,7 @@ __device__ __forceinline__ void bands_infeasible(const BandsTask& task, uint32_t
     if (tid < k - 1) task.cuts[(size_t)inst * (k - 1) + tid] = -1;
 }
 
-template <int KMAX, int PART>
+template <int KMAX, int PART, bool RAW>
 __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void bands_solve_kernel(const BandsTask task) {
     extern __shared__ __align__(16) unsigned char sm[];
     BandsFirst<KMAX> sets;
@@ -896,21 +1068,29 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
     }
     for (uint32_t inst = blockIdx.x; inst < (uint32_t)task.n_inst; inst += gridDim.x) {
         if (PART == kTail) {
-            const BandsLds lds = BandsLds::make(task.L, task.k);
+            const BandsLds lds = BandsLds::make(task.L, task.k, false);
             const uint4* image = reinterpret_cast<const uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + area_dwords(task.k, task.L));
             for (uint32_t i = threadIdx.x; i < lds.run_off / 16u; i += blockDim.x) reinterpret_cast<uint4*>(sm)[i] = image[i];
         } else {
-            bands_inputs<KMAX, PART>(sm, task, inst, fresh, sets);
+            bands_inputs<KMAX, PART, RAW>(sm, task, inst, fresh, sets);
             __syncthreads();
-            bands_prefix<KMAX, PART>(sm, task, inst, fresh, sets);
+            bands_prefix<KMAX, PART, RAW>(sm, task, inst, fresh, sets);
             fresh = false;
             __syncthreads();
-            bands_windows<KMAX, PART>(sm, task, inst);
-            bands_ranges<KMAX, PART>(sm, task, inst);
-            bands_codes<KMAX, PART>(sm, task, inst);
+            bands_windows<KMAX, PART, RAW>(sm, task, inst);
+            bands_ranges<KMAX, PART, RAW>(sm, task, inst);
+            bands_codes<KMAX, PART, RAW>(sm, task, inst);
         }
         __syncthreads();
-        if (PART != kTail) bands_singles<KMAX, PART>(sm, task, inst);
+        if (reinterpret_cast<const BandsShared*>(sm)->over64) {   // (the same in all threads: nobody clears it)
+            if (PART != kTail) {
+                bands_whole_rows<KMAX, PART, RAW>(sm, task, inst);
+            } else if (reinterpret_cast<const BandsShared*>(sm)->whole) {
+                PPO_BANDS_VIEW
+                bands_queries(sh, view.hi_s, query, L, k, hp, threads);
+            }
+        }
+        if (PART != kTail) bands_singles<KMAX, PART, RAW>(sm, task, inst);
         else if (threadIdx.x == 0) {
             BandsShared& sh = *reinterpret_cast<BandsShared*>(sm);
             sh.bucket_lo = ~0u;
@@ -918,8 +1098,8 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
         }
         __syncthreads();
         if (PART == kHead) {
-            bands_levels<KMAX, PART>(sm, task, inst, 1, task.from);
-            const BandsLds lds = BandsLds::make(task.L, task.k);
+            bands_levels<KMAX, PART, RAW>(sm, task, inst, 1, task.from);
+            const BandsLds lds = BandsLds::make(task.L, task.k, false);
             uint4* image = reinterpret_cast<uint4*>(task.slots + (size_t)blockIdx.x * task.slot_dwords + area_dwords(task.k, task.L));
             for (uint32_t i = threadIdx.x; i < lds.run_off / 16u; i += blockDim.x) image[i] = reinterpret_cast<const uint4*>(sm)[i];
             __syncthreads();
@@ -927,10 +1107,10 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
         }
         uint32_t best, best_bits = kInfBits;
         for (int from = PART == kTail ? task.to : 1;; from = 1) {
-            bands_levels<KMAX, PART>(sm, task, inst, from, task.k - 1);
-            best = bands_best<KMAX, PART>(sm, task, inst);
+            bands_levels<KMAX, PART, RAW>(sm, task, inst, from, task.k - 1);
+            best = bands_best<KMAX, PART, RAW>(sm, task, inst);
             if (best >= kCodeInf) break;
-            if (KMAX > kSmallK || task.prepared) {   // its codes are exact
+            if (!RAW) {   // its codes are exact
                 const float* dec = reinterpret_cast<const float*>(task.prepared + (size_t)inst * task.y.stride + task.y.dec_off);
                 best_bits = __float_as_uint(dec[best - kCodeZero]);
                 break;
@@ -939,7 +1119,7 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
                 best_bits = 0u;
                 break;
             }
-            bands_bucket<KMAX, PART>(sm, task, inst, best);
+            bands_bucket<KMAX, PART, RAW>(sm, task, inst, best);
             __syncthreads();
             BandsShared& sh = *reinterpret_cast<BandsShared*>(sm);
             const uint32_t low = sh.bucket_lo, high = sh.bucket_hi;
@@ -953,13 +1133,13 @@ __global__ __launch_bounds__(kSubsetMaxWaves * 64, KMAX <= kSmallK ? 8 : 4) void
                 sh.hi_bits = high;
             }
             __syncthreads();
-            bands_codes<KMAX, PART>(sm, task, inst);
-            bands_singles<KMAX, PART>(sm, task, inst);
+            bands_codes<KMAX, PART, RAW>(sm, task, inst);
+            bands_singles<KMAX, PART, RAW>(sm, task, inst);
             __syncthreads();
         }
-        if (best >= kCodeInf || best_bits >= kInfBits) bands_infeasible<KMAX, PART>(task, inst);
-        else if (reinterpret_cast<const BandsShared*>(sm)->widest > 64u) bands_trace<KMAX, PART, true>(sm, task, inst, best, best_bits);
-        else bands_trace<KMAX, PART, false>(sm, task, inst, best, best_bits);
+        if (best >= kCodeInf || best_bits >= kInfBits) bands_infeasible<KMAX, PART, RAW>(task, inst);
+        else if (reinterpret_cast<const BandsShared*>(sm)->widest > 64u) bands_trace<KMAX, PART, RAW, true>(sm, task, inst, best, best_bits);
+        else bands_trace<KMAX, PART, RAW, false>(sm, task, inst, best, best_bits);
         __syncthreads();   // the next instance overwrites what the last steps read
     }
 }
@@ -973,7 +1153,7 @@ __global__ __launch_bounds__(kLevelWaves * 64, 6) void bands_level_kernel(const 
     const int L = task.L, k = task.k;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const BandsLds lds = BandsLds::make(L, k);
+    const BandsLds lds = BandsLds::make(L, k, false);
     uint32_t* slot = task.slots + (size_t)blockIdx.y * task.slot_dwords;
     const unsigned char* image = reinterpret_cast<const unsigned char*>(slot + area_dwords(k, L));
     const BandsShared& shg = *reinterpret_cast<const BandsShared*>(image);
@@ -982,7 +1162,7 @@ __global__ __launch_bounds__(kLevelWaves * 64, 6) void bands_level_kernel(const 
         const uint32_t here = 3u << C, nsets = shg.level[C + 1] - shg.level[C];
         const int s = (int)(task.splits >> (4 * C));
         const uint32_t G = shg.over64 & here ? 1u : shg.over32 & here ? 2u : shg.over16 & here ? 4u : 8u;
-        const uint32_t items = ((nsets + G - 1u) / G) << (G >= 4u ? (s >> 2) & 3 : s & 3);
+        const uint32_t items = shg.whole ? nsets << ((task.whole_splits >> (2 * C)) & 3u) : ((nsets + G - 1u) / G) << (G >= 4u ? (s >> 2) & 3 : s & 3);
         if (blockIdx.x * (uint32_t)kLevelWaves >= items) return;
     }
     // the header, the sets and the window ends, and the quotients; the rest of the image is not needed
@@ -993,18 +1173,26 @@ __global__ __launch_bounds__(kLevelWaves * 64, 6) void bands_level_kernel(const 
     for (uint32_t i = (uint32_t)tid; i < (lds.run_off - lds.q_off) / 16u; i += blockDim.x)
         reinterpret_cast<uint4*>(sm + lds.q_off)[i] = reinterpret_cast<const uint4*>(image + lds.q_off)[i];
     __syncthreads();
-    const BandsShared& sh = *reinterpret_cast<const BandsShared*>(sm);
+    BandsShared& sh = *reinterpret_cast<BandsShared*>(sm);
     uint32_t* run32 = reinterpret_cast<uint32_t*>(sm + lds.run_off) + (uint32_t)wave * run_dwords(1);
+    uint32_t* query = reinterpret_cast<uint32_t*>(sm + lds.run_off) + (uint32_t)kLevelWaves * run_dwords(1);
+    if (sh.whole) {
+        bands_queries(sh, sm + lds.hi_off, query, L, k, lds.hp, (int)blockDim.x);
+        __syncthreads();
+    }
     const BandsCtx ctx{reinterpret_cast<const uint32_t*>(sm + lds.q_off), sm + lds.hi_off,
                         reinterpret_cast<const uint32_t*>(sm + lds.info_off), nullptr, L, k, ((int)sh.widest + 1) / 2, lds.hp, lds.qp};
     bands_level_any<C>(sh, ctx, reinterpret_cast<const uint16_t*>(sm + lds.order_off), lane, (int)blockIdx.x * kLevelWaves + wave,
-                        (int)gridDim.x * kLevelWaves, task.splits, run32, slot);
+                        (int)gridDim.x * kLevelWaves, task, query, run32, slot);
 }
 
 namespace {
+constexpr size_t kLdsGrain = 1280;   // a workgroup's LDS is a multiple of it
+// (A search of few instances, or of ample memory on whole rows, wants all the waves there are: 16 x (100, 8) with three times the
+// memory they need 85 us staged with eight, 65 with sixteen.)
 // Eight waves: with four, ranges that are not narrow take rows in global memory (2048 x (96, 8) of random chains 402 us, with
 // eight 327); with sixteen the phases that one wave works alone leave more idle (4096 x (96, 8) of transformers 480 us against 360).
-int bands_waves(int k) { return k <= kSmallK ? 8 : kSubsetMaxWaves; }
+int bands_waves(int L, int k, int n_inst) { return k <= kSmallK && (k < 7 || L - k + 2 <= 64 || n_inst > 256) ? 8 : kSubsetMaxWaves; }
 
 // Parts of the nodes outside a set for `waves` waves: the least number of rows that one wave works in turn.
 int best_split(int sets, int outside, int waves) {
@@ -1023,24 +1211,32 @@ int level_cost(int k, int C, int waves) {   // rows that one wave works in turn,
     const int sets = ((int)kSetsHost.choose[k][C] + 1) / 2, s = best_split(sets, k - C, waves);
     return (((sets << s) + waves - 1) / waves) * ((k - C + (1 << s) - 1) >> s);
 }
-unsigned long long level_splits(int k, int waves) {
-    unsigned long long all = 0;
-    for (int C = 1; C < k; ++C) {
-        const int n = (int)kSetsHost.choose[k][C];
-        const int two = best_split((n + 1) / 2, k - C, waves), four = best_split((n + 3) / 4, k - C, waves);
-        all |= (unsigned long long)(two | (four << 2)) << (4 * C);
-    }
-    return all;
+void set_splits(BandsTask& task, int C, int waves) {
+    const int k = task.k, n = (int)kSetsHost.choose[k][C];
+    const int two = best_split((n + 1) / 2, k - C, waves), four = best_split((n + 3) / 4, k - C, waves);
+    task.splits |= (unsigned long long)(two | (four << 2)) << (4 * C);
+    task.whole_splits |= (uint32_t)best_split(n, k - C, waves) << (2 * C);
+}
+void set_splits(BandsTask& task, int waves) {
+    for (int C = 1; C < task.k; ++C) set_splits(task, C, waves);
 }
 
-// LDS of a workgroup that does the whole search, without rows; with rows as long as the chain; and what it is given where
+// LDS of a workgroup that does the whole search, without rows; with rows as long as a range can be; and what it is given where
 // there are row areas in global memory as well: a quarter of a compute unit's, for rows of narrow ranges.
-uint32_t fixed_lds(int L, int k) { return BandsLds::make(L, k).run_off + (uint32_t)bands_waves(k) * run_dwords(L <= 64 ? 2 : 1) * 4u; }
-size_t longest_lds(int L, int k) { return fixed_lds(L, k) + (size_t)row_dwords(k, (L + 1) / 2) * 4; }
-uint32_t whole_lds(int L, int k) {
-    const uint32_t fixed = fixed_lds(L, k), quarter = (uint32_t)kLdsBytesPerCU / 4u;
-    const size_t need = longest_lds(L, k);
+uint32_t fixed_lds(int L, int k, int waves, bool raw) { return BandsLds::make(L, k, raw).run_off + (uint32_t)waves * run_dwords(L <= 64 ? 2 : 1) * 4u + query_bytes(L, k); }
+size_t longest_lds(int L, int k, int waves, bool raw) { return fixed_lds(L, k, waves, raw) + (size_t)area_dwords(k, L) * 4; }
+uint32_t whole_lds(int L, int k, int waves, bool raw) {
+    const uint32_t fixed = fixed_lds(L, k, waves, raw), quarter = (uint32_t)kLdsBytesPerCU / 4u;
+    const size_t need = longest_lds(L, k, waves, raw);
     return need <= quarter ? (uint32_t)need : fixed > quarter ? fixed : quarter;
+}
+
+size_t level_lds(int L, int k) { return BandsLds::make(L, k, false).run_off + (size_t)kLevelWaves * run_dwords(1) * 4; }
+// Room for the table of whole rows where a compute unit holds as many workgroups with it (up to three: their registers).
+uint32_t level_query_bytes(int L, int k) {
+    auto held = [](size_t lds) { return (size_t)kLdsBytesPerCU / align_up(lds, kLdsGrain); };
+    const size_t without = held(level_lds(L, k)), with = held(level_lds(L, k) + query_bytes(L, k));
+    return with >= (without < 3 ? without : 3) ? query_bytes(L, k) : 0u;
 }
 
 // Launches of the levels from task.from to `last` of `cnt` instances whose tables are in place.
@@ -1052,14 +1248,14 @@ hipError_t launch_levels(const BandsTask& task, int cnt, int last, hipStream_t s
             static std::atomic<uint64_t> lds_allowed{0};
             hipError_t e = allow_full_lds(reinterpret_cast<const void*>(&bands_level_kernel<C>), lds_allowed);
             if (e != hipSuccess) return e;
-            const size_t lds = BandsLds::make(task.L, task.k).run_off + (size_t)kLevelWaves * run_dwords(1) * 4;
+            const size_t lds = level_lds(task.L, task.k) + task.query_bytes;
             const uint32_t cap = (768u + (uint32_t)cnt - 1u) / (uint32_t)cnt;
             // nodes outside a set in as many parts as keep the workgroups that stay resident busy
             BandsTask one = task;
-            const int waves = (int)cap * kLevelWaves, sets = (int)kSetsHost.choose[task.k][C];
-            const int two = best_split((sets + 1) / 2, task.k - C, waves), four = best_split((sets + 3) / 4, task.k - C, waves);
-            one.splits = (unsigned long long)(two | (four << 2)) << (4 * C);
-            const uint32_t most = (((uint32_t)sets << two) + (uint32_t)kLevelWaves - 1u) / (uint32_t)kLevelWaves;
+            one.splits = one.whole_splits = 0;
+            set_splits(one, C, (int)cap * kLevelWaves);
+            const int two = (int)(one.splits >> (4 * C)) & 3, whole = (int)(one.whole_splits >> (2 * C)) & 3;
+            const uint32_t most = ((kSetsHost.choose[task.k][C] << (two > whole ? two : whole)) + (uint32_t)kLevelWaves - 1u) / (uint32_t)kLevelWaves;
             hipLaunchKernelGGL((bands_level_kernel<C>), dim3(most < cap ? most : cap, cnt), dim3(kLevelWaves * 64), lds, stream, one);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
@@ -1081,31 +1277,38 @@ hipError_t launch_solve(Kernel kernel, std::atomic<uint64_t>& lds_allowed, const
 // The whole search in one launch, up to kSmallK nodes: with row areas (slot > 0 bytes each) a workgroup to each, else one
 // to an instance.
 hipError_t launch_whole(BandsTask task, size_t slot, size_t slot_count, hipStream_t stream) {
-    static std::atomic<uint64_t> allowed{0};
-    const int waves = bands_waves(task.k);
-    task.splits = level_splits(task.k, waves);
+    static std::atomic<uint64_t> allowed[2];
+    const int waves = bands_waves(task.L, task.k, task.n_inst);
+    auto launch = [&](uint32_t grid) -> hipError_t {
+        return task.prepared ? launch_solve(&bands_solve_kernel<kSmallK, kWhole, false>, allowed[0], task, grid, waves, stream)
+                             : launch_solve(&bands_solve_kernel<kSmallK, kWhole, true>, allowed[1], task, grid, waves, stream);
+    };
+    set_splits(task, waves);
     task.slot_dwords = (uint32_t)(slot / 4);
     if (slot != 0) {
         if (slot_count > (size_t)task.n_inst) slot_count = (size_t)task.n_inst;
-        task.lds_bytes = whole_lds(task.L, task.k);
-        return launch_solve(&bands_solve_kernel<kSmallK, kWhole>, allowed, task, (uint32_t)slot_count, waves, stream);
+        task.lds_bytes = whole_lds(task.L, task.k, waves, !task.prepared);
+        return launch((uint32_t)slot_count);
     }
-    task.lds_bytes = (uint32_t)longest_lds(task.L, task.k);
+    task.lds_bytes = (uint32_t)longest_lds(task.L, task.k, waves, !task.prepared);
     const uint32_t each = (uint32_t)kLdsBytesPerCU / task.lds_bytes, resident = 256u * (each < 4u ? each : 4u);
     // (no more workgroups than a few times those that stay resident: a launch may have fewer than 2^32 threads)
     const uint32_t grid = (uint32_t)task.n_inst < 16u * resident ? (uint32_t)task.n_inst : 16u * resident;
-    return launch_solve(&bands_solve_kernel<kSmallK, kWhole>, allowed, task, grid, waves, stream);
+    return launch(grid);
 }
 }  // namespace
 
-// Whether ppo_solve goes by ranges: many instances of long chains on six to eight nodes.  The launch is bound by issue then,
+// Whether ppo_solve goes by ranges: many instances of long chains on six to eight nodes, whose rows lie in global memory or leave
+// room for three workgroups to a compute unit (six nodes: up to 80 layers).  The launch is bound by issue then,
 // and rows of 20 to 60 entries in place of 65 to 128 save more than the ranges cost: in us, without and with them, 4096 x
-// (96, 8) of transformers 624 / 354, of random chains 739 / 583, 1024 x (65, 8) 218 / 143, 2048 x (70, 6) 150 / 115; but
-// 4096 x (128, 6), whose rows leave two workgroups to a compute unit, 286 / 298, 512 x (96, 8) 134 / 141 and 64 x (96, 8) 96 / 111: with few instances the longer chain of phases
-// counts.  Up to 64 layers two sets share a wave without ranges (1024 x (50, 6): 43 / 48), up to five nodes there is little
+// (96, 8) of transformers 624 / 354, of random chains 739 / 583, 1024 x (65, 8) 218 / 143, 2048 x (70, 6) 150 / 115, 4096 x (80, 6)
+// 311 / 227; but 4096 x (128, 6) 286 / 298, 512 x (96, 8) 134 / 141 and 64 x (96, 8) 96 / 111: with few instances the longer
+// chain of phases counts.  Ample memory (ranges as long as the chain, see bands_whole_rows) gains nothing and loses little: 4096 x
+// (80, 6) 295 / 287, (128, 7) 616 / 617, (96, 8) 1067 / 1104, (112, 8) 980 / 1097, with twice the memory needed 994 / 1037 of
+// (96, 8).  Up to 64 layers two sets share a wave without ranges (1024 x (50, 6): 43 / 48), up to five nodes there is little
 // to share (4096 x (128, 5): 152 / 170).  With fewer areas than keep the chip busy the instances go in turns.
 bool bands_apply(int L, int k, int n_inst, size_t slot, size_t slot_count) {
-    return L > 64 && k >= 6 && k <= kSmallK && n_inst >= 1024 && (slot != 0 ? slot_count >= 1024 : 3u * longest_lds(L, k) <= (size_t)kLdsBytesPerCU);
+    return L > 64 && k >= 6 && k <= kSmallK && n_inst >= 1024 && (slot != 0 ? slot_count >= 1024 : 3u * align_up(longest_lds(L, k, 8, true), kLdsGrain) <= (size_t)kLdsBytesPerCU);
 }
 
 hipError_t launch_bands_solve(const float* t, const float* m, const float* M, const float* B, int L, int k, int n_inst,
@@ -1130,8 +1333,8 @@ hipError_t launch_bands_solve(const float* t, const float* m, const float* M, co
 // Areas are as small as can be told beforehand: the stream-ordered allocator hands out up to 64 MiB in 60 us and more in 340 (the
 // memory goes back to the system after each call that is waited for).  64 x (100, 10) takes 60 MiB; with rows of L entries it would be 65.
 size_t bands_slot_bytes(int L, int k) {
-    if (k <= kSmallK && longest_lds(L, k) <= whole_lds(L, k)) return 0;
-    return (size_t)area_dwords(k, L) * 4 + (k <= kSmallK ? 0 : BandsLds::make(L, k).run_off);
+    if (k <= kSmallK && longest_lds(L, k, 8, false) <= whole_lds(L, k, 8, false)) return 0;
+    return (size_t)area_dwords(k, L) * 4 + (k <= kSmallK ? 0 : BandsLds::make(L, k, false).run_off);
 }
 int bands_resident(int k) { return k <= kSmallK ? 1024 : 256; }
 
@@ -1153,18 +1356,19 @@ hipError_t launch_bands_keys(const Layout& y, const void* prepared, int n_inst, 
     if (k <= kSmallK) return launch_whole(task, slot, slot_count, stream);
     static std::atomic<uint64_t> allowed[3];
     if (slot_count > (size_t)n_inst) slot_count = (size_t)n_inst;
-    const BandsLds lds = BandsLds::make(L, k);
+    const BandsLds lds = BandsLds::make(L, k, false);
     task.slot_dwords = (uint32_t)(slot / 4);
-    task.splits = level_splits(k, kSubsetMaxWaves);
+    set_splits(task, kSubsetMaxWaves);
     if (slot_count >= (size_t)bands_resident(k)) {
         task.lds_bytes = (uint32_t)kLdsBytesPerCU;   // its registers leave room for one workgroup
-        return launch_solve(&bands_solve_kernel<PPO_MAX_K, kWhole>, allowed[0], task, (uint32_t)slot_count, kSubsetMaxWaves, stream);
+        return launch_solve(&bands_solve_kernel<PPO_MAX_K, kWhole, false>, allowed[0], task, (uint32_t)slot_count, kSubsetMaxWaves, stream);
     }
     // levels of few sets stay with the tables and with the answer: a launch costs about as much as a dozen rows in turn
     int from = 1, to = k - 1;
     while (from < k && level_cost(k, from, kSubsetMaxWaves) <= 12) ++from;
     while (to > from && level_cost(k, to - 1, kSubsetMaxWaves) <= 12) --to;
-    task.lds_bytes = lds.run_off + (uint32_t)kSubsetMaxWaves * run_dwords(1) * 4u;
+    task.query_bytes = level_query_bytes(L, k);
+    task.lds_bytes = lds.run_off + (uint32_t)kSubsetMaxWaves * run_dwords(1) * 4u + query_bytes(L, k);
     for (int first = 0; first < n_inst; first += (int)slot_count) {
         const int cnt = n_inst - first < (int)slot_count ? n_inst - first : (int)slot_count;
         BandsTask p = task;
@@ -1173,13 +1377,13 @@ hipError_t launch_bands_keys(const Layout& y, const void* prepared, int n_inst, 
         p.n_inst = cnt;
         p.from = from - 1;
         p.to = to;
-        hipError_t e = launch_solve(&bands_solve_kernel<PPO_MAX_K, kHead>, allowed[1], p, (uint32_t)cnt, kSubsetMaxWaves, stream);
+        hipError_t e = launch_solve(&bands_solve_kernel<PPO_MAX_K, kHead, false>, allowed[1], p, (uint32_t)cnt, kSubsetMaxWaves, stream);
         if (e != hipSuccess) return e;
         BandsTask mid = p;
         mid.from = from;
         e = launch_levels<1>(mid, cnt, to - 1, stream);
         if (e != hipSuccess) return e;
-        e = launch_solve(&bands_solve_kernel<PPO_MAX_K, kTail>, allowed[2], p, (uint32_t)cnt, kSubsetMaxWaves, stream);
+        e = launch_solve(&bands_solve_kernel<PPO_MAX_K, kTail, false>, allowed[2], p, (uint32_t)cnt, kSubsetMaxWaves, stream);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

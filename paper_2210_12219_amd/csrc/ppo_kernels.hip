@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kEnumThreads) void enumerate_kernel(Layout y, const
 // i whose candidate max(D_{s-1}[i], q[i-1]) does not exceed beta, and e <- c_s.  Because
 // D_{s-1}[i] <= beta exactly when some feasible prefix ends at i within the bottleneck, this yields
 // the cut vector that minimises c_{k-1}, then c_{k-2}, ..., then c_1.
-// What bounds it: the latency of one wave's LDS reads, row after row.  Windows are answered from minima over runs of
+// What bounds it: the latency of one wave's LDS reads, row after row.  Long windows are answered from minima over runs of
 // 2, 4, .. candidates: 64 x (100, 10) 36 us a call with a scan of each window, 24 now; 37 x (127, 9) 36 and 22.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned char* __restrict__ ws,
@@ -319,9 +319,15 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
     // the rows of the winner's DP: one wave, lanes over the segment end; the quotient codes of its links and
     // the window starts of its nodes are staged first (loads that do not depend on each other)
     const uint64_t perm = unrank_packed(r, k);
+    const int short_windows = L <= 64 ? 14 : L <= 67 ? 20 : 12;   // see below
+    uint32_t has_long = 0;                                        // bit s: row s has a longer one, at a cut of this lane
     for (int s = 0; s < k; ++s) {
         const unsigned char* lo = lo_t + perm_at(perm, s) * (L + 1);
-        for (int e = lane; e <= L; e += 64) lo_s[s][e] = lo[e];
+        for (int e = lane; e <= L; e += 64) {
+            const int first = lo[e];
+            lo_s[s][e] = (unsigned char)first;
+            if (e <= L - (k - 1 - s) && e - (first > s ? first : s) > short_windows) has_long |= 1u << s;
+        }
         if (s == 0) continue;
         const uint16_t* q = qc + pair_index(perm_at(perm, s - 1), perm_at(perm, s), k) * L;
         for (int i = lane; i < L; i += 64) q_s[s][i] = q[i];
@@ -333,22 +339,24 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
     for (int s = 1; s < k; ++s) {
         const uint16_t* q = q_s[s];
         const unsigned char* lo = lo_s[s];
-        int longest = 0;   // of the windows that this lane answers
-        for (int e = lane; e <= L; e += 64)
-            if (e >= s + 1 && e <= L - (k - 1 - s)) {
-                const int len = e - (lo[e] > s ? lo[e] : s);
-                longest = len > longest ? len : longest;
-            }
-        if (!__any(longest > 8)) {
-            // short windows: one candidate after the other (300 x (20, 10): 13 us a call, by runs 15)
+        // Short windows: their candidates two at a time, up to a length at which runs take the same.  That is 14 candidates where
+        // the cuts fit the lanes, 12 where they go twice, and 20 where all but a few of them fit (runs go twice there, and so does
+        // the scan, but for its last cuts alone).  64 instances on 10 nodes, windows of 9 / 12 / 16 / 20 / 24, in us by scan and by
+        // runs: 40 layers 14.4 15.1 16.6 18.0 19.4 and 15.8 15.9 16.7 16.7 16.7, 65 layers 17.0 17.7 19.2 20.6 22.1 and 20.7 20.7 22.1 22.0
+        // 22.0, 100 layers (from 12 on) 21.3 23.6 26.0 28.3 and 21.9 23.2 23.2 23.1.  Whether a row has a longer one is told while the
+        // tables are staged, not row by row, and a single candidate at a time took 15 % more: what binds is the one wave's latency.
+        if (!__any((has_long >> s) & 1u)) {
             for (int e = lane; e <= L; e += 64) {
                 uint32_t acc = kCodeInf;
                 if (e >= s + 1 && e <= L - (k - 1 - s)) {
                     const int first = lo[e] > s ? lo[e] : s;
-                    for (int i = first; i < e; ++i) {
-                        const uint32_t d = rows[s - 1][i], g = q[i - 1];
-                        const uint32_t c = d > g ? d : g;
-                        acc = c < acc ? c : acc;
+                    const uint16_t *row = rows[s - 1] + first, *link = q + first - 1;
+                    for (int left = e - first; left > 0; left -= 2, row += 2, link += 2) {   // two at a time (the last one twice)
+                        const int other = left > 1 ? 1 : 0;
+                        const uint32_t d0 = row[0], g0 = link[0], d1 = row[other], g1 = link[other];
+                        const uint32_t c0 = d0 > g0 ? d0 : g0, c1 = d1 > g1 ? d1 : g1;
+                        acc = c0 < acc ? c0 : acc;
+                        acc = c1 < acc ? c1 : acc;
                     }
                 }
                 rows[s][e] = (uint16_t)acc;
@@ -356,6 +364,12 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
             __syncthreads();
             continue;
         }
+        int longest = 0;   // of the windows that this lane answers
+        for (int e = lane; e <= L; e += 64)
+            if (e >= s + 1 && e <= L - (k - 1 - s)) {
+                const int len = e - (lo[e] > s ? lo[e] : s);
+                longest = len > longest ? len : longest;
+            }
         // minima over runs of candidates (runs that pass the chain's end stop there), then two runs cover a window
         for (int i = lane; i < L; i += 64) {
             uint32_t c = kCodeInf;

@@ -1,5 +1,5 @@
-"""The final stage (ppo_finalize) where its windows change form: up to 8 candidates one after the other, longer ones by minima
-over runs.  Equal layers and nodes of a given number of layers make every window that long."""
+"""The final stage (ppo_finalize) where its windows change form: up to 14 candidates (20 or 12 on longer chains) two at a time,
+longer ones by minima over runs.  Equal layers and nodes of a given number of layers make every window that long."""
 import numpy as np
 import pytest
 
@@ -10,7 +10,8 @@ from paper_2210_12219_amd import workloads as W
 
 
 @pytest.mark.parametrize("L,k,longest", [(30, 5, 7), (30, 5, 8), (30, 5, 9), (64, 9, 8), (65, 9, 16), (128, 12, 17), (128, 2, 127), (128, 3, 64),
-                                         (12, 12, 8), (16, 2, 9)])
+                                         (12, 12, 8), (16, 2, 9), (64, 9, 14), (64, 9, 15), (65, 9, 20), (67, 9, 21), (68, 9, 12), (68, 9, 13),
+                                         (128, 12, 12), (128, 12, 13)])
 def test_windows(L, k, longest):
     import torch
     from paper_2210_12219_amd import binding as ppo

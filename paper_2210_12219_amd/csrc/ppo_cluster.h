@@ -25,8 +25,11 @@ __host__ __device__ constexpr int cluster_sets_per_wave(int mode) { return mode 
 __host__ __device__ constexpr int cluster_run_pitch(int mode) { return mode == kClWide ? 80 : 64; }
 __host__ __device__ constexpr int cluster_run_levels(int mode) { return mode == kClTwoSets ? 6 : 7; }
 __host__ __device__ constexpr int cluster_run_dwords(int mode) {
-    return cluster_run_levels(mode) * cluster_run_pitch(mode) + (mode == kClTwoSets ? 64 : 4);
+    return cluster_run_levels(mode) * cluster_run_pitch(mode) + (mode == kClTwoSets ? 36 : 4);
 }
+// A search on fewer nodes and cuts: four to eight sets to a wave on up to 31 layers, which have runs of up to 16 entries and
+// the +inf in the row of the next longer ones, up to 56 dwords on; else two sets.
+__host__ __device__ constexpr int cluster_part_none(int L) { return (L <= 31 ? 5 : 6) * 64; }
 
 struct ClusterLayout {
     int L, n, npairs, nq, rs;                       // rs: entries per row of A: 0..L-1 (entry L is never finite

@@ -385,7 +385,7 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
         uint32_t* choose = reinterpret_cast<uint32_t*>(cl_smem + small.run_off);
         for (int i = tid; i < (int)(kClBinomialBytes / 4u); i += threads) choose[i] = kClBinomials.c[0][i];
         uint32_t* run = reinterpret_cast<uint32_t*>(cl_smem + small.run_off + kClBinomialBytes) + wave * cluster_run_dwords(kClTwoSets);
-        run[6 * 64 + lane] = kClInf | (kClInf << 16);   // empty windows
+        if (cluster_part_none(part.L) + lane < cluster_run_dwords(kClTwoSets)) run[cluster_part_none(part.L) + lane] = kClInf | (kClInf << 16);   // empty windows
         __syncthreads();
         const uint32_t* windows = reinterpret_cast<const uint32_t*>(cl_smem + small.query_off);
         const uint32_t index = blockIdx.x * (uint32_t)waves + (uint32_t)wave, total = gridDim.x * (uint32_t)waves;
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
             q16[r * y.rs + e] = (uint16_t)((a != b && e >= 1 && e <= L - 1) ? q[e - 1] : kClInf);
     }
     for (int i = nrows * y.rs + tid; i < (int)(y.q_image_bytes() / 2); i += kClPreThreads) q16[i] = (uint16_t)kClInf;   // the padding
-    const uint32_t none = (uint32_t)(cluster_run_levels(mode) * pitch) * 4u;
+    const uint32_t none = (uint32_t)(cluster_reduced(whole, base) ? cluster_part_none(L) : cluster_run_levels(mode) * pitch) * 4u;
     int top_run = 0;
     for (int i = tid; i < n * per_node; i += kClPreThreads) {
         const int j = i / per_node, e = i - j * per_node;

@@ -263,8 +263,13 @@ static_assert(kFewRunRow / 2 >= 64 + (1 << (kFewRunLevels - 3)), "the longest ru
 
 // of a wave that works several nodes at a time: the least values at the start of the chain, and the nodes outside the set
 constexpr int kFewPackDwords = kFewMaxN + kFewMaxN / 4;
+// Several nodes at a time are for rows of up to 64 entries only, so what that needs lies where longer rows have their windows
+// (10 x (100 layers, 40 nodes, 4 segments): two workgroups fit a compute unit with both, three so, and the level of three nodes
+// takes 115 us or 69).
 static size_t few_level_lds(const FewLayout& y) {
-    return ((size_t)y.n * y.rs + (size_t)kFewLevelWaves * (kFewRunLevels * kFewRunRow + kFewPackDwords) + 4) * 4;
+    const size_t runs = (size_t)kFewLevelWaves * kFewRunLevels * kFewRunRow + 4, pack = (size_t)kFewLevelWaves * kFewPackDwords;
+    const size_t one = (size_t)y.n * y.rs + runs, several = (size_t)y.n * (y.rs < 64 ? y.rs : 64) + runs + pack;
+    return (one > several ? one : several) * 4;
 }
 
 // the value of the next lane; `last` in lane 63
@@ -296,7 +301,7 @@ __global__ __launch_bounds__(kFewLevelWaves * 64) void few_level_kernel(FewLayou
     // short rows: as many nodes at a time as have room beside each other, 8, 16 or 32 lanes each (one cluster of 50 nodes and
     // 5 segments, 12 to 17 of 100 layers left: the level of three nodes 120 us with a node at a time, 34 with four)
     const int shift = rd <= 8 ? 3 : rd <= 16 ? 4 : rd <= 32 ? 5 : 6, lanes = 1 << shift, hl = lane & (lanes - 1);
-    least_s[lane] = kInfBits;
+    if (shift < 6) least_s[lane] = kInfBits;
     if (tid == 0) longest_s = 1;
     __syncthreads();
     {

@@ -759,13 +759,16 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
 }
 
 // Whether a search is confined to the nodes and cuts that can matter (ppo_cluster_bound.hip).  That costs about 45 us before
-// the levels and, where little can be left out, saves less: paper-shaped clusters of 16 MB devices keep all their nodes.
-// Measured in us, without and with it: one cluster of 16 such nodes 239 / 234, 16 of 13 nodes 236 / 224, 128 of 11 nodes 277 /
-// 229, but 128 of 10 nodes 177 / 185, 16 of 12 nodes 162 / 187, one of 14 nodes 176 / 193.  (Mixed capacities, 100 layers: one of
-// 20 nodes 2040 / 135, one of 16 nodes 309 / 178, 128 of 11 nodes 418 / 218.)  With fewer segments allowed than nodes the upper
+// the levels, 10 to 15 where nine nodes do not hold the chain, and may leave little out: paper-shaped clusters of 16 MB devices
+// keep all their nodes.  Measured in us, without and with it: one cluster of 16 such nodes 239 / 234, 16 of 13 nodes 236 / 224, 128
+// of 11 nodes 277 / 229, but 128 of 10 nodes 177 / 185, 16 of 12 nodes 162 / 187, one of 14 nodes 176 / 193.  Mixed
+// capacities, 100 layers: one of 20 nodes 2040 / 120 to 250, one of 16 nodes 275 to 309 / 95 to 178, 128 of 11 nodes 418 / 218; 20 layers: 64 of
+// 13 nodes 390 / 238, but 132 of 12 nodes 447 / 500 and 288 of 11 nodes 455 / 541 (26 layers: 474 / 250 and 478 / 367).  Nothing to
+// leave out: short of memory on the nine nodes, 16 nodes and 100 layers 252 / 271, 288 of 11 nodes 795 / 827; one transfer size
+// and bandwidth, 16 nodes and 50 layers 223 / 262, 64 of 13 nodes 463 / 500.  With fewer segments allowed than nodes the upper
 // levels are not searched, and those that are start from the nodes' number, which the host would not know.
-static bool cluster_confined(int n, int n_inst, int pmax) {
-    return pmax == n && (n >= 16 || (n >= 11 && ((unsigned long long)n_inst * (unsigned long long)n << (n - 1)) >= 800000ull));
+static bool cluster_confined(int L, int n, int n_inst, int pmax) {
+    return pmax == n && (n >= 16 || (n >= (L >= 24 ? 11 : 13) && ((unsigned long long)n_inst * (unsigned long long)n << (n - 1)) >= 800000ull));
 }
 
 hipError_t launch_cluster_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
@@ -773,7 +776,7 @@ hipError_t launch_cluster_tables(const float* t, const float* m, const float* M,
     const ClusterLayout y = ClusterLayout::make(L, n);
     unsigned char* w = static_cast<unsigned char*>(ws);
     hipError_t e;
-    if (cluster_confined(n, n_inst, pmax)) {
+    if (cluster_confined(L, n, n_inst, pmax)) {
         e = launch_cluster_reduce(t, m, M, B, y, n_inst, w, stream);
     } else {
         hipLaunchKernelGGL(cluster_tables_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, t, m, M, B, y, w);

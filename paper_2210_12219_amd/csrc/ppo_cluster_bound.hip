@@ -38,6 +38,7 @@ __device__ __forceinline__ uint32_t b_max(uint32_t a, uint32_t b) {
 constexpr int kBoundNodes = 9, kBoundThreads = 1024, kBoundWaves = kBoundThreads / 64;
 constexpr int kBoundEntries = 32, kBoundRow = kBoundEntries / 2;   // the start of the chain and 31 cuts; dwords of a row
 constexpr uint32_t kBoundInf = kInfBits >> 16;                     // codes: the upper half of the pattern, rounded up
+constexpr int kMostCuts = 62;                                      // that the walks take: a bit each, and the chain's start
 constexpr int kBoundRuns = 5;                                      // minima over runs of 1 .. 16 entries
 constexpr int kBoundPad = 52;                                      // dwords of +inf, then of 0, after the runs of a wave
 constexpr int kBoundRunDwords = kBoundRuns * 64 + 2 * kBoundPad;
@@ -53,6 +54,7 @@ struct BoundShared {
     float t[PPO_MAX_L], m[PPO_MAX_L], M[PPO_CLUSTER_FEW_MAX_N], B[PPO_CLUSTER_FEW_MAX_N * PPO_CLUSTER_FEW_MAX_N];
     unsigned long long cuts[2];                    // bit e: the cut e is one of the 31
     uint32_t best;
+    int least[2];                                  // cuts with the least transfer size of all
     int level[kBoundNodes + 2];
     unsigned char node[16], pos[kBoundEntries];    // cluster nodes and cuts of the small search; pos[0] = 0
     uint16_t order[1 << kBoundNodes], place[1 << kBoundNodes];
@@ -215,14 +217,42 @@ __global__ __launch_bounds__(kBoundThreads) void cluster_bound_kernel(const floa
     } else if (wave < 4) {
         // the cuts: after the layers with the smallest t (ties by index)
         const int i = (wave - 2) * 64 + lane;   // the cut i + 1
-        int rank = 0;
+        int rank = 0, smaller = 0;
         const float x = i < L - 1 ? s.t[i] : 0.0f;
-        for (int u = 0; u < L - 1; ++u) rank += (s.t[u] < x || (s.t[u] == x && u < i)) ? 1 : 0;
-        const unsigned long long some = __ballot(i < L - 1 && rank < kBoundEntries - 1);
-        if (lane == 0) s.cuts[wave - 2] = some;
+        for (int u = 0; u < L - 1; ++u) {
+            smaller += s.t[u] < x ? 1 : 0;
+            rank += (s.t[u] < x || (s.t[u] == x && u < i)) ? 1 : 0;
+        }
+        const unsigned long long some = __ballot(i < L - 1 && rank < kBoundEntries - 1), least = __ballot(i < L - 1 && smaller == 0);
+        if (lane == 0) {
+            s.cuts[wave - 2] = some;
+            s.least[wave - 2] = __popcll(least);
+        }
     }
     __syncthreads();
-    // as cuts (bit e), and in increasing order
+    // What cannot lead to a confined search ends here: nine nodes that do not hold the chain (as many of the largest as there
+    // may be segments), or, where a link is needed, more cuts with the least transfer size than the walks take.  One cluster of 16
+    // nodes and 100 layers whose nine best nodes are short of memory, in us: 252 without a bound, 293 with all of this, 271 so.
+    {
+        const int j = lane < kBoundNodes ? lane : 0, most = pmax < kBoundNodes ? pmax : kBoundNodes;
+        const float cap = s.M[s.node[j]];
+        int rank = 0;   // among the nine
+        if (most < kBoundNodes)
+#pragma unroll
+            for (int b = 0; b < kBoundNodes; ++b) {
+                const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cap), b));
+                rank += (other > cap || (other == cap && b < j)) ? 1 : 0;
+            }
+        double held = lane < kBoundNodes && rank < most ? (double)cap : 0.0;
+        for (int off = 8; off >= 1; off >>= 1) held += __shfl_xor(held, off, 64);
+        const bool alone = __ballot(lane < n && (double)s.M[lane < n ? lane : 0] >= s.P[L]) != 0ull;
+        // (lanes 0 .. 15 have the sum; what is in doubt by a rounding is gone through)
+        if (__ballot(lane == 0 && held < s.P[L]) != 0ull || (!alone && s.least[0] + s.least[1] > kMostCuts)) {
+            if (tid == 0) reinterpret_cast<uint32_t*>(out + (size_t)inst * stride)[blockIdx.x] = kInfBits;
+            return;
+        }
+    }
+    // the cuts as bits (bit e), and in increasing order
     const unsigned long long c0 = s.cuts[0] << 1, c1 = s.cuts[1] << 1 | s.cuts[0] >> 63;
     const int count = __popcll(c0) + __popcll(c1);
     if (tid < 128 && tid >= 1 && ((tid < 64 ? c0 >> tid : c1 >> (tid - 64)) & 1ull)) s.pos[cuts_upto(c0, c1, tid)] = (unsigned char)tid;
@@ -357,7 +387,7 @@ __device__ __forceinline__ bool confine(ConfineShared<MAXN>& s, const float* __r
     }
     const unsigned long long c0 = s.cuts[0], c1 = s.cuts[1];
     const int count = __popcll(c0) + __popcll(c1);
-    if (bound >= kInfBits || count > 62) return false;
+    if (bound >= kInfBits || count > kMostCuts) return false;
     {
         // positions: 0 the start of the chain, then the cuts
         if (tid >= 1 && tid < L && ((tid < 64 ? c0 >> tid : c1 >> (tid - 64)) & 1ull)) s.pos[cuts_upto(c0, c1, tid)] = (unsigned char)tid;
@@ -514,10 +544,12 @@ __global__ __launch_bounds__(kClPreThreads) void few_confine_kernel(const float*
     FewConfined* mine = reinterpret_cast<FewConfined*>(reinterpret_cast<unsigned char*>(out) + (size_t)blockIdx.x * stride);
     const uint32_t u0 = mine->bounds[0], u1 = mine->bounds[1];
     unsigned long long c0 = 0ull, c1 = 0ull, left = 0ull;
-    const bool in = confine(s, t, m, M, B, L, n, pmax, (int)blockIdx.x, u0 < u1 ? u0 : u1, c0, c1, left);
+    const uint32_t bound = u0 < u1 ? u0 : u1;
+    const bool in = bound < kInfBits && confine(s, t, m, M, B, L, n, pmax, (int)blockIdx.x, bound, c0, c1, left);
+    __syncthreads();   // (the bounds lie where the nodes go)
     if (threadIdx.x == 0) {
         mine->in = in ? 1u : 0u;
-        mine->bound = u0 < u1 ? u0 : u1;
+        mine->bound = bound;
         mine->nodes = left;
         mine->cuts[0] = c0;
         mine->cuts[1] = c1;

@@ -850,14 +850,17 @@ __global__ __launch_bounds__(kFewScanWaves * 64) void few_scan_kernel(FewLayout 
 // Host side
 // ---------------------------------------------------------------------------------------------
 // Whether the search is confined to the nodes and cuts that can matter (ppo_cluster_bound.hip), and to values within the bound
-// found there.  That costs about 70 us (the bound 27, the walks 25 to 45).  Measured in us, without and with it: one cluster of
-// 50 nodes, 100 layers and 5 segments 480 / 259, of 40 nodes 273 / 204, 8 of 64 nodes, 30 layers and 4 segments 516 / 321, 4
-// paper-shaped ones of 50 nodes and 4 segments 945 / 206; but 8 of 21 nodes, 40 layers and 5 segments (230 thousand rows)
-// 200 / 214 and one of 60 layers, 30 nodes and 5 segments (120 thousand) 138 / 162.
+// found there.  That costs about 70 us (the bound 27, the walks 25 to 45), 15 to 20 where the nodes of the bound do not hold the
+// chain.  Measured in us, without and with it, nodes just large enough: one cluster of 50 nodes, 100 layers and 5 segments 480 / 259,
+// of 40 nodes 273 / 204, 8 of 64 nodes, 30 layers and 4 segments 516 / 321, 3 of 30 nodes, 50 layers and 5 segments 255 / 209, 4
+// paper-shaped ones of 50 nodes and 4 segments 945 / 206.  Of fewer nodes most stay: 11 of 21 nodes, 30 layers and 5 segments (320
+// thousand rows) 209 / 245, 57 of 14 nodes, 50 layers and 5 segments 234 / 231, but 44 of 21 nodes 650 / 619.  Nothing to leave out:
+// one of 50 nodes and 100 layers that does not fit 371 / 385, 4 of 40 nodes and 50 layers with one transfer size and bandwidth
+// 1122 / 1132, one of them 350 / 452 (the ties are scanned by fewer workgroups, see few_grid).
 static bool few_confined(int n, int pmax, int n_inst) {
     unsigned long long rows = 0;
     for (int c = 1; c < pmax; ++c) rows += kFewBinomialsHost.c[n][c] * (unsigned long long)c;
-    return n >= 9 && pmax >= 2 && rows * (unsigned long long)n_inst >= 300000ull;
+    return n >= 9 && pmax >= 2 && rows * (unsigned long long)n_inst >= (n >= 30 ? 300000ull : 1200000ull);
 }
 hipError_t launch_cluster_few_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
                                      int pmax, int n_inst, void* ws, void* rows, hipStream_t stream) {
@@ -916,7 +919,9 @@ static hipError_t few_launch_levels(int n_inst, hipStream_t stream, const FewLay
 }
 
 static uint32_t few_grid(unsigned long long sets, int waves_per_block) {
-    // enough workgroups to fill the chip several times over, never more than there are sets
+    // enough workgroups to fill the chip, never more than there are sets (with four times as many, 12 clusters of 30 nodes, 100
+    // layers and 5 segments that leave most sets without a mark took 519 us in place of 279; where every link ties and no
+    // set is without one, one cluster of 40 nodes took 404 in place of 535)
     unsigned long long blocks = (sets + (unsigned long long)waves_per_block - 1ull) / (unsigned long long)waves_per_block;
     const unsigned long long cap = 256ull * 8ull;
     if (blocks > cap) blocks = cap;

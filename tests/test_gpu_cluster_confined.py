@@ -50,7 +50,7 @@ def test_cuts_left(cheap):
     check(w, oracle=1)
 
 
-@pytest.mark.parametrize("n,L", [(11, 2), (11, 64), (12, 128), (13, 63), (14, 127), (15, 17)])
+@pytest.mark.parametrize("n,L", [(13, 13), (11, 24), (11, 64), (12, 128), (13, 63), (14, 127), (15, 17)])
 def test_ties_zeros_and_capacities(n, L):
     w = W.random_instances(950 + n, batch(n), L, n, capacity_factor=1.5, quantised=L % 2 == 0)
     rng = np.random.default_rng(n)
@@ -71,7 +71,7 @@ def test_paper_shaped_clusters():
 def few_batch(n, segments):
     """instances that ppo_solve_cluster_few searches on what can matter"""
     from math import comb
-    return -(-300000 // sum(comb(n, c) * c for c in range(1, segments)))
+    return -(-(300000 if n >= 30 else 1200000) // sum(comb(n, c) * c for c in range(1, segments)))
 
 
 @pytest.mark.parametrize("n,L,segments", [(12, 100, 6), (14, 33, 5), (30, 100, 5), (30, 17, 5), (50, 64, 4), (50, 128, 4), (64, 40, 4),

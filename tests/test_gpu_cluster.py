@@ -199,10 +199,10 @@ def embed_with_decoys(w, i, n_big, rng):
 
 
 def test_cluster_of_twenty_exact_through_decoy_nodes(ppo):
-    """n = 20 with every segment count allowed (a million node sets, 32-bit row numbers, every level of the
-    DP), bit for bit: a cluster of 11 to 13 real nodes that the oracle solves, plus nodes too small for any
-    layer, which change nothing (the oracle's own pins show that).  Expected beta, segment count, cuts are
-    the small cluster's; the node sequence is the small one's through the embedding."""
+    """n = 20 with every segment count allowed, bit for bit: a cluster of 11 to 13 real nodes that the oracle
+    solves, plus nodes too small for any layer, which change nothing (the oracle's own pins show that).
+    Expected beta, segment count, cuts are the small cluster's; the node sequence is the small one's through
+    the embedding.  (The nodes that hold no layer can be left out by the search; the next test is searched whole.)"""
     import torch
     rng = np.random.default_rng(2020)
     cases = [(W.random_instances(311, 2, 100, 12, capacity_factor=1.7), "L=100, eight segments or so"),
@@ -230,6 +230,32 @@ def test_cluster_of_twenty_exact_through_decoy_nodes(ppo):
             assert np.array_equal(got[3][i], want_order), (what, i, got[3][i], want_order)
             assert np.array_equal(got[2][i], want_cuts), (what, i)
         assert max(int(x) for x in got[1]) >= 2
+
+
+@pytest.mark.parametrize("n0,L,cf", [(12, 100, 1.7), (11, 128, 2.5), (13, 70, 1.4)])
+def test_cluster_of_twenty_searched_whole(ppo, n0, L, cf):
+    """The same with a million node sets, 32-bit row numbers and every level of the DP for sure: transfer sizes and
+    bandwidths differ by less than a part in a thousand, so that any bound within 2^-8 of the optimum lets all of the
+    69 to 127 cuts pass, which is more than a search can be confined to."""
+    rng = np.random.default_rng(n0 + L)
+    w = W.random_instances(400 + L, 2, L, n0, capacity_factor=cf)
+    poss, Ms, Bs = [], [], []
+    w.t[...] = 1.503 + 1e-3 * rng.random(w.t.shape)
+    for i in range(w.n_inst):
+        pos, M, B = embed_with_decoys(w, i, 20, rng)
+        up = np.triu(1.0 + 1e-4 * rng.random((20, 20)), 1).astype(np.float32)
+        B = up + up.T
+        w.B[i] = B[np.ix_(pos, pos)]
+        poss.append(pos); Ms.append(M); Bs.append(B)
+    big = W.Workload(w.name + "+decoys", L, 20, w.n_inst, w.seed, w.t, w.m, np.stack(Ms), np.stack(Bs))
+    print(f"cluster n=20 whole, {n0} real nodes, L={L}", flush=True)
+    got = solve(ppo, big)
+    for i in range(w.n_inst):
+        beta, p, cuts, order = CO.subset_dp(w.t[i], w.m[i], w.M[i], w.B[i])
+        assert p >= 3
+        assert bits(got[0][i]) == bits(beta) and got[1][i] == p, (i, got[0][i], beta, got[1][i], p)
+        assert list(got[3][i]) == list(poss[i][order[:p]]) + [-1] * (20 - p)
+        assert list(got[2][i]) == list(cuts[:p - 1]) + [-1] * (20 - p)
 
 
 def test_cluster_seventeen_and_eighteen_against_the_oracle(ppo):

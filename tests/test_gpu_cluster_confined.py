@@ -65,7 +65,7 @@ def test_paper_shaped_clusters():
     """one capacity, many ties: nine nodes may be too few to hold the chain, and no node is left out"""
     for capacity in (10.0, 16.0, 64.0, 200.0):
         check(W.cluster_geometric(12, capacity, n_inst=batch(12), seed=int(capacity)), oracle=1)
-    check(W.cluster_mixed(16, L=100, n_inst=2, seed=3))
+    check(W.cluster_mixed(16, L=100, n_inst=2, seed=3), oracle=1)   # from 16 nodes on one instance is confined as well
 
 
 def few_batch(n, segments):

@@ -133,8 +133,8 @@ def test_beyond_twenty_nodes_against_the_oracle(ppo):
 def test_fifty_nodes_five_segments(ppo):
     """The paper's largest cluster with more segments than the oracle can walk sequences for: clusters of 50 and 64
     in which 8 nodes matter and the rest are too small for any layer.  The answer is the small cluster's (oracle:
-    subset route), carried to the places of its nodes; every set of up to five or six of the 50 goes through the
-    kernels all the same."""
+    subset route), carried to the places of its nodes.  (Nodes that hold no layer can be left out by the search; the next
+    test is searched whole.)"""
     rng = np.random.default_rng(9)
     for n, L, pmax, seed in ((50, 100, 5, 0), (50, 60, 6, 1), (64, 100, 4, 2)):
         small = W.cluster_mixed(8, L=L, n_inst=2, seed=60 + seed, capacity_factor=0.3)
@@ -159,6 +159,29 @@ def test_fifty_nodes_five_segments(ppo):
             q = int(rng.integers(1, 6))
             seq = rng.permutation(50)[:q]
             assert bits(CO.sequence_beta(t, m, M, B, seq)) >= bits(got[0][i])
+
+
+@pytest.mark.parametrize("n,L,pmax", [(50, 100, 5), (50, 70, 6), (64, 128, 4)])
+def test_fifty_nodes_searched_whole(ppo, n, L, pmax):
+    """Every set of up to five or six of the 50 nodes goes through the kernels: transfer sizes and bandwidths differ by less
+    than a part in a thousand, so that any bound within 2^-8 of the optimum lets all cuts pass, more than a search can be
+    confined to."""
+    rng = np.random.default_rng(n + L)
+    small = W.cluster_mixed(8, L=L, n_inst=2, seed=80 + L, capacity_factor=0.3)
+    small.t[...] = 1.503 + 1e-3 * rng.random(small.t.shape)
+    big, places = with_decoys(small, n, rng)
+    for i in range(big.n_inst):
+        up = np.triu(1.0 + 1e-4 * rng.random((n, n)), 1).astype(np.float32)
+        big.B[i] = up + up.T
+        small.B[i] = big.B[i][np.ix_(places[i], places[i])]
+    print(f"few whole n={n} L={L} pmax={pmax}", flush=True)
+    got = solve_few(ppo, big, pmax)
+    for i in range(big.n_inst):
+        beta, p, cuts, order = CO.subset_dp(small.t[i], big.m[i], small.M[i], small.B[i], pmax)
+        assert p >= 2
+        assert bits(got[0][i]) == bits(beta) and got[1][i] == p, (n, i, got[0][i], beta, got[1][i], p)
+        assert list(got[3][i]) == [int(places[i][j]) for j in order[:p]] + [-1] * (n - p)
+        assert list(got[2][i]) == list(cuts[:p - 1]) + [-1] * (n - p)
 
 
 def test_workspace_size_does_not_matter_and_bad_shapes_are_refused(ppo):

@@ -16,7 +16,8 @@
 // the rows of R matter only for e in [max(least[R], k - |R|), min(most[All \ R], L - |R|)].  Below that range every entry is
 // +inf; above it no prefix arrives, so windows may stop at its end.  Capacities of 1.25 of the model leave 20 to 25 entries of
 // 96, of 1.3 10 to 45 of 50 to 127.  A row is held from an even entry at or before its range, and a wave takes eight, four,
-// two or one sets, as many as the widest ranges of the level allow (16, 32, 64 or 128 entries).
+// two or one sets, as many as the widest ranges of the level allow (16, 32, 64 or 128 entries).  With ample memory a range is
+// nearly the chain, and there is nothing to gain: see bands_whole_rows.
 //
 // Values.  The rows hold 16-bit codes that do not decrease with the quotient: kCodeZero for 0, then kCodeZero + 1 +
 // ((bits - lo) >> shift) with [lo, hi] the range of the quotients' binary32 patterns and the least shift that fits, and
@@ -29,8 +30,9 @@
 // of them in the levels (75 vector instructions for four rows of 25 entries, where a row of 96 took 47 by itself); the rest is
 // what every wave of a workgroup works out for itself in each phase, and it grows with the waves.  The phases that one wave
 // or a few work alone (sums, windows, answer) overlap with those of the other workgroups of the compute unit.
-// Measured, before and now: 4096 x (96, 8) of transformers 624 / 354 us, of random chains 739 / 583, 1024 x (65, 8) 218 / 143;
-// staged (tables and final stage included) 64 x (100, 10) 260 / 197, 1024 x (50, 6) 180 / 125, 300 x (20, 10) 313 / 159.
+// Measured, before and now: 4096 x (96, 8) of transformers 624 / 354 us, of random chains 739 / 583, 1024 x (65, 8) 218 / 143,
+// 4096 x (80, 6) 311 / 227; staged (tables and final stage included) 64 x (100, 10) 260 / 197, 1024 x (50, 6) 180 / 125, 300 x
+// (20, 10) 313 / 159.  (Memory of 1.2 to 1.3 times what the chain needs; of twice and four times: bands_whole_rows.)
 #include "ppo_sets.h"
 
 namespace ppo {

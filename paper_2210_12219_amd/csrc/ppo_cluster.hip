@@ -260,7 +260,7 @@ __device__ __forceinline__ uint32_t cluster_next_set(uint32_t set, uint32_t& fir
 
 // The same for an instance on fewer nodes and cuts: G sets to a wave, 64 / G lanes of two entries each, with every set's
 // values in its lanes (C <= n - 1).  The parts of a wave take a run of consecutive sets each.  15 nodes of a paper-shaped
-// cluster keep 11 to 18 of their 50 layers: four or eight sets to a wave.
+// cluster keep 11 to 18 of their 50 layers: eight sets to a wave up to 15 layers, six up to 19 (then five up to 23, four up to 31).
 template <int C, int G>
 __device__ __forceinline__ void cluster_level_parts(const ClusterLayout y, const uint32_t* query, uint32_t* run32, uint32_t* A32,
                                                     const uint32_t (*choose)[PPO_CLUSTER_MAX_N + 1], bool more, int run_top, int lane,
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
         }
         query[i] = o1 | (o2 << 16);
     }
-    // (an atomic by every thread made 73 us of the 65 that a staged search of 1024 instances of (12, 5) takes)
+    // (one atomic a wave: an atomic by every thread made the table's kernel 8 us longer for 1024 instances of 12 layers)
     for (int off = 32; off >= 1; off >>= 1) {
         const int o = __shfl_xor(top_run, off, 64);
         top_run = o > top_run ? o : top_run;

@@ -320,13 +320,13 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
     // the window starts of its nodes are staged first (loads that do not depend on each other)
     const uint64_t perm = unrank_packed(r, k);
     const int short_windows = L <= 64 ? 14 : L <= 67 ? 20 : 12;   // see below
-    uint32_t has_long = 0;                                        // bit s: row s has a longer one, at a cut of this lane
+    uint32_t has_long = 0;                                        // bit s: row s may have a longer one, at a cut of this lane
     for (int s = 0; s < k; ++s) {
         const unsigned char* lo = lo_t + perm_at(perm, s) * (L + 1);
         for (int e = lane; e <= L; e += 64) {
             const int first = lo[e];
             lo_s[s][e] = (unsigned char)first;
-            if (e <= L - (k - 1 - s) && e - (first > s ? first : s) > short_windows) has_long |= 1u << s;
+            has_long |= e - first > short_windows ? 1u << s : 0u;
         }
         if (s == 0) continue;
         const uint16_t* q = qc + pair_index(perm_at(perm, s - 1), perm_at(perm, s), k) * L;
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64) void traceback_kernel(Layout y, const unsigned 
         // the cuts fit the lanes, 12 where they go twice, and 20 where all but a few of them fit (runs go twice there, and so does
         // the scan, but for its last cuts alone).  64 instances on 10 nodes, windows of 9 / 12 / 16 / 20 / 24, in us by scan and by
         // runs: 40 layers 14.4 15.1 16.6 18.0 19.4 and 15.8 15.9 16.7 16.7 16.7, 65 layers 17.0 17.7 19.2 20.6 22.1 and 20.7 20.7 22.1 22.0
-        // 22.0, 100 layers (from 12 on) 21.3 23.6 26.0 28.3 and 21.9 23.2 23.2 23.1.  Whether a row has a longer one is told while the
+        // 22.0, 100 layers (from 12 on) 21.3 23.6 26.0 28.3 and 21.9 23.2 23.2 23.1.  Whether a row may have a longer one is told while the
         // tables are staged, not row by row, and a single candidate at a time took 15 % more: what binds is the one wave's latency.
         if (!__any((has_long >> s) & 1u)) {
             for (int e = lane; e <= L; e += 64) {

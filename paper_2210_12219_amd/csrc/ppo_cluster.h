@@ -35,9 +35,11 @@ struct ClusterLayout {
     int L, n, npairs, nq, rs;                       // rs: entries per row of A: 0..L-1 (entry L is never finite
                                                     // and not stored), rounded up to even
     uint32_t hi_off, qc_off, dec_off, qv_off, ord_off, img_off, stride;   // bytes within one instance's tables
+    bool may_be_reduced;                            // the call's instances may be searched on fewer nodes and cuts
 
-    __host__ __device__ static ClusterLayout make(int L, int n) {
+    __host__ __device__ static ClusterLayout make(int L, int n, bool may_be_reduced = false) {
         ClusterLayout y;
+        y.may_be_reduced = may_be_reduced;
         y.L = L;
         y.n = n;
         y.npairs = n * (n - 1) / 2;
@@ -89,9 +91,10 @@ struct ClusterRecord {
 };
 static_assert(sizeof(ClusterRecord) <= 32, "the record lies in the last 32 bytes of the image");
 
-// What the tables at `base` (of an instance whose slice has the layout `whole`) are made of.
+// What the tables at `base` (of an instance whose slice has the layout `whole`) are made of.  (Where the call says that it is all of
+// it, the flag is not read: it took 3 of 50 us of calls with one segment.)
 __device__ __forceinline__ bool cluster_reduced(const ClusterLayout& whole, const unsigned char* base) {
-    return __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(base + whole.flag_off())) != 0;
+    return whole.may_be_reduced && __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(base + whole.flag_off())) != 0;
 }
 __device__ __forceinline__ ClusterLayout cluster_layout(const ClusterLayout& whole, const unsigned char* base) {
     if (!cluster_reduced(whole, base)) return whole;

@@ -767,16 +767,17 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
 // leave out: short of memory on the nine nodes, 16 nodes and 100 layers 252 / 271, 288 of 11 nodes 795 / 827; one transfer size
 // and bandwidth, 16 nodes and 50 layers 223 / 262, 64 of 13 nodes 463 / 500.  With fewer segments allowed than nodes the upper
 // levels are not searched, and those that are start from the nodes' number, which the host would not know.
+static bool cluster_may_be_confined(int L, int n, int pmax) { return pmax == n && n >= (L >= 24 ? 11 : 13); }
 static bool cluster_confined(int L, int n, int n_inst, int pmax) {
-    return pmax == n && (n >= 16 || (n >= (L >= 24 ? 11 : 13) && ((unsigned long long)n_inst * (unsigned long long)n << (n - 1)) >= 800000ull));
+    return cluster_may_be_confined(L, n, pmax) && (n >= 16 || ((unsigned long long)n_inst * (unsigned long long)n << (n - 1)) >= 800000ull);
 }
 
 hipError_t launch_cluster_tables(const float* t, const float* m, const float* M, const float* B, int L, int n,
                                  int n_inst, int pmax, void* ws, hipStream_t stream) {
-    const ClusterLayout y = ClusterLayout::make(L, n);
+    const ClusterLayout y = ClusterLayout::make(L, n, cluster_confined(L, n, n_inst, pmax));
     unsigned char* w = static_cast<unsigned char*>(ws);
     hipError_t e;
-    if (cluster_confined(L, n, n_inst, pmax)) {
+    if (y.may_be_reduced) {
         e = launch_cluster_reduce(t, m, M, B, y, n_inst, w, stream);
     } else {
         hipLaunchKernelGGL(cluster_tables_kernel, dim3(n_inst), dim3(kClPreThreads), 0, stream, t, m, M, B, y, w);
@@ -827,7 +828,8 @@ static const std::array<ClLevelLaunch, PPO_CLUSTER_MAX_N> kClLevelLaunch =
 
 hipError_t launch_cluster_solve(int L, int n, int n_inst, int pmax, const void* ws, void* rows, float* beta_out,
                                 int32_t* segs_out, int32_t* cuts_out, int32_t* order_out, hipStream_t stream) {
-    const ClusterLayout y = ClusterLayout::make(L, n);
+    // (the tables may have been made for more instances at once than are searched here: their flag says)
+    const ClusterLayout y = ClusterLayout::make(L, n, cluster_may_be_confined(L, n, pmax));
     const unsigned char* w = static_cast<const unsigned char*>(ws);
     uint16_t* r = static_cast<uint16_t*>(rows);
     const ClusterLds lds = ClusterLds::choose(y);

@@ -91,16 +91,23 @@ struct ClusterRecord {
 };
 static_assert(sizeof(ClusterRecord) <= 32, "the record lies in the last 32 bytes of the image");
 
-// What the tables at `base` (of an instance whose slice has the layout `whole`) are made of.  (Where the call says that it is all of
-// it, the flag is not read: it took 3 of 50 us of calls with one segment.)
-__device__ __forceinline__ bool cluster_reduced(const ClusterLayout& whole, const unsigned char* base) {
-    return whole.may_be_reduced && __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(base + whole.flag_off())) != 0;
+// What the tables at `base` (of an instance whose slice has the layout `whole`) are made of.  The flag is always written.  The
+// kernels that run once a call do not read it where the call says that everything is searched (calls with one segment, which have
+// one level); the levels just read it: asking first made every level of a confined search 0.1 to 0.2 us longer (one cluster of 20
+// nodes 316 us a call so, 320 without the question anywhere, 1.3 % more with it in the levels too; 32 of 15 nodes 494, 493 and 497).
+__device__ __forceinline__ bool cluster_flag(const ClusterLayout& whole, const unsigned char* base) {
+    return __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(base + whole.flag_off())) != 0;
 }
-__device__ __forceinline__ ClusterLayout cluster_layout(const ClusterLayout& whole, const unsigned char* base) {
-    if (!cluster_reduced(whole, base)) return whole;
+__device__ __forceinline__ bool cluster_reduced(const ClusterLayout& whole, const unsigned char* base) {
+    return whole.may_be_reduced && cluster_flag(whole, base);
+}
+__device__ __forceinline__ ClusterLayout cluster_part_layout(const ClusterLayout& whole, const unsigned char* base) {
     const ClusterRecord r = *reinterpret_cast<const ClusterRecord*>(base + whole.record_off());
     return ClusterLayout::make(__builtin_amdgcn_readfirstlane(__popcll(r.cuts[0]) + __popcll(r.cuts[1]) + 1),
                                __builtin_amdgcn_readfirstlane(__popc(r.nodes)));
+}
+__device__ __forceinline__ ClusterLayout cluster_layout(const ClusterLayout& whole, const unsigned char* base) {
+    return cluster_reduced(whole, base) ? cluster_part_layout(whole, base) : whole;
 }
 
 // Tables of an instance on the nodes and cuts that can matter, where every node may be used or not: what

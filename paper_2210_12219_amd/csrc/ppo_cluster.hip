@@ -370,8 +370,8 @@ __global__ __launch_bounds__(1024, 8) void cluster_level_kernel(ClusterLayout y,
     const uint32_t* query = reinterpret_cast<const uint32_t*>(cl_smem + lds.query_off);
     uint32_t* run32 = reinterpret_cast<uint32_t*>(cl_smem + lds.run_off) + wave * cluster_run_dwords(MODE);
     uint32_t* A32 = reinterpret_cast<uint32_t*>(rows) + (size_t)inst * (y.rows_per_instance() * rd);
-    if (cluster_reduced(y, base)) {
-        const ClusterLayout part = cluster_layout(y, base);
+    if (cluster_flag(y, base)) {
+        const ClusterLayout part = cluster_part_layout(y, base);
         if (C >= part.n) return;
         // as many waves as have a set to work on
         // entries 0 .. L of a set in its lanes

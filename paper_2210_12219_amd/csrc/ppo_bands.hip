@@ -26,11 +26,11 @@
 // below counts as 0, everything above as +inf): a pass divides the range by 30,000, so there are at most three, and
 // after the last one "code <= code of beta*" says the same as "value <= beta*".
 //
-// What bounds it: instruction issue.  4096 x (96, 8) take 35,000 vector and 22,000 scalar instructions an instance, about half
+// What bounds it: instruction issue.  4096 x (96, 8) take 35,000 vector and 21,000 scalar instructions an instance, about half
 // of them in the levels (75 vector instructions for four rows of 25 entries, where a row of 96 took 47 by itself); the rest is
 // what every wave of a workgroup works out for itself in each phase, and it grows with the waves.  The phases that one wave
 // or a few work alone (sums, windows, answer) overlap with those of the other workgroups of the compute unit.
-// Measured, before and now: 4096 x (96, 8) of transformers 624 / 354 us, of random chains 739 / 583, 1024 x (65, 8) 218 / 143,
+// Measured, before and now: 4096 x (96, 8) of transformers 624 / 347 to 354 us, of random chains 739 / 583, 1024 x (65, 8) 218 / 143,
 // 4096 x (80, 6) 311 / 227; staged (tables and final stage included) 64 x (100, 10) 260 / 197, 1024 x (50, 6) 180 / 125, 300 x
 // (20, 10) 313 / 159.  (Memory of 1.2 to 1.3 times what the chain needs; of twice and four times: bands_whole_rows.)
 #include "ppo_sets.h"

@@ -762,7 +762,7 @@ __global__ __launch_bounds__(kClPreThreads) void cluster_image_kernel(ClusterLay
 // the levels, 10 to 15 where nine nodes do not hold the chain, and may leave little out: paper-shaped clusters of 16 MB devices
 // keep all their nodes.  Measured in us, without and with it: one cluster of 16 such nodes 239 / 234, 16 of 13 nodes 236 / 224, 128
 // of 11 nodes 277 / 229, but 128 of 10 nodes 177 / 185, 16 of 12 nodes 162 / 187, one of 14 nodes 176 / 193.  Mixed
-// capacities, 100 layers: one of 20 nodes 2040 / 120 to 250, one of 16 nodes 275 to 309 / 95 to 178, 128 of 11 nodes 418 / 218; 20 layers: 64 of
+// capacities, 100 layers: one of 20 nodes 2040 / 120 to 320, one of 16 nodes 275 to 309 / 95 to 178, 128 of 11 nodes 418 / 218; 20 layers: 64 of
 // 13 nodes 390 / 238, but 132 of 12 nodes 447 / 500 and 288 of 11 nodes 455 / 541 (26 layers: 474 / 250 and 478 / 367).  Nothing to
 // leave out: short of memory on the nine nodes, 16 nodes and 100 layers 252 / 271, 288 of 11 nodes 795 / 827; one transfer size
 // and bandwidth, 16 nodes and 50 layers 223 / 262, 64 of 13 nodes 463 / 500.  With fewer segments allowed than nodes the upper

@@ -19,7 +19,7 @@
 //
 // What bounds these two: the one workgroup's instruction issue in the levels of the first (2304 rows, 22 of its 30 us) and
 // chains of LDS reads and barriers in the second (24 to 28 us).  One cluster of 20 nodes and 100 layers: 2040 us a call without
-// them, 120 to 250 with them, by how much can be left out; 32 of 15 devices and 50 layers: 827 and 480 to 500 (no node and two
+// them, 120 to 320 with them, by how much can be left out; 32 of 15 devices and 50 layers: 827 and 480 to 500 (no node and two
 // thirds of the layers left out).  What they cost where nothing can be: beside cluster_confined and few_confined.
 #include "ppo_cluster.h"
 #include "ppo_sets.h"
